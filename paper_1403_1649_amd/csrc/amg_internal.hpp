@@ -449,8 +449,8 @@ bool tune_cache_get(const TuneKey& k, Level::Tune* t);
 void tune_cache_put(const TuneKey& k, const Level::Tune& t);
 int mlp_num_params();
 void mlp_features(Hierarchy& h, const Level& lv, int level, float* F, double* beta);
-void mlp_omega(Hierarchy& h, const Level& lv, const float* F, const double* beta, const float* wdev, double* omega,
-               double* wdinv, float* wdinv32, double* sig);
+void mlp_omega(Hierarchy& h, Arena& tmp, const Level& lv, const float* F, const double* beta, const float* wdev,
+               double* omega, double* wdinv, float* wdinv32, double* sig);
 double mlp_loss_grad(Hierarchy& h, Arena& tmp, const Level& lv, int level, const float* wdev, int S_rand,
                      uint32_t seed, const double* extra, int S_extra, const double* omega_fixed, float* grad,
                      int accumulate, bool raw_extra = false);

@@ -491,7 +491,7 @@ int32_t amg_mlp_omega(const amg_hierarchy* H, int32_t k, const float* w, double*
     float* F = tmp.alloc_n<float>((size_t)lv.n * 9);
     double* beta = tmp.alloc_n<double>(lv.n);
     amg::mlp_features(h, lv, k, F, beta);
-    amg::mlp_omega(h, lv, F, beta, w, omega, nullptr, nullptr, nullptr);
+    amg::mlp_omega(h, tmp, lv, F, beta, w, omega, nullptr, nullptr, nullptr);
     h.stream = keep;
     AMG_HIP(hipGetLastError());
   });

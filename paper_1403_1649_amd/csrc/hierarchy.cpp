@@ -913,7 +913,7 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
         float* F = vt.alloc_n<float>((size_t)n * 9);
         double* beta = vt.alloc_n<double>(n);
         mlp_features(h, lv, k, F, beta);
-        mlp_omega(h, lv, F, beta, h.mlp_w, nullptr, lv.wdinv, lv.wdinv32, nullptr);
+        mlp_omega(h, vt, lv, F, beta, h.mlp_w, nullptr, lv.wdinv, lv.wdinv32, nullptr);
         lv.learned = 1;
       }
       sy.wait_and_check();

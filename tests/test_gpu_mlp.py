@@ -262,3 +262,28 @@ def test_trained_network_gains_over_plain_jacobi():
         assert itl < itp, (A.n, itl, itp)
         hp.close()
         hl.close()
+
+
+@pytest.mark.parametrize("shape, nrand, nextra", [((4, 4, 4), 0, 1), ((5, 5, 5), 0, 3), ((3, 7, 9), 2, 3),
+                                                  ((8, 8, 8), 0, 64), ((9, 9, 9), 33, 0)])
+def test_loss_and_gradient_at_tile_edges(shape, nrand, nextra):
+    """Rows that fill, end inside or span several 64-row tiles and two-wave
+    blocks, and sample counts that divide a 256-thread block or do not (1 to
+    64), with samples taken as given beside projected ones."""
+    A = P.hetero3d(max(shape), seed=21) if len(set(shape)) == 1 else P.poisson2d(shape[2] * shape[0], shape[1])
+    h = _setup(A, coarse_max=8)
+    w = _weights(6)
+    wd = torch.from_numpy(w).cuda()
+    ex = h.export_level(0)
+    S = O.validate_csr(ex["row_ptr"], ex["col"], ex["val"])
+    F = amg.mlp_features(h, 0).cpu().numpy().astype(np.float64)
+    extra = np.random.default_rng(4).uniform(-1.0, 1.0, (A.n, nextra))
+    E = np.concatenate([M.projected_errors(S, ex["agg"], ex["pval"], ex["nc"], nrand, 5), extra], axis=1)
+    g = torch.zeros_like(wd)
+    ed = torch.from_numpy(extra).cuda() if nextra else None
+    loss = amg.mlp_loss_grad(h, 0, wd, nrand, 5, ed, g, raw_extra=True)
+    lo, dlo, go, dgo = MB.loss_grad_bounds(w.astype(np.float64), S, F, E)
+    assert abs(loss - lo) <= 1.5 * dlo
+    err = np.abs(g.cpu().numpy().astype(np.float64) - go)
+    assert np.all(err <= 1.5 * dgo), f"gradient off by {np.max(err / dgo):.3g} of its bound"
+    assert amg.mlp_loss_grad(h, 0, wd, nrand, 5, ed, None, raw_extra=True) == loss
