@@ -157,6 +157,19 @@ struct Level {
   float* rval32 = nullptr;
   int nr = 0;
   int rlpr = 8;                // lanes per aggregate of the restriction kernel
+  // post-smoothing operator T_k = (I - W_k A_k) P_k in CSR over the fine rows
+  // (damped Jacobi, plain or learned): with y = W b + W (b - A W b) written by
+  // the pre-smoothing, the corrected and post-smoothed iterate is y + T_k e, so
+  // the cycle takes A_k once instead of twice (null: the level has a row too
+  // long for the kernel that builds it, and post-smooths with A_k)
+  int* tp = nullptr;
+  int* tc = nullptr;
+  int16_t* tc16 = nullptr;     // the columns as offsets from their 64-row group's tbase, where all fit
+  int* tbase = nullptr;
+  double* tv = nullptr;
+  float* tv32 = nullptr;
+  int tnnz = 0;
+  int tlpr = 4;                // lanes per row of the product with T_k; < 0: streamed, -tlpr per lane
   double omega = 0.0, rho = 0.0;
   double* wdinv = nullptr;     // omega / a_ii (or omega_i / a_ii with learned weights)
   int learned = 0;             // learned weights in use on this level
@@ -165,6 +178,7 @@ struct Level {
   // solve scratch (typed by the cycle precision; size n or n_{k+1})
   void* r = nullptr;           // fine residual
   void* xt = nullptr;          // fine iterate inside the cycle
+  void* y = nullptr;           // the iterate after both smoothing steps, where xt is still gathered
   void* rc = nullptr;          // restricted residual
   void* c = nullptr;           // first inner correction (or the V-cycle correction)
   void* v = nullptr;           // A_{k+1} c
@@ -421,6 +435,23 @@ void launch_galerkin_finish(const GalerkinScratch& g, int nc, const int* agg_ptr
 void launch_dense_inverse(int n, const int* rp, const int* ci, const double* val, double* work,
                           double* inv, float* inv32, int* sync, int* err, hipStream_t s);
 
+// smooth_interp.hip: the post-smoothing operator T = (I - W A) P
+// cnt: row lengths; *flags: what a level's T has, shifted by `shift`
+constexpr int kTFlagBits = 5;
+enum : int {
+  kTLongRow = 1,    // a row too long to build
+  kTFar = 2,        // a column beyond 16 bits of its 64-row group's base
+  kTGroup256 = 4,   // a 64-row group of more than 256 entries
+  kTGroup320 = 8,
+  kTGroup512 = 16,
+};
+void launch_tsmooth_count(int n, const int* rp, const int* ci, const int* agg, int* cnt, int* flags, int shift,
+                          hipStream_t s);
+// levels above this size merge a row per lane (and know their groups' sizes);
+// only they are streamed by the post-smoothing
+constexpr int kTsmoothRows = 65536;
+void launch_tsmooth_fill(const Level& lv, hipStream_t s);
+
 // arnoldi / reductions (solve_kernels.hip)
 // Reduction context of the solve-phase kernels: per-block partials and the
 // arrival counter of the in-kernel finalize (zero between kernels).
@@ -487,6 +518,7 @@ void spmv_sell_f64(Hierarchy& h, const amg_csr& A, const double* x, double* y, b
 void spmv_f64(int n, int nnz, const int* rp, const int* ci, const double* val, const double* x, double* y,
               int lpr, hipStream_t s);
 int pick_lanes_per_row(int n, int nnz);
+int post_lanes(int n, int nnz, int flags);
 
 // noalloc.hip: the Galerkin product with its scratch in a static device array;
 // returns AMG_EINVAL (nnz_c set, col_c / val_c untouched) when cap < nnz_c.

@@ -234,6 +234,55 @@ struct Sync {
   }
 };
 
+// Whether the level post-smooths by T_k = (I - W A) P (damped Jacobi weights).
+bool jacobi_smoothed(const Hierarchy& h) {
+  return h.opt.smoother != AMG_SMOOTHER_CHEBYSHEV && h.opt.smoother != AMG_SMOOTHER_MCSGS;
+}
+
+// The pattern of every level's T_k: row lengths, their scan, and the sizes
+// read back together; the values wait for the Jacobi weights (tsmooth_values).
+void tsmooth_patterns(Hierarchy& h, Arena& tmp, Sync& sy) {
+  if (!jacobi_smoothed(h)) return;
+  const int L = h.L();
+  constexpr int kBatch = 6;   // levels per read-back: their sizes and one word of flags
+  int* flags = tmp.alloc_n<int>(std::max(L, 1));
+  launch_fill_int(L, flags, 0, h.stream);
+  for (int k0 = 0; k0 < L; k0 += kBatch) {
+    const int k1 = std::min(L, k0 + kBatch);
+    for (int k = k0; k < k1; ++k) {
+      Level& lv = h.levels[k];
+      int* cnt = tmp.alloc_n<int>(lv.n);
+      launch_tsmooth_count(lv.n, lv.rp, lv.ci, lv.agg, cnt, flags + k0, kTFlagBits * (k - k0), h.stream);
+      lv.tp = h.arena.alloc_n<int>((size_t)lv.n + 1);
+      scan_to_ptr(cnt, lv.tp, lv.n, h.scan, h.stream);
+      sy.fetch(lv.tp + lv.n, k - k0);
+    }
+    sy.fetch(flags + k0, kBatch);
+    sy.wait_and_check();
+    for (int k = k0; k < k1; ++k) {
+      Level& lv = h.levels[k];
+      lv.tnnz = sy.hp()[k - k0];
+      const int fl = sy.hp()[kBatch] >> (kTFlagBits * (k - k0)) & ((1 << kTFlagBits) - 1);
+      if (std::getenv("AMG_DEBUG"))
+        std::fprintf(stderr, "amg: level %d T nnz=%d of A %d, flags %d\n", k, lv.tnnz, lv.nnz, fl);
+      if (fl & kTLongRow) {
+        lv.tp = nullptr;
+        continue;
+      }
+      const size_t m = (size_t)std::max(lv.tnnz, 1);
+      lv.tlpr = post_lanes(lv.n, lv.tnnz, fl);
+      if (lv.tlpr < 0 && !(fl & kTFar)) {
+        lv.tc16 = h.arena.alloc_n<int16_t>(m);
+        lv.tbase = h.arena.alloc_n<int>(((size_t)lv.n + 63) / 64);
+      } else {
+        lv.tc = h.arena.alloc_n<int>(m);
+      }
+      if (h.mixed()) lv.tv32 = h.arena.alloc_n<float>(m);
+      else lv.tv = h.arena.alloc_n<double>(m);
+    }
+  }
+}
+
 void alloc_solve_vectors(Hierarchy& h) {
   const size_t es = h.mixed() ? sizeof(float) : sizeof(double);
   const int L = h.L();
@@ -244,6 +293,7 @@ void alloc_solve_vectors(Hierarchy& h) {
     lv.xt = h.arena.alloc(n * es);
     lv.rc = h.arena.alloc(nc * es);
     lv.c = h.arena.alloc(nc * es);
+    if (lv.tp) lv.y = h.arena.alloc(n * es);
     if (h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV) {
       lv.cr = h.arena.alloc(n * es);
       lv.cd0 = h.arena.alloc(n * es);
@@ -431,6 +481,12 @@ void make_float_copies(Hierarchy& h) {
   }
 }
 }  // namespace
+
+// The values of every T_k for the current Jacobi weights.
+static void tsmooth_values(Hierarchy& h) {
+  for (int k = 0; k < h.L(); ++k)
+    if (h.levels[k].tp) launch_tsmooth_fill(h.levels[k], h.stream);
+}
 
 // Aggregate segments: members of aggregate I at agg_rows[agg_ptr[I]..agg_ptr[I+1]),
 // ascending.  Scratch from `tmp`.
@@ -678,6 +734,7 @@ static void judge_learned(Hierarchy& h, Arena& tmp) {
     Level& lv = h.levels[k];
     if (lv.learned) launch_jacobi_weights(lv.n, lv.omega, lv.diag, lv.wdinv, lv.wdinv32, s);
   }
+  tsmooth_values(h);
   probe(&h.judge_it_plain, &h.judge_rel_plain);
   const bool keep = h.judge_it_learned < h.judge_it_plain ||
                     (h.judge_it_learned == h.judge_it_plain && h.judge_rel_learned < h.judge_rel_plain);
@@ -693,6 +750,7 @@ static void judge_learned(Hierarchy& h, Arena& tmp) {
     if (keep32[k])
       AMG_HIP(hipMemcpyAsync(lv.wdinv32, keep32[k], (size_t)lv.n * sizeof(float), hipMemcpyDeviceToDevice, s));
   }
+  if (keep) tsmooth_values(h);
   AMG_HIP(hipStreamSynchronize(s));
 }
 
@@ -925,11 +983,13 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
   if (o.smoother == AMG_SMOOTHER_MCSGS)
     for (int k = 0; k < h.L(); ++k) color_level(h, tmp, h.levels[k], sy);
   if (h.mixed()) make_float_copies(h);
+  tsmooth_patterns(h, tmp, sy);
   alloc_solve_vectors(h);
   for (int k = 0; k < h.L(); ++k)
     if (h.levels[k].nslices == 0) build_sell(h, tmp, h.levels[k]);
-  sy.wait_and_check();
+  if (h.L() == 0 || !jacobi_smoothed(h)) sy.wait_and_check();   // else tsmooth_patterns has waited
   take_arnoldi();
+  tsmooth_values(h);
   using clk = std::chrono::steady_clock;
   const auto t_tune = clk::now();
   if (!(o.flags & AMG_FLAG_NO_TUNE)) autotune_levels(h);
@@ -1003,6 +1063,7 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
     arnoldi(h, lv, m, o.seed + 1, Q, w, Hh, wn);
     set_jacobi_weight(h, lv, m, Hh, wn);
   }
+  tsmooth_values(h);
   coarse_inverse(h, tmp, sy);
   sy.wait_and_check();
   if (repoint) h.multi.reset();   // the kept block workspace's graphs read level 0's old values

@@ -81,11 +81,19 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(Op op, const double* __r
 
 // y-side of a sparse row operation: Op provides
 //   static constexpr int NV;           number of fused reductions
+//   void begin();                      optional: device scalars read once, into the operation itself
 //   bool active() const;               kernel-wide enable
 //   void idle() const;                 run by thread 0 of block 0 when inactive
 //   T x(int j) const;                  the gathered operand
 //   void row(int i, T ax, double* acc) the epilogue of row i
 //   void finalize(const double* v)     totals of the reductions
+
+template <class Op>
+__device__ __forceinline__ auto op_begin(Op& op, int) -> decltype(op.begin(), void()) {
+  op.begin();
+}
+template <class Op>
+__device__ __forceinline__ void op_begin(Op&, long) {}
 
 // Blocks are dispatched round-robin over the 8 XCDs (each with its own L2).
 // The logical block index gives every XCD a contiguous run of blocks, and
@@ -149,6 +157,7 @@ __global__ void __launch_bounds__(kBlock) k_rows(int n, const int* __restrict__ 
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
+  op_begin(op, 0);
   constexpr int RPB = kBlock / LPR;
   const int lane = threadIdx.x & (LPR - 1);
   double acc[Op::NV > 0 ? Op::NV : 1];
@@ -190,6 +199,102 @@ __global__ void __launch_bounds__(kBlock) k_rows(int n, const int* __restrict__ 
   if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
 }
 
+// Orders a wave's own LDS writes before its later reads of other lanes' words
+// (and the reads before the next writes): the wave runs in step, so only the
+// compiler has to be held back.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// CSR rows streamed through LDS.  A wave takes groups of R consecutive rows of
+// at most 64 Q entries together (the caller's guarantee).  A group's entries
+// are one contiguous run, loaded coalesced, Q per lane; the products go to the
+// wave's LDS, and 64/R lanes sum each row there.  So there is no padding, no
+// idle lane on short rows, and every load instruction covers whole lines.
+// What bounds it otherwise is the chain row pointers -> columns -> gathers ->
+// sum: the loop keeps three groups in flight (the gathers of one, the columns
+// and values of the next, the row pointers of the one after, and the row
+// operands, Op::Pre, with the gathers), so a group costs one round trip.  All
+// loads are unconditional, at clamped positions, for the same reason.
+// Groups go to the XCDs in contiguous eighths, swept by the blocks of the XCD
+// side by side (block_steps, -1).
+// D16: columns as 16-bit offsets from the group's base column gbase[g].
+template <typename T, class Op, int R, int Q, bool D16, bool NT>
+__global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict__ rp, const void* __restrict__ cols,
+                                                   const int* __restrict__ gbase, const T* __restrict__ av, Op op,
+                                                   RedCtx rc) {
+  static_assert(R == 64 || R == 32, "rows per group");
+  if (!op.active()) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
+    return;
+  }
+  op_begin(op, 0);
+  constexpr int SPB = kBlock / kWave;
+  constexpr int LPR = kWave / R;
+  __shared__ T s_prod[SPB][kWave * Q];
+  double acc[Op::NV > 0 ? Op::NV : 1];
+#pragma unroll
+  for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int rl = lane & (R - 1), part = lane / R;   // this lane's row in the group, and its share of it
+  const int wv = threadIdx.x / kWave;
+  T* prod = s_prod[wv];
+  const int ngroups = (n + R - 1) / R;
+  const int steps = (ngroups + SPB - 1) / SPB;
+  const Steps st = block_steps(steps, -1);
+  struct Rows { int beg, end, cbase; };
+  struct Entries { int c[Q]; T v[Q]; };
+  auto rows_of = [&](int u) {   // groups past the end: an empty run at the matrix's end
+    Rows w;
+    const int grp = u < st.end ? min(u * SPB + wv, ngroups) : ngroups;
+    const int row = grp * R + rl;
+    w.beg = rp[min(row, n)];
+    w.end = rp[min(row + 1, n)];
+    w.cbase = D16 ? gbase[min(grp, ngroups - 1)] : 0;
+    return w;
+  };
+  auto entries_of = [&](const Rows& w) {
+    Entries t;
+    const int base = __builtin_amdgcn_readfirstlane(w.beg);
+    const int last = max(__builtin_amdgcn_readlane(w.end, R - 1) - 1, 0);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int k = min(base + q * kWave + lane, last);
+      if constexpr (D16) t.c[q] = w.cbase + (int)static_cast<const int16_t*>(cols)[k];
+      else t.c[q] = static_cast<const int*>(cols)[k];
+      if constexpr (NT) t.v[q] = __builtin_nontemporal_load(av + k);
+      else t.v[q] = av[k];
+    }
+    return t;
+  };
+  Rows r0 = rows_of(st.u), r1 = rows_of(st.u + st.inc);
+  Entries e0 = entries_of(r0);
+  for (int u = st.u; u < st.end; u += st.inc) {
+    const int row = (u * SPB + wv) * R + rl;
+    T xv[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) xv[q] = op.x(e0.c[q]);
+    const typename Op::Pre pre = op.pre(min(row, n - 1));
+    const Entries e1 = entries_of(r1);
+    const Rows r2 = rows_of(u + 2 * st.inc);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) prod[q * kWave + lane] = e0.v[q] * xv[q];
+    wave_lds_order();
+    const int base = __builtin_amdgcn_readfirstlane(r0.beg);
+    T sum = T(0);
+    for (int k = r0.beg - base + part; k < r0.end - base; k += LPR) sum += prod[k];
+    wave_lds_order();
+    if constexpr (LPR == 2) sum += __shfl_xor(sum, 32, kWave);
+    if (row < n && part == 0) op.row(row, sum, pre, acc);
+    r0 = r1;
+    r1 = r2;
+    e0 = e1;
+  }
+  if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
+}
+
 // Sliced ELL with slices of H rows (H = 64, 32 or 16): slice s holds the rows
 // of slots s*H .. s*H + H - 1 column-major, element (slot s*H + l, k) at
 // sl_ptr[s] + H k + l, padded with zero values that point at the row itself.
@@ -214,6 +319,7 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, int nslices, const int* 
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
+  op_begin(op, 0);
   double acc[Op::NV > 0 ? Op::NV : 1];
 #pragma unroll
   for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
@@ -332,6 +438,7 @@ __global__ void __launch_bounds__(kBlock) k_elem(int n, Op op, RedCtx rc) {
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
+  op_begin(op, 0);
   double acc[Op::NV > 0 ? Op::NV : 1];
 #pragma unroll
   for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
@@ -383,6 +490,16 @@ int resident_blocks(K k) {
   return g;
 }
 
+// Grid of a slice kernel over `steps` steps: one block per step up to the
+// resident cap, a multiple of 8 above 8 blocks (the XCD mapping).
+inline int step_grid(int steps, int resident) {
+  long g = steps;
+  if (g < 1) g = 1;
+  if (g > resident) g = resident;
+  if (g > 8) g &= ~7L;
+  return (int)g;
+}
+
 template <typename T, int LPR, class Op, bool D16 = false>
 void launch_rows_l(int n, const int* rp, const void* ci, const T* av, const Op& op, RedCtx rc, hipStream_t s) {
   int g = rows_grid(n, LPR, Op::NV > 0);
@@ -391,6 +508,20 @@ void launch_rows_l(int n, const int* rp, const void* ci, const T* av, const Op& 
   const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
   const RedCtx r2{rc.part, tail ? rc.ticket : nullptr};
   k_rows<T, LPR, Op, D16><<<g, kBlock, 0, s>>>(n, rp, ci, av, op, r2);
+  if constexpr (Op::NV > 0)
+    if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
+}
+
+// The streamed kernel (a step is four groups of R rows).  gbase non-null:
+// cols are 16-bit offsets.
+template <typename T, class Op, int R, int Q, bool D16, bool NT>
+void launch_stream_l(int n, const int* rp, const void* cols, const int* gbase, const T* av, const Op& op, RedCtx rc,
+                     hipStream_t s) {
+  constexpr int rows = R * (kBlock / kWave);
+  const int g = step_grid((n + rows - 1) / rows, resident_blocks(k_stream<T, Op, R, Q, D16, NT>));
+  const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
+  k_stream<T, Op, R, Q, D16, NT><<<g, kBlock, 0, s>>>(n, rp, cols, gbase, av, op,
+                                                      RedCtx{rc.part, tail ? rc.ticket : nullptr});
   if constexpr (Op::NV > 0)
     if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
 }
@@ -422,16 +553,6 @@ void launch_rows16(int n, int lpr, const int* rp, const int16_t* ci16, const T* 
   }
 }
 
-
-// Grid of a slice kernel over `steps` steps: one block per step up to the
-// resident cap, a multiple of 8 above 8 blocks (the XCD mapping).
-inline int step_grid(int steps, int resident) {
-  long g = steps;
-  if (g < 1) g = 1;
-  if (g > resident) g = resident;
-  if (g > 8) g &= ~7L;
-  return (int)g;
-}
 
 // sl_dcol non-null: the kernel reads the 16-bit column offsets instead of sl_col.
 

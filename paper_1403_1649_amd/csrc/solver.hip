@@ -60,6 +60,122 @@ struct OpPresmoothResid {
   __device__ void finalize(const double*) const {}
 };
 
+// The same for a level that post-smooths by T = (I - W A) P (Level::tp): the
+// second smoothing step goes out with the residual, y = x + w.*r.  From a zero
+// guess (y replaces the first step, which nobody reads), and on a first step
+// x = w.*b that the right-hand side's kernel has written (gathered, so y goes
+// to a vector of its own).
+// The iterate after two smoothing steps from zero: w b, then w (b - A w b) on
+// top, as one fused product in every kernel that forms it (the bits agree).
+__device__ __forceinline__ double two_steps(double w, double b, double r) { return __builtin_fma(w, r, w * b); }
+__device__ __forceinline__ float two_steps(float w, float b, float r) { return __builtin_fmaf(w, r, w * b); }
+template <typename T>
+struct OpPresmooth2 {
+  static constexpr int NV = 0;
+  Act a;
+  const T* b;
+  const T* wd;
+  T* y;
+  T* r;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ T x(int j) const { return wd[j] * b[j]; }
+  __device__ void row(int i, T ax, double*) const {
+    const T bi = b[i], wi = wd[i];
+    const T t = bi - ax;
+    r[i] = t;
+    y[i] = two_steps(wi, bi, t);
+  }
+  __device__ void finalize(const double*) const {}
+};
+template <typename T>
+struct OpResid2 {
+  static constexpr int NV = 0;
+  Act a;
+  const T* b;
+  const T* xv;
+  const T* wd;
+  T* r;
+  T* y;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ T x(int j) const { return xv[j]; }
+  __device__ void row(int i, T ax, double*) const {
+    const T t = b[i] - ax;
+    r[i] = t;
+    y[i] = xv[i] + wd[i] * t;
+  }
+  __device__ void finalize(const double*) const {}
+};
+
+// Correction and post-smoothing by T: x_out = y + T e, the row operation over
+// T's rows.  V-cycle: e = c; K-cycle: e = coef_c c (+ coef_d d).  At level 0 of
+// the outer iteration with z'q for the FCG beta (q given).
+template <typename T>
+struct CoarseV {
+  const T* c;
+  __device__ void begin() {}
+  __device__ T at(int J) const { return c[J]; }
+};
+template <typename T>
+struct CoarseK {
+  const T* c;
+  const T* d;
+  const double* K;
+  const int* F;
+  T cc, cd;
+  bool two;
+  __device__ void begin() {
+    cc = (T)K[kKCoefC];
+    two = F[1] != 0;
+    cd = two ? (T)K[kKCoefD] : T(0);
+  }
+  __device__ T at(int J) const { return two ? cc * c[J] + cd * d[J] : cc * c[J]; }
+};
+template <typename T, class Coarse>
+struct OpPostT {
+  static constexpr int NV = 0;
+  Act a;
+  const T* y;
+  T* xo;
+  Coarse e;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ void begin() { e.begin(); }
+  __device__ T x(int J) const { return e.at(J); }
+  __device__ void row(int i, T te, double*) const { xo[i] = y[i] + te; }
+  using Pre = T;
+  __device__ Pre pre(int i) const { return y[i]; }
+  __device__ void row(int i, T te, Pre yi, double*) const { xo[i] = yi + te; }
+  __device__ void finalize(const double*) const {}
+};
+template <typename T, class Coarse>
+struct OpPostTDot {
+  static constexpr int NV = 1;
+  Act a;
+  const T* y;
+  T* xo;
+  Coarse e;
+  const double* q;
+  double* sc;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ void begin() { e.begin(); }
+  __device__ T x(int J) const { return e.at(J); }
+  struct Pre {
+    T y;
+    double q;
+  };
+  __device__ Pre pre(int i) const { return Pre{y[i], q[i]}; }
+  __device__ void row(int i, T te, Pre p, double* acc) const {
+    const T z = p.y + te;
+    xo[i] = z;
+    acc[0] += (double)z * p.q;
+  }
+  __device__ void row(int i, T te, double* acc) const { row(i, te, pre(i), acc); }
+  __device__ void finalize(const double* s) const { sc[kScBeta] = -s[0] / sc[kScPQ]; }
+};
+
 // On small levels (at most kFuseCorrectionRows rows, where a launch costs more
 // than the work) the coarse-grid correction is applied where the
 // post-smoothing reads the iterate, x_j + P_j (correction of aggregate agg_j),
@@ -606,6 +722,29 @@ struct OpRestrict {   // rows of R = P^T (aggregates)
   __device__ void finalize(const double*) const {}
 };
 
+// the K-cycle's combination in place, c <- coef_c c (+ coef_d d), where a large
+// level's post-smoothing then gathers one coarse vector instead of two
+template <typename T>
+struct OpCombine {
+  static constexpr int NV = 0;
+  Act a;
+  T* c;
+  const T* d;
+  const double* K;
+  const int* F;
+  T cc, cd;
+  bool two;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ void begin() {
+    cc = (T)K[kKCoefC];
+    two = F[1] != 0;
+    cd = two ? (T)K[kKCoefD] : T(0);
+  }
+  __device__ void elem(int i, double*) const { c[i] = two ? cc * c[i] + cd * d[i] : cc * c[i]; }
+  __device__ void finalize(const double*) const {}
+};
+
 // prolongation x += P c
 template <typename T>
 struct OpProlong {
@@ -759,13 +898,15 @@ __global__ void __launch_bounds__(kBlock) k_gemv(int n, const T* __restrict__ A,
 // kernels' lane split), 256/LPR members at a time, the restricted value summed
 // over the members in segment order through LDS, so the fine residual is
 // never stored.  x = w.*b on the members, r_c(I) = sum_i R(I,i) (b_i - (A x)_i).
+// two: the members' iterate goes out after both smoothing steps (Level::tp).
 template <typename T, int LPR>
 __global__ void __launch_bounds__(256) k_presmooth_restrict(int nc, const int* __restrict__ agg_ptr,
                                                             const int* __restrict__ agg_rows,
                                                             const T* __restrict__ rv, const int* __restrict__ rp,
                                                             const int* __restrict__ ci, const T* __restrict__ av,
                                                             const T* __restrict__ b, const T* __restrict__ wd,
-                                                            T* __restrict__ xt, T* __restrict__ rcv, Act a) {
+                                                            T* __restrict__ xt, T* __restrict__ rcv, Act a,
+                                                            bool two) {
   if (!a.on()) return;
   constexpr int MPB = 256 / LPR;   // members per pass
   __shared__ T part[MPB];
@@ -787,9 +928,9 @@ __global__ void __launch_bounds__(256) k_presmooth_restrict(int nc, const int* _
       }
       sum = group_sum<LPR>(sum);
       if (lane == 0 && k < e) {
-        const T bi = b[i];
-        xt[i] = wd[i] * bi;
-        part[slot] = rv[k] * (bi - sum);
+        const T bi = b[i], wi = wd[i], ri = bi - sum;
+        xt[i] = two ? two_steps(wi, bi, ri) : wi * bi;
+        part[slot] = rv[k] * ri;
       }
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -814,6 +955,9 @@ template <> const float* rvals<float>(const Level& l) { return l.rval32; }
 template <typename T> const T* pvals(const Level& l);
 template <> const double* pvals<double>(const Level& l) { return l.pval; }
 template <> const float* pvals<float>(const Level& l) { return l.pval32; }
+template <typename T> const T* tvals(const Level& l);
+template <> const double* tvals<double>(const Level& l) { return l.tv; }
+template <> const float* tvals<float>(const Level& l) { return l.tv32; }
 template <typename T> const T* cinv(const Hierarchy& h);
 template <> const double* cinv<double>(const Hierarchy& h) { return h.cinv; }
 template <> const float* cinv<float>(const Hierarchy& h) { return h.cinv32; }
@@ -907,11 +1051,13 @@ struct TailLevel {
   const int* agg_ptr;
   const int* agg_rows;
   const T* rv;
-  const int* agg;
-  const T* pv;
+  const int* tp;    // T = (I - W A) P
+  const int* tc;
+  const T* tv;
+  int tlpr;
   const T* wd;
   const T* b;   // right-hand side (written in this launch except on the first level)
-  T* xt;        // pre-smoothed iterate
+  T* xt;        // iterate after both smoothing steps
   T* rc;        // restricted residual = right-hand side of the next level
   T* c;         // correction = iterate of the next level
   T* xo;        // smoothed output
@@ -960,9 +1106,9 @@ __device__ void tail_presmooth(const TailLevel<T>& L, bool first, int I0, int I1
       }
       sum = group_sum<LPR>(sum);
       if (lane == 0 && k < e) {
-        const T bi = tail_ldb(L.b + i, first);
-        L.xt[i] = L.wd[i] * bi;
-        part[slot] = L.rv[k] * (bi - sum);
+        const T bi = tail_ldb(L.b + i, first), wi = L.wd[i], ri = bi - sum;
+        L.xt[i] = two_steps(wi, bi, ri);
+        part[slot] = L.rv[k] * ri;
       }
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -975,37 +1121,36 @@ __device__ void tail_presmooth(const TailLevel<T>& L, bool first, int I0, int I1
   }
 }
 
-// row groups [g0, g1) of a level: the arithmetic of k_rows with
-// OpResidSmooth<T, CorrV<T>> (x_j = xt_j + P_j c_agg(j))
+// row groups [g0, g1) of a level: the arithmetic of k_rows with OpPostT<T,
+// CoarseV<T>> (x_out = y + T c)
 template <typename T, int LPR>
-__device__ void tail_postsmooth(const TailLevel<T>& L, bool first, int g0, int g1) {
+__device__ void tail_postsmooth(const TailLevel<T>& L, int g0, int g1) {
   constexpr int RPB = 256 / LPR;
   const int lane = threadIdx.x & (LPR - 1);
-  auto corr = [&](int j) { return tail_ld(L.xt + j) + L.pv[j] * tail_ld(L.c + L.agg[j]); };
   for (int g = g0; g < g1; ++g) {
     const int row = g * RPB + threadIdx.x / LPR;
     T sum = T(0);
     if (row < L.n) {
-      const int s = L.rp[row], e = L.rp[row + 1];
+      const int s = L.tp[row], e = L.tp[row + 1];
       for (int k0 = s + lane; k0 < e; k0 += 4 * LPR) {
         int c[4];
         T v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int k = k0 + q * LPR;
-          c[q] = k < e ? L.ci[k] : 0;
-          v[q] = k < e ? L.av[k] : T(0);
+          c[q] = k < e ? L.tc[k] : 0;
+          v[q] = k < e ? L.tv[k] : T(0);
         }
         T xv[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) xv[q] = k0 + q * LPR < e ? corr(c[q]) : T(0);
+        for (int q = 0; q < 4; ++q) xv[q] = k0 + q * LPR < e ? tail_ld(L.c + c[q]) : T(0);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           if (k0 + q * LPR < e) sum += v[q] * xv[q];
       }
     }
     sum = group_sum<LPR>(sum);
-    if (row < L.n && lane == 0) L.xo[row] = corr(row) + L.wd[row] * (tail_ldb(L.b + row, first) - sum);
+    if (row < L.n && lane == 0) L.xo[row] = tail_ld(L.xt + row) + sum;
   }
 }
 
@@ -1062,12 +1207,11 @@ __global__ void __launch_bounds__(256) k_vtail(TailArgs<T> a, Act act) {
     } else {                                // residual + post-smoothing + prolongation, up
       const int q = a.nlev - 1 - (p - a.nlev - 1);
       const TailLevel<T>& L = a.lv[q];
-      const int rpb = 256 / L.lpr;
+      const int rpb = 256 / L.tlpr;
       const int groups = (L.n + rpb - 1) / rpb;
       const int g0 = it * kTailGroupsPerItem, g1 = min(groups, g0 + kTailGroupsPerItem);
-      if (L.lpr == 8) tail_postsmooth<T, 8>(L, q == 0, g0, g1);
-      else if (L.lpr == 16) tail_postsmooth<T, 16>(L, q == 0, g0, g1);
-      else tail_postsmooth<T, 32>(L, q == 0, g0, g1);
+      if (L.tlpr == 4) tail_postsmooth<T, 4>(L, g0, g1);
+      else tail_postsmooth<T, 8>(L, g0, g1);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1097,7 +1241,9 @@ int tail_first(const Hierarchy& h) {
   while (k0 - 1 >= 1 && k0 - 1 >= h.opt.kcycle_levels) {
     const Level& lv = h.levels[k0 - 1];
     const int lpr = tune_of<T>(lv).lpr;
-    if (lv.n > kFuseCorrectionRows || (lpr != 8 && lpr != 16 && lpr != 32)) break;
+    if (lv.n > kFuseCorrectionRows || (lpr != 8 && lpr != 16 && lpr != 32) || !lv.tp ||
+        (lv.tlpr != 4 && lv.tlpr != 8))
+      break;
     --k0;
   }
   if (L - k0 > kTailMax) k0 = L - kTailMax;
@@ -1130,8 +1276,10 @@ bool vtail(Hierarchy& h, int k0, const T* b, T* xo, const int* act) {
     t.agg_ptr = lv.agg_ptr;
     t.agg_rows = lv.agg_rows;
     t.rv = rvals<T>(lv);
-    t.agg = lv.agg;
-    t.pv = pvals<T>(lv);
+    t.tp = lv.tp;
+    t.tc = lv.tc;
+    t.tv = tvals<T>(lv);
+    t.tlpr = lv.tlpr;
     t.wd = wdinv<T>(lv);
     t.b = q == 0 ? b : static_cast<const T*>(h.levels[k0 + q - 1].rc);
     t.xt = static_cast<T*>(lv.xt);
@@ -1142,7 +1290,7 @@ bool vtail(Hierarchy& h, int k0, const T* b, T* xo, const int* act) {
   }
   phase((a.ncoarse + kBlock / kWave - 1) / (kBlock / kWave));
   for (int q = a.nlev - 1; q >= 0; --q) {
-    const int rpb = 256 / a.lv[q].lpr;
+    const int rpb = 256 / a.lv[q].tlpr;
     const int groups = (a.lv[q].n + rpb - 1) / rpb;
     phase((groups + kTailGroupsPerItem - 1) / kTailGroupsPerItem);
   }
@@ -1267,6 +1415,40 @@ void post_smooth(Hierarchy& h, const Level& lv, int k, Act A, const T* b, const 
   }
 }
 
+// A row operation on T_k: streamed (tlpr <= 0: -tlpr entries per lane and
+// group), or with a few lanes per row.
+template <typename T, class Op>
+void launch_post(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
+  if (lv.tlpr > 0) {
+    launch_rows<T>(lv.n, lv.tlpr, lv.tp, lv.tc, tvals<T>(lv), op, rc, s);
+    return;
+  }
+  const void* cols = lv.tc16 ? static_cast<const void*>(lv.tc16) : static_cast<const void*>(lv.tc);
+  auto go = [&](auto q) {
+    constexpr int Q = decltype(q)::value;
+    if (lv.tc16) launch_stream_l<T, Op, 64, Q, true, false>(lv.n, lv.tp, cols, lv.tbase, tvals<T>(lv), op, rc, s);
+    else launch_stream_l<T, Op, 64, Q, false, false>(lv.n, lv.tp, cols, nullptr, tvals<T>(lv), op, rc, s);
+  };
+  if (lv.tlpr == -4) go(std::integral_constant<int, 4>());
+  else if (lv.tlpr == -5) go(std::integral_constant<int, 5>());
+  else go(std::integral_constant<int, 8>());
+}
+
+// Correction and post-smoothing of a level by T: xo = y + T e (and z'q).
+template <typename T, class Coarse>
+void post_smooth_t(Hierarchy& h, const Level& lv, int k, Act A, const T* y, T* xo, Coarse e, const double* fuse_q,
+                   RedCtx rc) {
+  const Level* lp = &lv;
+  const bool sel = k == 0 && h.opt.probe == AMG_PROBE_L0_POSTSMOOTH;
+  if (fuse_q) {
+    const OpPostTDot<T, Coarse> op{A, y, xo, e, fuse_q, h.d_sc};
+    probe_point(h, sel, [=](hipStream_t st) { launch_post<T>(*lp, op, rc, st); });
+  } else {
+    const OpPostT<T, Coarse> op{A, y, xo, e};
+    probe_point(h, sel, [=](hipStream_t st) { launch_post<T>(*lp, op, rc, st); });
+  }
+}
+
 // Whether cycle(k) pre-smooths with the row kernel of its level from a zero
 // guess (damped Jacobi, a level that is not the coarsest and does not take the
 // fused pre-smoothing + restriction of small V-cycle levels): then whoever
@@ -1306,6 +1488,8 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
   const bool kcyc = k < h.opt.kcycle_levels && k + 1 < L;
   const bool cheb = h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV;
   const bool sgs = h.opt.smoother == AMG_SMOOTHER_MCSGS;
+  const bool byT = lv.tp != nullptr;   // post-smoothing by T = (I - W A) P
+  const T* y = xt;                     // then the iterate after both smoothing steps
   if (cheb || sgs) {
     if (cheb) {
       cheb_pre<T>(h, lv, k, A, b, xt, r);
@@ -1319,16 +1503,23 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
     const int grid = lv.nc < 1 ? 1 : lv.nc < 65536 ? lv.nc : 65536;
     with_lanes(lpr, [&](auto g) {
       k_presmooth_restrict<T, decltype(g)::value><<<grid, 256, 0, s>>>(
-          lv.nc, lv.agg_ptr, lv.agg_rows, rvals<T>(lv), lv.rp, lv.ci, vals<T>(lv), b, wd, xt, rcv, A);
+          lv.nc, lv.agg_ptr, lv.agg_rows, rvals<T>(lv), lv.rp, lv.ci, vals<T>(lv), b, wd, xt, rcv, A, byT);
     });
   } else {
     const Level* lp = &lv;
-    if (x0) {
+    const bool sel = k == 0 && h.opt.probe == AMG_PROBE_L0_PRESMOOTH;
+    if (x0 && byT) {
+      T* y2 = static_cast<T*>(lv.y);
+      launch_level<T>(lv, OpResid2<T>{A, b, xt, wd, r, y2}, rc, s);
+      y = y2;
+    } else if (x0) {
       launch_level<T>(lv, OpResid<T>{A, b, xt, r}, rc, s);
+    } else if (byT) {
+      const OpPresmooth2<T> op{A, b, wd, xt, r};
+      probe_point(h, sel, [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
     } else {
       const OpPresmoothResid<T> op{A, b, wd, xt, r};
-      probe_point(h, k == 0 && h.opt.probe == AMG_PROBE_L0_PRESMOOTH,
-                  [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
+      probe_point(h, sel, [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
     }
   }
   // the next level's first smoothing step goes out with its right-hand side
@@ -1341,7 +1532,9 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
   if (!kcyc) {
     if (k + 1 == L) coarse_solve<T>(h, rcv, c, act);
     else cycle<T>(h, k + 1, rcv, c, act, nullptr, nx0);
-    if (lv.n <= kFuseCorrectionRows) {
+    if (byT) {
+      post_smooth_t<T>(h, lv, k, A, y, xo, CoarseV<T>{c}, fuse_q, rc);
+    } else if (lv.n <= kFuseCorrectionRows) {
       post_smooth<T>(h, lv, k, A, b, xt, wd, xo, CorrV<T>{lv.agg, pv, c}, fuse_q, rc);
     } else {
       launch_elem(lv.n, OpProlong<T>{A, lv.agg, pv, c, xt}, rc, s);
@@ -1363,7 +1556,12 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
     launch_elem(lc.n, OpRtilde<T>{Act{F}, rcv, v, rt, K, wdn, xtn}, rc, s);
     cycle<T>(h, k + 1, rt, d, F, nullptr, nx0);                        // second inner iteration
     launch_level<T>(lc, OpKDots2<T>{Act{F}, d, v, rt, w, K, F, gm}, rc, s);
-    if (lv.n <= kFuseCorrectionRows) {
+    if (byT && lv.tlpr <= 0) {
+      launch_elem(lc.n, OpCombine<T>{A, c, d, K, F, T(0), T(0), false}, rc, s);
+      post_smooth_t<T>(h, lv, k, A, y, xo, CoarseV<T>{c}, fuse_q, rc);
+    } else if (byT) {
+      post_smooth_t<T>(h, lv, k, A, y, xo, CoarseK<T>{c, d, K, F, T(0), T(0), false}, fuse_q, rc);
+    } else if (lv.n <= kFuseCorrectionRows) {
       post_smooth<T>(h, lv, k, A, b, xt, wd, xo, CorrK<T>{lv.agg, pv, c, d, K, F}, fuse_q, rc);
     } else {
       launch_elem(lv.n, OpProlongK<T>{A, lv.agg, pv, c, d, xt, K, F}, rc, s);
@@ -1945,6 +2143,7 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
   const OpPresmoothResid<T> op{Act{nullptr}, x, x, y, y};
   for (int lpr = 2; lpr <= 32; lpr <<= 1) {
     const float us = time_it([&] { launch_rows<T>(lv.n, lpr, lv.rp, lv.ci, vals<T>(lv), op, rc, s); });
+    if (std::getenv("AMG_DEBUG")) std::fprintf(stderr, "amg: level n=%d CSR lanes=%d: %.2f us\n", lv.n, lpr, us);
     if (us < best.us) { best.us = us; best.fmt = 0; best.lpr = lpr; }
   }
   if (lv.ci16) {   // 16-bit column offsets: 2 bytes less per entry, taken within kPreferFewerBytes of CSR
@@ -2198,6 +2397,14 @@ void arnoldi(Hierarchy& h, Level& lv, int m, uint32_t stream, double* Q, double*
 }
 
 int pick_lanes_per_row(int n, int nnz) { return pick_lpr(n, nnz); }
+
+// The kernel of the product with T_k (rows of 3 to 8 entries): streamed on
+// large levels (flags: the largest 64-row group's entries, tsmooth_patterns),
+// on small ones a few lanes per row so that the level spreads over the chip.
+int post_lanes(int n, int nnz, int flags) {
+  if (n > kTsmoothRows && !(flags & kTGroup512)) return flags & kTGroup320 ? -8 : flags & kTGroup256 ? -5 : -4;
+  return nnz > 4L * n ? 8 : 4;
+}
 
 // q_i = unit_uniform(i, stream), the seeded hash vector in [-1, 1)
 void launch_hash_vector(int n, uint32_t stream, double* q, hipStream_t s) {
