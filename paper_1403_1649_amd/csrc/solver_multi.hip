@@ -1,9 +1,9 @@
 // Several right-hand sides with one hierarchy: the cycle of Algorithms 4/5 and
 // the outer flexible CG applied to a row-major block X[n][R] (R <= 64).
-// Each matrix row is handled by W = pow2(R) lanes, lane c owning column c:
-// the row's values and columns are loaded once (a broadcast within the lane
-// group) and the gathered X rows are contiguous, so A is streamed once for
-// all R columns.  Per level, an autotuner may instead split the columns into
+// Each matrix row is handled by one lane per V columns (16 bytes of them where
+// R divides, else one): the row's values and columns are loaded once (a
+// broadcast within the lane group) and the gathered X rows are contiguous, so
+// A is streamed once for all R columns.  Per level, an autotuner may instead split the columns into
 // tiles of W/2 or W/4 (one pass over A each), where the narrower gathered
 // working set stays in the caches.  Every scalar of the K-cycle and of the outer iteration is
 // per column, and so is the K-cycle branch: the second inner step runs when
@@ -56,23 +56,41 @@ struct ActAny {
   __device__ __forceinline__ bool on() const { return p == nullptr || *p != 0; }
 };
 
-// per-block partials of columns c0 .. c0 + W - 1
-template <int NV, int W>
-__device__ __forceinline__ void write_partials_m(double (&acc)[NV], int R, int c0, double* part) {
-  __shared__ double red[NV][kBlock / kWave][W];
+// V neighbouring columns of a block, one 16-byte access where V * sizeof(T) = 16
+template <typename T, int V>
+struct alignas(sizeof(T) * V) Pack {
+  T v[V];
+};
+template <int V, typename T>
+__device__ __forceinline__ Pack<T, V> ldp(const T* p) {
+  return *reinterpret_cast<const Pack<T, V>*>(p);
+}
+template <int V, typename T>
+__device__ __forceinline__ void stp(T* p, const Pack<T, V>& x) {
+  *reinterpret_cast<Pack<T, V>*>(p) = x;
+}
+
+// per-block partials of columns c0 .. c0 + WL V - 1 (WL lanes of V columns)
+template <int NV, int WL, int V>
+__device__ __forceinline__ void write_partials_m(double (&acc)[NV][V], int R, int c0, double* part) {
+  __shared__ double red[NV][kBlock / kWave][WL * V];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
+  for (int k = 0; k < NV; ++k)
 #pragma unroll
-    for (int off = W; off < kWave; off <<= 1) acc[k] += __shfl_xor(acc[k], off, kWave);
-  }
+    for (int v = 0; v < V; ++v) {
+#pragma unroll
+      for (int off = WL; off < kWave; off <<= 1) acc[k][v] += __shfl_xor(acc[k][v], off, kWave);
+    }
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  if (lane < W) {
+  if (lane < WL) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) red[k][wid][lane] = acc[k];
+    for (int k = 0; k < NV; ++k)
+#pragma unroll
+      for (int v = 0; v < V; ++v) red[k][wid][lane * V + v] = acc[k][v];
   }
   __syncthreads();
   const int c = threadIdx.x;
-  if (c < W && c0 + c < R) {
+  if (c < WL * V && c0 + c < R) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       double s = 0.0;
@@ -129,56 +147,107 @@ __device__ __forceinline__ int xcd_block() {
   return (b & 7) * (g >> 3) + (b >> 3);
 }
 
-// rows of A times columns c0 .. c0 + W - 1 of the block, W lanes per row
-template <typename T, int W, class Op>
-__global__ void __launch_bounds__(kBlock) k_rows_m(int n, int R, int c0, const int* __restrict__ rp,
-                                                   const int* __restrict__ ci, const T* __restrict__ av,
-                                                   Op op, double* part) {
+// Rows of A times columns c0 .. c0 + WL V - 1 of the block: WL lanes of V
+// columns, times `split` lane groups that share the row's entries (small
+// levels, where rows are few and long; their sums are added by lane exchange).
+// What bounds a level that fills the chip is the vectors' traffic, if enough
+// loads are in flight: the chain row pointers -> columns and values -> block
+// rows left the first version (one column per lane, nothing ahead) at 2 TB/s.
+// Here a lane moves 16 bytes per gather, and while the gathers of one row run
+// the columns and values of the next are loaded, and the row pointers of the
+// one after, all unconditionally at clamped positions.
+// D16: columns as 16-bit offsets from their 64-row group's base gbase.
+constexpr int kEnt = 8;   // entries a lane holds at a time
+template <typename T, int WL, int V, bool D16, class Op>
+__global__ void __launch_bounds__(kBlock) k_rows_m(int n, int R, int c0, int split, const int* __restrict__ rp,
+                                                   const void* __restrict__ cols, const int* __restrict__ gbase,
+                                                   const T* __restrict__ av, Op op, double* part) {
   if (!op.active()) {
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
   constexpr int NV = Op::NV > 0 ? Op::NV : 1;
-  constexpr int RPB = kBlock / W;
-  const int c = c0 + (threadIdx.x & (W - 1));
-  double acc[NV];
+  const int lpr = WL * split, rpb = kBlock / lpr;
+  const int c = c0 + (threadIdx.x & (WL - 1)) * V;
+  const int sub = (threadIdx.x / WL) & (split - 1);   // this lane's entries: sub, sub + split, ...
+  const int rl = threadIdx.x / lpr;
+  double acc[NV][V];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+  for (int k = 0; k < NV; ++k)
+#pragma unroll
+    for (int v = 0; v < V; ++v) acc[k][v] = 0.0;
   // The blocks of one XCD (block ids congruent mod 8) own a contiguous eighth
   // of the row groups and sweep it side by side, group j, j + blocks, ...:
   // the rows they gather at any time lie in one window of the XCD's L2.
-  const int groups = (n + RPB - 1) / RPB;
+  const int groups = (n + rpb - 1) / rpb;
   const int nx = (gridDim.x >= 8 && !(gridDim.x & 7)) ? 8 : 1;
   const int bpx = gridDim.x / nx;
   const int gpx = (groups + nx - 1) / nx;
   const int gbeg = (blockIdx.x % nx) * gpx, gend = min(groups, gbeg + gpx);
-  for (int g = gbeg + blockIdx.x / nx; g < gend; g += bpx) {
-    const int row = g * RPB + threadIdx.x / W;
-    if (row < n && c < R) {
-      T sum = T(0);
-      const int e = rp[row + 1];
-      // eight entries at a time: their columns and values, then the eight
-      // gathered block rows, then the products in entry order, so the
-      // gathers of a chunk are in flight together
-      for (int k0 = rp[row]; k0 < e; k0 += 8) {
-        int cj[8];
-        T v[8];
+  struct Row { int beg, end, base; };
+  struct Ents { int j[kEnt]; T v[kEnt]; };
+  auto row_of = [&](int g) {   // past the end: an empty row
+    const int i = g < gend ? min(g * rpb + rl, n) : n;
+    Row w;
+    w.beg = rp[min(i, n)];
+    w.end = rp[min(i + 1, n)];
+    w.base = D16 ? gbase[min(i, n - 1) >> 6] : 0;
+    return w;
+  };
+  auto ents_of = [&](const Row& w, int k0) {   // entries k0 + sub + q split; those past the row: value 0
+    Ents t;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          cj[q] = k0 + q < e ? ci[k0 + q] : 0;
-          v[q] = k0 + q < e ? av[k0 + q] : T(0);
-        }
-        T xv[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) xv[q] = k0 + q < e ? op.x(cj[q], c) : T(0);
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          if (k0 + q < e) sum += v[q] * xv[q];
-      }
-      op.row(row, c, sum, acc);
+    for (int q = 0; q < kEnt; ++q) {
+      const int k = k0 + sub + q * split;
+      const int kc = max(min(k, w.end - 1), 0);
+      if constexpr (D16) t.j[q] = w.base + (int)static_cast<const int16_t*>(cols)[kc];
+      else t.j[q] = static_cast<const int*>(cols)[kc];
+      const T v = av[kc];
+      t.v[q] = k < w.end ? v : T(0);
     }
+    return t;
+  };
+  int g = gbeg + blockIdx.x / nx;
+  Row r0 = row_of(g), r1 = row_of(g + bpx);
+  Ents e0 = ents_of(r0, r0.beg);
+  const int cc = min(c, R - V);   // lanes past the last column read its pack again
+  for (; g < gend; g += bpx) {
+    const int row = g * rpb + rl;
+    Pack<T, V> xv[kEnt];
+#pragma unroll
+    for (int q = 0; q < kEnt; ++q) xv[q] = op.template x<V>(e0.j[q], cc);
+    const Ents e1 = ents_of(r1, r1.beg);
+    const Row r2 = row_of(g + 2 * bpx);
+    Pack<T, V> sum;
+#pragma unroll
+    for (int v = 0; v < V; ++v) sum.v[v] = T(0);
+    // a padded product is left out, not added as zero: the row it gathers
+    // again may hold an infinity
+    auto add = [&](const Ents& t, const Pack<T, V>(&x)[kEnt], int left) {
+#pragma unroll
+      for (int q = 0; q < kEnt; ++q) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) sum.v[v] = q * split < left ? sum.v[v] + t.v[q] * x[q].v[v] : sum.v[v];
+      }
+    };
+    add(e0, xv, r0.end - r0.beg - sub);
+    for (int k0 = r0.beg + kEnt * split; k0 < r0.end; k0 += kEnt * split) {   // rows of more entries
+      const Ents t = ents_of(r0, k0);
+      Pack<T, V> x2[kEnt];
+#pragma unroll
+      for (int q = 0; q < kEnt; ++q) x2[q] = op.template x<V>(t.j[q], cc);
+      add(t, x2, r0.end - k0 - sub);
+    }
+    for (int off = WL; off < lpr; off <<= 1) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) sum.v[v] += __shfl_xor(sum.v[v], off, kWave);
+    }
+    if (row < n && c < R && sub == 0) op.template row<V>(row, c, sum, acc);
+    r0 = r1;
+    r1 = r2;
+    e0 = e1;
   }
-  if constexpr (Op::NV > 0) write_partials_m<Op::NV, W>(acc, R, c0, part);
+  if constexpr (Op::NV > 0) write_partials_m<Op::NV, WL, V>(acc, R, c0, part);
 }
 
 template <int W, class Op>
@@ -190,17 +259,17 @@ __global__ void __launch_bounds__(kBlock) k_elem_m(int n, int R, Op op, double* 
   constexpr int NV = Op::NV > 0 ? Op::NV : 1;
   constexpr int RPB = kBlock / W;
   const int c = threadIdx.x & (W - 1);
-  double acc[NV];
+  double acc[NV][1];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+  for (int k = 0; k < NV; ++k) acc[k][0] = 0.0;
   const int groups = (n + RPB - 1) / RPB;
   const int per = (groups + gridDim.x - 1) / gridDim.x;
   const int g0 = xcd_block() * per, g1 = min(groups, g0 + per);
   for (int g = g0; g < g1; ++g) {
     const int i = g * RPB + threadIdx.x / W;
-    if (i < n && c < R) op.elem(i, c, acc);
+    if (i < n && c < R) op.elem(i, c, acc[0]);
   }
-  if constexpr (Op::NV > 0) write_partials_m<Op::NV, W>(acc, R, 0, part);
+  if constexpr (Op::NV > 0) write_partials_m<Op::NV, W, 1>(acc, R, 0, part);
 }
 
 inline int grid_m(int n, int W, bool reduce) {
@@ -213,13 +282,38 @@ inline int grid_m(int n, int W, bool reduce) {
   return (int)g;
 }
 
-// The columns in tiles of W (one pass over the rows per tile, so a tile's
+// A row operator of the block kernels: CSR with 32-bit columns, or (gbase
+// non-null) 16-bit offsets from the base of each 64-row group.
+struct MCsr {
+  const int* rp;
+  const void* cols;
+  const int* gbase;
+};
+
+// Lane groups that share a row's entries: on levels too small to fill the
+// chip with one, as many (up to 8, within a wave) as bring it to kSplitThreads
+// threads, while each still has two entries.  41 x 43 x 40 cells, 5 columns: a
+// product with a level of 1,000 rows of 14 entries took 10.8 us with one group.
+constexpr long kSplitThreads = 131072;
+inline int split_of(int n, long nnz, int wl) {
+  int split = 1;
+  while (split < 8 && wl * split * 2 <= kWave && (long)n * wl * split < kSplitThreads && nnz > 2L * split * n) split <<= 1;
+  return split;
+}
+
+// The columns in tiles of WL V (one pass over the rows per tile, so a tile's
 // gathered block rows are a narrower working set in the caches), then the
 // totals of all columns.
-template <typename T, int W, class Op>
-void rows_m_w(int n, const MCtx& m, const int* rp, const int* ci, const T* av, const Op& op, hipStream_t s) {
-  const int g = grid_m(n, W, Op::NV > 0);
-  for (int c0 = 0; c0 < m.R; c0 += W) k_rows_m<T, W, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, rp, ci, av, op, m.part);
+template <typename T, int WL, int V, class Op>
+void rows_m_w(int n, long nnz, const MCtx& m, const MCsr& A, const T* av, const Op& op, hipStream_t s) {
+  const int split = split_of(n, nnz, WL);
+  const int g = grid_m(n, WL * split, Op::NV > 0);
+  for (int c0 = 0; c0 < m.R; c0 += WL * V) {
+    if (A.gbase)
+      k_rows_m<T, WL, V, true, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, A.gbase, av, op, m.part);
+    else
+      k_rows_m<T, WL, V, false, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, nullptr, av, op, m.part);
+  }
   if constexpr (Op::NV > 0) k_finalize_m<Op><<<Op::NV * m.R, kFinMBlock, 0, s>>>(op, m.part, g, m.R, m.tot, m.ticket);
 }
 
@@ -236,17 +330,34 @@ inline int width_of(int R) {
   return w;
 }
 
-// tile: columns per pass (a power of two; 0 = all columns in one pass)
+// tile: columns per pass (a power of two; 0 = all columns in one pass).  Packs
+// of 16 bytes where the columns divide into them (then a block row, 16 V-byte
+// aligned from an aligned block, holds whole packs); `aligned` is false for a
+// caller's block that does not start on 16 bytes.
 template <typename T, class Op>
-void rows_m(int n, const MCtx& m, int tile, const int* rp, const int* ci, const T* av, const Op& op, hipStream_t s) {
-  switch (tile > 0 ? std::min(tile, width_of(m.R)) : width_of(m.R)) {
-    case 1: rows_m_w<T, 1>(n, m, rp, ci, av, op, s); break;
-    case 2: rows_m_w<T, 2>(n, m, rp, ci, av, op, s); break;
-    case 4: rows_m_w<T, 4>(n, m, rp, ci, av, op, s); break;
-    case 8: rows_m_w<T, 8>(n, m, rp, ci, av, op, s); break;
-    case 16: rows_m_w<T, 16>(n, m, rp, ci, av, op, s); break;
-    case 32: rows_m_w<T, 32>(n, m, rp, ci, av, op, s); break;
-    default: rows_m_w<T, 64>(n, m, rp, ci, av, op, s); break;
+void rows_m(int n, long nnz, const MCtx& m, int tile, const MCsr& A, const T* av, const Op& op, hipStream_t s,
+            bool aligned = true) {
+  constexpr int VM = 16 / sizeof(T);
+  const int w = tile > 0 ? std::min(tile, width_of(m.R)) : width_of(m.R);
+  if (aligned && m.R % VM == 0 && w >= VM) {
+    switch (w / VM) {
+      case 1: rows_m_w<T, 1, VM>(n, nnz, m, A, av, op, s); break;
+      case 2: rows_m_w<T, 2, VM>(n, nnz, m, A, av, op, s); break;
+      case 4: rows_m_w<T, 4, VM>(n, nnz, m, A, av, op, s); break;
+      case 8: rows_m_w<T, 8, VM>(n, nnz, m, A, av, op, s); break;
+      case 16: rows_m_w<T, 16, VM>(n, nnz, m, A, av, op, s); break;
+      default: rows_m_w<T, 32, VM>(n, nnz, m, A, av, op, s); break;
+    }
+    return;
+  }
+  switch (w) {
+    case 1: rows_m_w<T, 1, 1>(n, nnz, m, A, av, op, s); break;
+    case 2: rows_m_w<T, 2, 1>(n, nnz, m, A, av, op, s); break;
+    case 4: rows_m_w<T, 4, 1>(n, nnz, m, A, av, op, s); break;
+    case 8: rows_m_w<T, 8, 1>(n, nnz, m, A, av, op, s); break;
+    case 16: rows_m_w<T, 16, 1>(n, nnz, m, A, av, op, s); break;
+    case 32: rows_m_w<T, 32, 1>(n, nnz, m, A, av, op, s); break;
+    default: rows_m_w<T, 64, 1>(n, nnz, m, A, av, op, s); break;
   }
 }
 
@@ -269,6 +380,8 @@ void elem_m(int n, const MCtx& m, const Op& op, hipStream_t s) {
   __device__ void idle() const {}                                \
   __device__ void finalize_all() const {}
 
+// two: the iterate goes out after both smoothing steps, x + w.*r (levels that
+// post-smooth by T, Level::tp)
 template <typename T>
 struct MPresmoothResid {
   static constexpr int NV = 0;
@@ -278,13 +391,30 @@ struct MPresmoothResid {
   const T* wd;
   T* xt;
   T* r;
+  bool two;
   M_COMMON
-  __device__ T x(int j, int c) const { return wd[j] * b[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, T ax, double*) const {
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const {
+    Pack<T, V> t = ldp<V>(b + (size_t)j * R + c);
+    const T w = wd[j];
+#pragma unroll
+    for (int v = 0; v < V; ++v) t.v[v] *= w;
+    return t;
+  }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&)[1][V]) const {
     const size_t q = (size_t)i * R + c;
-    const T bi = b[q];
-    xt[q] = wd[i] * bi;
-    r[q] = bi - ax;
+    const Pack<T, V> bi = ldp<V>(b + q);
+    const T w = wd[i];
+    Pack<T, V> xo, ro;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      ro.v[v] = bi.v[v] - ax.v[v];
+      xo.v[v] = w * bi.v[v];
+      if (two) xo.v[v] += w * ro.v[v];
+    }
+    stp<V>(xt + q, xo);
+    stp<V>(r + q, ro);
   }
   __device__ void finalize(int, const double*) const {}
 };
@@ -299,31 +429,103 @@ struct MResidSmooth {
   const T* wd;
   T* xo;
   M_COMMON
-  __device__ T x(int j, int c) const { return xt[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, T ax, double*) const {
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(xt + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&)[1][V]) const {
     const size_t q = (size_t)i * R + c;
-    xo[q] = xt[q] + wd[i] * (b[q] - ax);
+    const Pack<T, V> bi = ldp<V>(b + q), xi = ldp<V>(xt + q);
+    const T w = wd[i];
+    Pack<T, V> o;
+#pragma unroll
+    for (int v = 0; v < V; ++v) o.v[v] = xi.v[v] + w * (bi.v[v] - ax.v[v]);
+    stp<V>(xo + q, o);
   }
   __device__ void finalize(int, const double*) const {}
 };
 
+// correction and post-smoothing by T: x_out = y + T e; DOT: with z'q per column
+// for the FCG beta (level 0 of the outer iteration).  K non-null: e = coef_c c
+// (+ coef_d d) per column, else e = c.
 template <typename T, bool DOT>
-struct MRestrict {   // rows of R = P^T (aggregates) times the block
+struct MPostT {
   static constexpr int NV = DOT ? 1 : 0;
+  ActAny a;
+  int R;
+  const T* y;
+  T* xo;
+  const T* cc;
+  const T* d;
+  const double* K;
+  const int* F;
+  const double* q;
+  double* sc;
+  M_COMMON
+  template <int V>
+  __device__ Pack<T, V> x(int J, int c) const {
+    Pack<T, V> t = ldp<V>(cc + (size_t)J * R + c);
+    if (K) {
+      const Pack<T, V> u = ldp<V>(d + (size_t)J * R + c);
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        t.v[v] *= (T)K[kKCoefC * R + c + v];
+        if (F[R + c + v]) t.v[v] += (T)K[kKCoefD * R + c + v] * u.v[v];
+      }
+    }
+    return t;
+  }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& te, double (&acc)[1][V]) const {
+    const size_t k = (size_t)i * R + c;
+    const Pack<T, V> yi = ldp<V>(y + k);
+    Pack<T, V> z;
+#pragma unroll
+    for (int v = 0; v < V; ++v) z.v[v] = yi.v[v] + te.v[v];
+    stp<V>(xo + k, z);
+    if constexpr (DOT) {
+      const Pack<double, V> qi = ldp<V>(q + k);
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[0][v] += (double)z.v[v] * qi.v[v];
+    }
+  }
+  __device__ void finalize(int c, const double* s) const {
+    if (DOT) sc[mBeta * R + c] = -s[0] / sc[mPQ * R + c];
+  }
+};
+
+// the K-cycle's combination per column, in place: c <- coef_c c (+ coef_d d)
+template <typename T>
+struct MCombine {
+  static constexpr int NV = 0;
+  ActAny a;
+  int R;
+  T* cc;
+  const T* d;
+  const double* K;
+  const int* F;
+  M_COMMON
+  __device__ void elem(int i, int c, double*) const {
+    const size_t k = (size_t)i * R + c;
+    T t = (T)K[kKCoefC * R + c] * cc[k];
+    if (F[R + c]) t += (T)K[kKCoefD * R + c] * d[k];
+    cc[k] = t;
+  }
+  __device__ void finalize(int, const double*) const {}
+};
+
+template <typename T>
+struct MRestrict {   // rows of R = P^T (aggregates) times the block
+  static constexpr int NV = 0;
   ActAny a;
   int R;
   const T* r;
   T* rcv;
-  double* K;   // per-column K slots of this level (slot * R + c)
   M_COMMON
-  __device__ T x(int j, int c) const { return r[(size_t)j * R + c]; }
-  __device__ void row(int I, int c, T s, double* acc) const {
-    rcv[(size_t)I * R + c] = s;
-    if (DOT) acc[0] += (double)s * (double)s;
-  }
-  __device__ void finalize(int c, const double* v) const {
-    if (DOT) K[kKRcRc * R + c] = v[0];
-  }
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(r + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int I, int c, const Pack<T, V>& s, double (&)[1][V]) const { stp<V>(rcv + (size_t)I * R + c, s); }
+  __device__ void finalize(int, const double*) const {}
 };
 
 template <typename T>
@@ -342,60 +544,57 @@ struct MProlong {
   __device__ void finalize(int, const double*) const {}
 };
 
+// first inner step: v = A c, rho1 and alpha1 per column, and the test of the
+// second step in the same reduction, as the single-vector cycle does it: with
+// a = alpha1 / rho1, ||r~||^2 = r_c'r_c - 2 a v'r_c + a^2 v'v
 template <typename T>
 struct MKDots1 {
-  static constexpr int NV = 2;
+  static constexpr int NV = 5;
   ActAny a;
   int R;
   const T* cc;
   const T* rcv;
-  T* v;
-  double* K;
-  int gmres;
-  M_COMMON
-  __device__ T x(int j, int c) const { return cc[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, T ax, double* acc) const {
-    const size_t q = (size_t)i * R + c;
-    v[q] = ax;
-    const double l = gmres ? (double)ax : (double)cc[q];
-    acc[0] += l * (double)ax;
-    acc[1] += l * (double)rcv[q];
-  }
-  __device__ void finalize(int c, const double* s) const {
-    K[kKRho1 * R + c] = s[0];
-    K[kKAlpha1 * R + c] = s[1];
-  }
-};
-
-template <typename T>
-struct MRtilde {
-  static constexpr int NV = 1;
-  ActAny a;
-  int R;
-  const T* rcv;
-  const T* v;
-  T* rt;
+  T* vo;
   double* K;
   int* F;       // per-column: F[c] step 2, F[R + c] use d
   int* any2;    // any column needs step 2
+  int gmres;
   double t;
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const { *any2 = 0; }
-  __device__ void elem(int i, int c, double* acc) const {
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(cc + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&acc)[5][V]) const {
     const size_t q = (size_t)i * R + c;
-    const T ar = (T)(K[kKAlpha1 * R + c] / K[kKRho1 * R + c]);
-    const T u = rcv[q] - ar * v[q];
-    rt[q] = u;
-    acc[0] += (double)u * (double)u;
+    stp<V>(vo + q, ax);
+    const Pack<T, V> ci = ldp<V>(cc + q), ri = ldp<V>(rcv + q);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const double av = (double)ax.v[v], rr = (double)ri.v[v];
+      const double l = gmres ? av : (double)ci.v[v];
+      acc[0][v] += l * av;
+      acc[1][v] += l * rr;
+      acc[2][v] += rr * rr;
+      acc[3][v] += av * av;
+      acc[4][v] += av * rr;
+    }
   }
   __device__ void finalize(int c, const double* s) const {
-    const double rho1 = K[kKRho1 * R + c];
-    K[kKRtRt * R + c] = s[0];
+    const double rho1 = s[0], alpha1 = s[1];
+    K[kKRho1 * R + c] = rho1;
+    K[kKAlpha1 * R + c] = alpha1;
+    K[kKRcRc * R + c] = s[2];
     F[R + c] = 0;
     if (rho1 > 0.0) {
-      K[kKCoefC * R + c] = K[kKAlpha1 * R + c] / rho1;
-      F[c] = (sqrt(s[0]) <= t * sqrt(K[kKRcRc * R + c])) ? 0 : 1;
+      const double ar = alpha1 / rho1;
+      double rt2 = s[2] - 2.0 * ar * s[4] + ar * ar * s[3];
+      rt2 = rt2 > 0.0 ? rt2 : 0.0;
+      K[kKRtRt * R + c] = rt2;
+      K[kKCoefC * R + c] = ar;
+      F[c] = (sqrt(rt2) <= t * sqrt(s[2])) ? 0 : 1;
     } else {
+      K[kKRtRt * R + c] = s[2];
       K[kKCoefC * R + c] = 0.0;
       F[c] = 0;
     }
@@ -407,27 +606,52 @@ struct MRtilde {
   }
 };
 
+// r~ = r_c - (alpha1 / rho1) v (only when some column's second step runs)
+template <typename T>
+struct MRtilde {
+  static constexpr int NV = 0;
+  ActAny a;
+  int R;
+  const T* rcv;
+  const T* v;
+  T* rt;
+  const double* K;
+  M_COMMON
+  __device__ void elem(int i, int c, double*) const {
+    const size_t q = (size_t)i * R + c;
+    const T ar = (T)(K[kKAlpha1 * R + c] / K[kKRho1 * R + c]);
+    rt[q] = rcv[q] - ar * v[q];
+  }
+  __device__ void finalize(int, const double*) const {}
+};
+
 template <typename T>
 struct MKDots2 {
   static constexpr int NV = 3;
   ActAny a;
   int R;
   const T* d;
-  const T* v;
+  const T* vc;
   const T* rt;
   T* w;
   double* K;
   int* F;
   int gmres;
   M_COMMON
-  __device__ T x(int j, int c) const { return d[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, T ax, double* acc) const {
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(d + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&acc)[3][V]) const {
     const size_t q = (size_t)i * R + c;
-    w[q] = ax;
-    const double l = gmres ? (double)ax : (double)d[q];
-    acc[0] += l * (double)v[q];
-    acc[1] += l * (double)ax;
-    acc[2] += l * (double)rt[q];
+    stp<V>(w + q, ax);
+    const Pack<T, V> di = ldp<V>(d + q), vi = ldp<V>(vc + q), ri = ldp<V>(rt + q);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const double l = gmres ? (double)ax.v[v] : (double)di.v[v];
+      acc[0][v] += l * (double)vi.v[v];
+      acc[1][v] += l * (double)ax.v[v];
+      acc[2][v] += l * (double)ri.v[v];
+    }
   }
   __device__ void finalize(int c, const double* s) const {
     if (!F[c]) return;
@@ -556,12 +780,18 @@ struct MFcgSpmv {
   int* err;
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
-  __device__ double x(int j, int c) const { return p[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, double ax, double* acc) const {
+  template <int V>
+  __device__ Pack<double, V> x(int j, int c) const { return ldp<V>(p + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<double, V>& ax, double (&acc)[2][V]) const {
     const size_t k = (size_t)i * R + c;
-    q[k] = ax;
-    acc[0] += p[k] * ax;
-    acc[1] += p[k] * r[k];
+    stp<V>(q + k, ax);
+    const Pack<double, V> pi = ldp<V>(p + k), ri = ldp<V>(r + k);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      acc[0][v] += pi.v[v] * ax.v[v];
+      acc[1][v] += pi.v[v] * ri.v[v];
+    }
   }
   __device__ void finalize(int c, const double* s) const {
     if (!fl[fRun * R + c]) return;
@@ -592,6 +822,7 @@ struct MFcgUpdate {
   int* fl;
   int* any;
   int* err;
+  float* r32;   // mixed precision: the cycle's FP32 right-hand side (a converged column keeps its own)
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
   __device__ void elem(int i, int c, double* acc) const {
@@ -601,6 +832,7 @@ struct MFcgUpdate {
     xv[k] += al * p[k];
     const double t = r[k] - al * q[k];
     r[k] = t;
+    if (r32) r32[k] = (float)t;
     acc[0] += t * t;
   }
   __device__ void finalize(int c, const double* s) const {
@@ -678,12 +910,18 @@ struct MTrueResid {
   double* r;
   double* sc;
   M_COMMON
-  __device__ double x(int j, int c) const { return xv[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, double ax, double* acc) const {
+  template <int V>
+  __device__ Pack<double, V> x(int j, int c) const { return ldp<V>(xv + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<double, V>& ax, double (&acc)[1][V]) const {
     const size_t k = (size_t)i * R + c;
-    const double t = b[k] - ax;
-    r[k] = t;
-    acc[0] += t * t;
+    Pack<double, V> t = ldp<V>(b + k);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      t.v[v] -= ax.v[v];
+      acc[0][v] += t.v[v] * t.v[v];
+    }
+    stp<V>(r + k, t);
   }
   __device__ void finalize(int c, const double* s) const { sc[mTrue * R + c] = s[0]; }
 };
@@ -697,8 +935,10 @@ struct MSpmvT {
   const T* xin;
   T* y;
   M_COMMON
-  __device__ T x(int j, int c) const { return xin[(size_t)j * R + c]; }
-  __device__ void row(int i, int c, T ax, double*) const { y[(size_t)i * R + c] = ax; }
+  template <int V>
+  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(xin + (size_t)j * R + c); }
+  template <int V>
+  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&)[1][V]) const { stp<V>(y + (size_t)i * R + c, ax); }
   __device__ void finalize(int, const double*) const {}
 };
 
@@ -738,6 +978,9 @@ template <> const float* wdinv_t<float>(const Level& l) { return l.wdinv32; }
 template <typename T> const T* pvals_t(const Level& l);
 template <> const double* pvals_t<double>(const Level& l) { return l.pval; }
 template <> const float* pvals_t<float>(const Level& l) { return l.pval32; }
+template <typename T> const T* tvals_t(const Level& l);
+template <> const double* tvals_t<double>(const Level& l) { return l.tv; }
+template <> const float* tvals_t<float>(const Level& l) { return l.tv32; }
 template <typename T> const T* rvals_t(const Level& l);
 template <> const double* rvals_t<double>(const Level& l) { return l.rval; }
 template <> const float* rvals_t<float>(const Level& l) { return l.rval32; }
@@ -768,13 +1011,17 @@ void coarse_m(Hierarchy& h, const MCtx& m, const T* b, T* x, const int* act) {
   k_gemm_coarse<T><<<tiles, kBlock, 0, h.stream>>>(n, m.R, h.cinv, b, x, ActAny{act});
 }
 
+MCsr csr_of(const Level& l) { return MCsr{l.rp, l.ci, nullptr}; }
+
+// xo = M_k b.  fuse_q: z'q per column (the FCG beta) in the last kernel, where
+// the level post-smooths by T; returns whether it was computed.
 template <typename T>
-void cycle_m(Hierarchy& h, MWork& W, int k, const T* b, T* xo, const int* act) {
+bool cycle_m(Hierarchy& h, MWork& W, int k, const T* b, T* xo, const int* act, const double* fuse_q = nullptr) {
   const MCtx& m = W.m;
   hipStream_t s = h.stream;
   if (h.L() == 0) {
     coarse_m<T>(h, m, b, xo, act);
-    return;
+    return false;
   }
   Level& lv = h.levels[k];
   MLevel& ml = W.lv[k];
@@ -788,42 +1035,58 @@ void cycle_m(Hierarchy& h, MWork& W, int k, const T* b, T* xo, const int* act) {
   const ActAny A{act};
   const int tk = W.tile[k];                                  // columns per pass on level k's rows
   const int tc = k + 1 < L ? W.tile[k + 1] : 0;              // ... and on level k+1's
-  rows_m<T>(lv.n, m, tk, lv.rp, lv.ci, vals_t<T>(lv), MPresmoothResid<T>{A, R, b, wd, xt, r}, s);
+  const MCsr Ak = csr_of(lv), Rk{lv.agg_ptr, lv.agg_rows, nullptr};
+  const bool byT = lv.tp != nullptr;   // post-smoothing by T = (I - W A) P
+  rows_m<T>(lv.n, lv.nnz, m, tk, Ak, vals_t<T>(lv), MPresmoothResid<T>{A, R, b, wd, xt, r, byT}, s);
+  rows_m<T>(lv.nc, lv.nr, m, tk, Rk, rvals_t<T>(lv), MRestrict<T>{A, R, r, rcv}, s);
   const bool kcyc = k < h.opt.kcycle_levels && k + 1 < L;
+  double* K = m.sc + (size_t)(mK0 + 16 * k) * R;
+  int* F = m.fl + (size_t)(fK0 + 2 * k) * R;
+  T* d = kcyc ? static_cast<T*>(ml.d) : nullptr;
   if (!kcyc) {
-    rows_m<T>(lv.nc, m, tk, lv.agg_ptr, lv.agg_rows, rvals_t<T>(lv), MRestrict<T, false>{A, R, r, rcv, nullptr}, s);
     if (k + 1 == L) coarse_m<T>(h, m, rcv, c, act);
     else cycle_m<T>(h, W, k + 1, rcv, c, act);
-    elem_m(lv.n, m, MProlong<T>{A, R, lv.agg, pv, c, xt}, s);
+    if (!byT) elem_m(lv.n, m, MProlong<T>{A, R, lv.agg, pv, c, xt}, s);
   } else {
     Level& lc = h.levels[k + 1];
-    double* K = m.sc + (size_t)(mK0 + 16 * k) * R;
-    int* F = m.fl + (size_t)(fK0 + 2 * k) * R;
+    const MCsr Ac = csr_of(lc);
     int* any2 = m.any + aK0 + k;
     T* v = static_cast<T*>(ml.v);
     T* rt = static_cast<T*>(ml.rt);
-    T* d = static_cast<T*>(ml.d);
     T* w = static_cast<T*>(ml.w);
     const int gm = h.opt.krylov == AMG_KRYLOV_FGMRES ? 1 : 0;
-    rows_m<T>(lv.nc, m, tk, lv.agg_ptr, lv.agg_rows, rvals_t<T>(lv), MRestrict<T, true>{A, R, r, rcv, K}, s);
     cycle_m<T>(h, W, k + 1, rcv, c, act);
-    rows_m<T>(lc.n, m, tc, lc.rp, lc.ci, vals_t<T>(lc), MKDots1<T>{A, R, c, rcv, v, K, gm}, s);
-    elem_m(lc.n, m, MRtilde<T>{A, R, rcv, v, rt, K, F, any2, h.opt.kcycle_t}, s);
+    rows_m<T>(lc.n, lc.nnz, m, tc, Ac, vals_t<T>(lc), MKDots1<T>{A, R, c, rcv, v, K, F, any2, gm, h.opt.kcycle_t}, s);
+    elem_m(lc.n, m, MRtilde<T>{ActAny{any2}, R, rcv, v, rt, K}, s);
     cycle_m<T>(h, W, k + 1, rt, d, any2);
-    rows_m<T>(lc.n, m, tc, lc.rp, lc.ci, vals_t<T>(lc), MKDots2<T>{ActAny{any2}, R, d, v, rt, w, K, F, gm}, s);
-    elem_m(lv.n, m, MProlongK<T>{A, R, lv.agg, pv, c, d, xt, K, F}, s);
+    rows_m<T>(lc.n, lc.nnz, m, tc, Ac, vals_t<T>(lc), MKDots2<T>{ActAny{any2}, R, d, v, rt, w, K, F, gm}, s);
+    if (!byT) elem_m(lv.n, m, MProlongK<T>{A, R, lv.agg, pv, c, d, xt, K, F}, s);
   }
-  rows_m<T>(lv.n, m, tk, lv.rp, lv.ci, vals_t<T>(lv), MResidSmooth<T>{A, R, b, xt, wd, xo}, s);
+  if (!byT) {
+    rows_m<T>(lv.n, lv.nnz, m, tk, Ak, vals_t<T>(lv), MResidSmooth<T>{A, R, b, xt, wd, xo}, s);
+    return false;
+  }
+  // on large levels the K-cycle's combination is formed once per coarse row,
+  // on small ones where it is gathered
+  const bool combine = kcyc && lv.n > kTsmoothRows;
+  if (combine) elem_m(lv.nc, m, MCombine<T>{A, R, c, d, K, F}, s);
+  const MCsr Tk{lv.tp, lv.tc16 ? static_cast<const void*>(lv.tc16) : static_cast<const void*>(lv.tc), lv.tbase};
+  const double* Kg = kcyc && !combine ? K : nullptr;
+  if (fuse_q) rows_m<T>(lv.n, lv.tnnz, m, tk, Tk, tvals_t<T>(lv), MPostT<T, true>{A, R, xt, xo, c, d, Kg, F, fuse_q, m.sc}, s);
+  else rows_m<T>(lv.n, lv.tnnz, m, tk, Tk, tvals_t<T>(lv), MPostT<T, false>{A, R, xt, xo, c, d, Kg, F, nullptr, m.sc}, s);
+  return fuse_q != nullptr;
 }
 
+// z = M r; r32_ready: the FP32 copy of r is written (mixed mode).  Returns
+// whether z'q was computed.
 template <typename T>
-void precondition_m(Hierarchy& h, MWork& W, const int* act) {
+bool precondition_m(Hierarchy& h, MWork& W, const int* act, const double* fuse_q = nullptr, bool r32_ready = false) {
   const int n = h.levels[0].n;
   if constexpr (sizeof(T) == sizeof(float)) {
-    elem_m(n, W.m, MToFloat{ActAny{act}, W.m.R, W.r, static_cast<float*>(W.bz)}, h.stream);
-    cycle_m<float>(h, W, 0, static_cast<const float*>(W.bz), static_cast<float*>(W.z), act);
+    if (!r32_ready) elem_m(n, W.m, MToFloat{ActAny{act}, W.m.R, W.r, static_cast<float*>(W.bz)}, h.stream);
+    return cycle_m<float>(h, W, 0, static_cast<const float*>(W.bz), static_cast<float*>(W.z), act, fuse_q);
   } else {
-    cycle_m<double>(h, W, 0, W.r, static_cast<double*>(W.z), act);
+    return cycle_m<double>(h, W, 0, W.r, static_cast<double*>(W.z), act, fuse_q);
   }
 }
 
@@ -835,10 +1098,11 @@ void iteration_m(Hierarchy& h, MWork& W) {
   const int* run = m.any + aRun;
   const ActAny A{run};
   hipStream_t s = h.stream;
-  rows_m<double>(n, m, W.tile0, l0.rp, l0.ci, l0.val, MFcgSpmv{A, R, W.p, W.r, W.q, m.sc, m.fl, m.any, m.err}, s);
-  elem_m(n, m, MFcgUpdate{A, R, W.p, W.q, W.xv, W.r, m.sc, m.fl, m.any, m.err}, s);
-  precondition_m<T>(h, W, run);
-  elem_m(n, m, MDotZQ<T>{A, R, static_cast<const T*>(W.z), W.q, m.sc}, s);
+  rows_m<double>(n, l0.nnz, m, W.tile0, csr_of(l0), l0.val, MFcgSpmv{A, R, W.p, W.r, W.q, m.sc, m.fl, m.any, m.err}, s);
+  float* r32 = sizeof(T) == sizeof(float) ? static_cast<float*>(W.bz) : nullptr;
+  elem_m(n, m, MFcgUpdate{A, R, W.p, W.q, W.xv, W.r, m.sc, m.fl, m.any, m.err, r32}, s);
+  if (!precondition_m<T>(h, W, run, W.q, r32 != nullptr))
+    elem_m(n, m, MDotZQ<T>{A, R, static_cast<const T*>(W.z), W.q, m.sc}, s);
   elem_m(n, m, MPUpdate<T>{A, R, static_cast<const T*>(W.z), W.p, m.sc, m.fl, 0}, s);
 }
 
@@ -882,8 +1146,8 @@ void alloc_work(Hierarchy& h, MWork& W, int R) {
   W.m.sc = W.arena.alloc_n<double>((size_t)mSlots * R);
   W.m.fl = W.arena.alloc_n<int>((size_t)fWords * R);
   W.m.any = W.arena.alloc_n<int>(aWords);
-  W.m.part = W.arena.alloc_n<double>((size_t)3 * R * kMultiBlocks);
-  W.m.tot = W.arena.alloc_n<double>((size_t)3 * R);
+  W.m.part = W.arena.alloc_n<double>((size_t)5 * R * kMultiBlocks);   // at most five values per column
+  W.m.tot = W.arena.alloc_n<double>((size_t)5 * R);
   W.m.ticket = W.arena.alloc_n<unsigned>(64);
   launch_fill_int(64, reinterpret_cast<int*>(W.m.ticket), 0, h.stream);
   W.m.err = h.d_err;
@@ -924,11 +1188,11 @@ int tune_tile(Hierarchy& h, const Level& lv, const MWork& W, T* x, T* y) {
   float best_us = 1e30f;
   int best = wf;
   for (int tw = wf; tw >= 8 && tw * 4 >= wf; tw >>= 1) {
-    rows_m<T>(lv.n, W.m, tw, lv.rp, lv.ci, av, op, s);
+    rows_m<T>(lv.n, lv.nnz, W.m, tw, csr_of(lv), av, op, s);
     float us = 1e30f;
     for (int trial = 0; trial < 2; ++trial) {
       AMG_HIP(hipEventRecord(e0, s));
-      for (int r = 0; r < 4; ++r) rows_m<T>(lv.n, W.m, tw, lv.rp, lv.ci, av, op, s);
+      for (int r = 0; r < 4; ++r) rows_m<T>(lv.n, lv.nnz, W.m, tw, csr_of(lv), av, op, s);
       AMG_HIP(hipEventRecord(e1, s));
       AMG_HIP(hipEventSynchronize(e1));
       float ms = 0.f;
@@ -1094,7 +1358,8 @@ int solve_multi_impl(Hierarchy& h, int R, const double* B, double rtol, double* 
       throw Error(AMG_EHIP, "device error bits " + std::to_string(hp[1]));
     }
     if (hp[0] && enqueued < max_iter) continue;
-    rows_m<double>(n, W.m, W.tile0, l0.rp, l0.ci, l0.val, MTrueResid{ActAny{nullptr}, R, B, W.xv, W.q, W.m.sc}, s);
+    rows_m<double>(n, l0.nnz, W.m, W.tile0, csr_of(l0), l0.val, MTrueResid{ActAny{nullptr}, R, B, W.xv, W.q, W.m.sc}, s,
+                   reinterpret_cast<uintptr_t>(B) % 16 == 0);
     AMG_HIP(hipMemcpyAsync(hfl.data(), W.m.fl, hfl.size() * sizeof(int), hipMemcpyDeviceToHost, s));
     AMG_HIP(hipMemcpyAsync(hsc.data(), W.m.sc, hsc.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     AMG_HIP(hipStreamSynchronize(s));
