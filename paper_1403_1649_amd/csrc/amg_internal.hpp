@@ -333,6 +333,9 @@ int scan_blocks_needed(int n);
 // setup_kernels.hip
 void launch_check_rowptr(int n, const int* rp, int* err, hipStream_t s);
 void launch_check_index(int n, const int* idx, int limit, int* err, hipStream_t s);
+// raises kErrNotSPD where a_ii |B_i| < sum_{j != i} |a_ij| |B_j| (to rounding)
+void launch_check_dominant(int n, const int* rp, const int* ci, const double* val, const double* B, int* err,
+                           hipStream_t s);
 void launch_check_matrix(int n, const int* rp, const int* ci, const double* val, int* err, hipStream_t s);
 // Up to 8 device ints copied to host pinned slots (0..62) by one launch,
 // together with the error word (slot 63).

@@ -208,8 +208,25 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Operands of row i that an operation wants loaded with the gathers (Op::Pre).
+template <class Op, class = void>
+struct RowPre {
+  struct type {};
+  __device__ static type load(const Op&, int) { return type{}; }
+  template <typename T>
+  __device__ static void row(const Op& op, int i, T sum, const type&, double* acc) { op.row(i, sum, acc); }
+};
+template <class Op>
+struct RowPre<Op, std::void_t<typename Op::Pre>> {
+  using type = typename Op::Pre;
+  __device__ static type load(const Op& op, int i) { return op.pre(i); }
+  template <typename T>
+  __device__ static void row(const Op& op, int i, T sum, const type& p, double* acc) { op.row(i, sum, p, acc); }
+};
+
 // CSR rows streamed through LDS.  A wave takes groups of R consecutive rows of
-// at most 64 Q entries together (the caller's guarantee).  A group's entries
+// about 64 Q entries together; a larger group takes a slow path, each row
+// summed by the whole wave.  A group's entries
 // are one contiguous run, loaded coalesced, Q per lane; the products go to the
 // wave's LDS, and 64/R lanes sum each row there.  So there is no padding, no
 // idle lane on short rows, and every load instruction covers whole lines.
@@ -276,18 +293,34 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
     T xv[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) xv[q] = op.x(e0.c[q]);
-    const typename Op::Pre pre = op.pre(min(row, n - 1));
+    const typename RowPre<Op>::type pre = RowPre<Op>::load(op, min(row, n - 1));
     const Entries e1 = entries_of(r1);
     const Rows r2 = rows_of(u + 2 * st.inc);
-#pragma unroll
-    for (int q = 0; q < Q; ++q) prod[q * kWave + lane] = e0.v[q] * xv[q];
-    wave_lds_order();
     const int base = __builtin_amdgcn_readfirstlane(r0.beg);
+    const int total = __builtin_amdgcn_readlane(r0.end, R - 1) - base;
     T sum = T(0);
-    for (int k = r0.beg - base + part; k < r0.end - base; k += LPR) sum += prod[k];
-    wave_lds_order();
-    if constexpr (LPR == 2) sum += __shfl_xor(sum, 32, kWave);
-    if (row < n && part == 0) op.row(row, sum, pre, acc);
+    if (total <= kWave * Q) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) prod[q * kWave + lane] = e0.v[q] * xv[q];
+      wave_lds_order();
+      for (int k = r0.beg - base + part; k < r0.end - base; k += LPR) sum += prod[k];
+      wave_lds_order();
+      if constexpr (LPR == 2) sum += __shfl_xor(sum, 32, kWave);
+    } else {
+      for (int i = 0; i < R; ++i) {
+        const int b = __builtin_amdgcn_readlane(r0.beg, i), e = __builtin_amdgcn_readlane(r0.end, i);
+        T t = T(0);
+        for (int k = b + lane; k < e; k += kWave) {
+          int c;
+          if constexpr (D16) c = r0.cbase + (int)static_cast<const int16_t*>(cols)[k];
+          else c = static_cast<const int*>(cols)[k];
+          t += av[k] * op.x(c);
+        }
+        t = wave_sum(t);
+        if (rl == i) sum = t;
+      }
+    }
+    if (row < n && part == 0) RowPre<Op>::row(op, row, sum, pre, acc);
     r0 = r1;
     r1 = r2;
     e0 = e1;
@@ -526,6 +559,17 @@ void launch_stream_l(int n, const int* rp, const void* cols, const int* gbase, c
     if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
 }
 
+// Streamed rows of a CSR matrix with short rows: groups of 64 rows up to 7.5
+// entries a row, of 32 up to 15 (the group's entries then fill eight loads per
+// lane).  Longer rows: lanes per row.
+inline bool stream_rows(int n, long nnz) { return nnz <= 15L * n; }
+template <typename T, class Op>
+void launch_stream(int n, long nnz, const int* rp, const int* ci, const T* av, const Op& op, RedCtx rc,
+                   hipStream_t s) {
+  if (2 * nnz <= 15L * n) launch_stream_l<T, Op, 64, 8, false, false>(n, rp, ci, nullptr, av, op, rc, s);
+  else launch_stream_l<T, Op, 32, 8, false, false>(n, rp, ci, nullptr, av, op, rc, s);
+}
+
 template <typename T, class Op>
 void launch_rows(int n, int lpr, const int* rp, const int* ci, const T* av, const Op& op, RedCtx rc,
                  hipStream_t s) {
@@ -607,10 +651,13 @@ void launch_elem(int n, const Op& op, RedCtx rc, hipStream_t s) {
     if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
 }
 
+// Lanes per row from the average row length: about two entries per lane, as a
+// lane keeps four in flight (7 entries a row, 28.5 M entries: 4 lanes 100 us,
+// 8 lanes 125; 13.4 a row, 4.9 M entries: 8 lanes 19.8 us, 16 lanes 22.2).
 inline int pick_lpr(int n, int nnz) {
   double avg = n > 0 ? (double)nnz / n : 1.0;
   int l = 1;
-  while (l < avg && l < 64) l <<= 1;
+  while (2 * l < avg && l < 64) l <<= 1;
   return l < 2 ? 2 : l;
 }
 

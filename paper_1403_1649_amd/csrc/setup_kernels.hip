@@ -866,6 +866,27 @@ void launch_mis_lists(int n, const int* gptr, const int* gcol, const uint64_t* T
   scan_to_ptr(ml.fnear, ml.pnear, n, sc, s);
   k_compact<<<grid_for(n), kT, 0, s>>>(n, ml.fnear, ml.pnear, ml.near);
 }
+// one wave per row
+__global__ void __launch_bounds__(256) k_check_dominant(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                        const double* __restrict__ val, const double* __restrict__ B,
+                                                        int* err) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int i = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  if (i >= n) return;
+  double d = 0.0, off = 0.0;
+  for (int k = rp[i] + lane; k < rp[i + 1]; k += kWave) {
+    const int j = ci[k];
+    if (j == i) d = val[k] * fabs(B[i]);
+    else off += fabs(val[k]) * fabs(B[j]);
+  }
+  d = wave_sum(d);
+  off = wave_sum(off);
+  if (lane == 0 && !(d >= (1.0 - 1e-10) * off && d > 0.0)) atomic_or_flag(err, kErrNotSPD);
+}
+void launch_check_dominant(int n, const int* rp, const int* ci, const double* val, const double* B, int* err,
+                           hipStream_t s) {
+  if (n > 0) k_check_dominant<<<(n + 3) / 4, 256, 0, s>>>(n, rp, ci, val, B, err);
+}
 void launch_root_flags(int n, const uint64_t* T, int* flags, hipStream_t s) {
   k_root_flags<<<grid_for(n), kT, 0, s>>>(n, T, flags);
 }

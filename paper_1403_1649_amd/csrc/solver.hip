@@ -100,11 +100,16 @@ struct OpResid2 {
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
   __device__ T x(int j) const { return xv[j]; }
-  __device__ void row(int i, T ax, double*) const {
-    const T t = b[i] - ax;
+  struct Pre {
+    T b, x, w;
+  };
+  __device__ Pre pre(int i) const { return Pre{b[i], xv[i], wd[i]}; }
+  __device__ void row(int i, T ax, Pre p, double*) const {
+    const T t = p.b - ax;
     r[i] = t;
-    y[i] = xv[i] + wd[i] * t;
+    y[i] = p.x + p.w * t;
   }
+  __device__ void row(int i, T ax, double* acc) const { row(i, ax, pre(i), acc); }
   __device__ void finalize(const double*) const {}
 };
 
@@ -442,10 +447,15 @@ struct OpKDots1 {
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const { F[0] = 0; }
   __device__ T x(int j) const { return c[j]; }
-  __device__ void row(int i, T ax, double* acc) const {
+  struct Pre {
+    T r, c;
+  };
+  __device__ Pre pre(int i) const { return Pre{rcv[i], c[i]}; }
+  __device__ void row(int i, T ax, double* acc) const { row(i, ax, pre(i), acc); }
+  __device__ void row(int i, T ax, Pre p, double* acc) const {
     v[i] = ax;
-    const double av = (double)ax, rr = (double)rcv[i];
-    const double l = gmres ? av : (double)c[i];
+    const double av = (double)ax, rr = (double)p.r;
+    const double l = gmres ? av : (double)p.c;
     acc[0] += l * av;
     acc[1] += l * rr;
     acc[2] += rr * rr;
@@ -489,12 +499,17 @@ struct OpKDots2 {
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
   __device__ T x(int j) const { return d[j]; }
-  __device__ void row(int i, T ax, double* acc) const {
+  struct Pre {
+    T d, v, rt;
+  };
+  __device__ Pre pre(int i) const { return Pre{d[i], v[i], rt[i]}; }
+  __device__ void row(int i, T ax, double* acc) const { row(i, ax, pre(i), acc); }
+  __device__ void row(int i, T ax, Pre p, double* acc) const {
     w[i] = ax;
-    const double l = gmres ? (double)ax : (double)d[i];
-    acc[0] += l * (double)v[i];
+    const double l = gmres ? (double)ax : (double)p.d;
+    acc[0] += l * (double)p.v;
     acc[1] += l * (double)ax;
-    acc[2] += l * (double)rt[i];
+    acc[2] += l * (double)p.rt;
   }
   __device__ void finalize(const double* s) const {
     const double gamma = s[0], beta = s[1], alpha2 = s[2];
@@ -992,6 +1007,7 @@ void launch_level(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
   else if (t.fmt >= 1 && lv.sl_ptr)
     launch_sell<T>(lv.n, lv.nslices, lv.sl_ptr, lv.sl_col, sell_vals<T>(lv), op, rc, s,
                    t.fmt == 2 ? lv.sl_dcol : nullptr, t.pz);
+  else if (t.lpr == 1) launch_stream<T>(lv.n, lv.nnz, lv.rp, lv.ci, vals<T>(lv), op, rc, s);
   else launch_rows<T>(lv.n, t.lpr, lv.rp, lv.ci, vals<T>(lv), op, rc, s);
 }
 
@@ -1738,7 +1754,7 @@ struct GmView {
   double* sn;
   double* g;
   double* y;
-  double* misc;   // misc[0] = ||b||, misc[1] = inner steps of this cycle
+  double* misc;   // misc[0] = ||b||, misc[1] = inner steps of this cycle, misc[2] = h_{j+1,j} of the last
   int m;
 };
 
@@ -1790,60 +1806,118 @@ struct OpGmInit {
   }
 };
 
-// w = A z_j (z in the cycle precision) with v_0' w -> H[0][j]
+// w = A z_j (z in the cycle precision), z_j kept
 template <typename T>
 struct OpGmSpmv {
-  static constexpr int NV = 1;
+  static constexpr int NV = 0;
   Act a;
   const T* z;
-  const double* v0;
+  T* zj;
   double* w;
-  double* hout;
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
   __device__ double x(int j) const { return (double)z[j]; }
-  __device__ void row(int i, double ax, double* acc) const {
+  __device__ void row(int i, double ax, double*) const {
     w[i] = ax;
-    acc[0] += v0[i] * ax;
+    zj[i] = z[i];
   }
-  __device__ void finalize(const double* s) const { *hout = s[0]; }
+  __device__ void finalize(const double*) const {}
 };
 
-struct OpGmAxpyDot {
-  static constexpr int NV = 1;
-  Act a;
-  const double* vi;
-  const double* vn;   // nullptr: the norm of w
-  double* w;
-  const double* hcoef;
-  double* out;
-  __device__ bool active() const { return a.on(); }
-  __device__ void idle() const {}
-  __device__ void elem(int i, double* acc) const {
-    const double t = w[i] - (*hcoef) * vi[i];
-    w[i] = t;
-    acc[0] += (vn ? vn[i] : t) * t;
-  }
-  __device__ void finalize(const double* s) const { *out = vn ? s[0] : sqrt(s[0]); }
-};
-
+// v = in / *den, and the cycle's next right-hand side (its precision)
+template <typename T>
 struct OpGmScale {
   static constexpr int NV = 0;
   Act a;
   const double* in;
   double* out;
+  T* rhs;
   const double* den;
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
-  __device__ void elem(int i, double*) const { out[i] = in[i] / *den; }
+  __device__ void elem(int i, double*) const {
+    const double t = in[i] / *den;
+    out[i] = t;
+    rhs[i] = (T)t;
+  }
   __device__ void finalize(const double*) const {}
 };
 
-// Givens update of column j and the convergence test
-__global__ void k_gm_givens(GmView gv, int j, double rtol, int* ctl, int* err) {
+// Orthogonalisation of w against V_0 .. V_{J-1}: classical Gram-Schmidt, done
+// twice (the second pass takes off what rounding left of the first, so the
+// basis is orthogonal to working precision; modified Gram-Schmidt, one dot and
+// one update per vector, was 2 J dependent launches of 4 us on 250,000 rows).
+// A pass is two launches: all dots (four basis vectors per block column, one
+// partial per block), then the update, whose blocks each sum the partials
+// themselves, so no launch stands between.
+constexpr int kGmVec = 4;
+constexpr int kGmMax = 64;   // restart length at most
+__global__ void __launch_bounds__(256) k_gm_dots(int n, int J, const double* __restrict__ V, size_t ld,
+                                                 const double* __restrict__ w, double* __restrict__ part, Act a) {
+  if (!a.on()) return;
+  __shared__ double red[kGmVec * 4];
+  const int v0 = blockIdx.y * kGmVec;
+  double acc[kGmVec] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    const double t = w[i];
+#pragma unroll
+    for (int q = 0; q < kGmVec; ++q)
+      if (v0 + q < J) acc[q] += V[(size_t)(v0 + q) * ld + i] * t;
+  }
+  block_sum<kGmVec>(acc, red);
+  if (threadIdx.x == 0)
+    for (int q = 0; q < kGmVec && v0 + q < J; ++q) part[(size_t)(v0 + q) * gridDim.x + blockIdx.x] = acc[q];
+}
+
+// w -= sum_i h_i V_i with h_i = sum of the nb partials; hcol (stride m, block
+// 0): h_i, added to the first pass's on the second, which also leaves the
+// partials of ||w||^2 in npart.
+template <bool SECOND>
+__global__ void __launch_bounds__(256) k_gm_update(int n, int J, const double* __restrict__ V, size_t ld,
+                                                   double* __restrict__ w, const double* __restrict__ part, int nb,
+                                                   double* __restrict__ hcol, int m, double* __restrict__ npart,
+                                                   Act a) {
+  if (!a.on()) return;
+  __shared__ double hs[kGmMax];
+  __shared__ double red[4];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  for (int v = wv; v < J; v += 4) {
+    double t = 0.0;
+    for (int b = lane; b < nb; b += kWave) t += part[(size_t)v * nb + b];
+    t = wave_sum(t);
+    if (lane == 0) {
+      hs[v] = t;
+      if (blockIdx.x == 0) hcol[(size_t)v * m] = SECOND ? hcol[(size_t)v * m] + t : t;
+    }
+  }
+  __syncthreads();
+  double acc[1] = {0.0};
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+    double t = w[i];
+#pragma unroll 4
+    for (int v = 0; v < J; ++v) t -= hs[v] * V[(size_t)v * ld + i];
+    w[i] = t;
+    acc[0] += t * t;
+  }
+  if constexpr (SECOND) {
+    block_sum<1>(acc, red);
+    if (threadIdx.x == 0) npart[blockIdx.x] = acc[0];
+  }
+}
+
+// ||w|| (kept in misc[2] for the scaling), the Givens update of column j and
+// the convergence test; progress (pinned host words): steps done, stopped
+__global__ void __launch_bounds__(256) k_gm_givens(GmView gv, int j, double rtol, const double* __restrict__ npart,
+                                                   int nb, int* ctl, int* err, int* progress) {
   if (!ctl[kCtlRunning]) return;
+  __shared__ double red[4];
+  double nw[1] = {0.0};
+  for (int b = threadIdx.x; b < nb; b += 256) nw[0] += npart[b];
+  block_sum<1>(nw, red);
+  if (threadIdx.x != 0) return;
   const int m = gv.m;
   double* Hc = gv.H;   // H[i][j] at Hc[i * m + j]
+  gv.misc[2] = Hc[(j + 1) * m + j] = sqrt(nw[0]);
   for (int i = 0; i < j; ++i) {
     const double t = gv.cs[i] * Hc[i * m + j] + gv.sn[i] * Hc[(i + 1) * m + j];
     Hc[(i + 1) * m + j] = -gv.sn[i] * Hc[i * m + j] + gv.cs[i] * Hc[(i + 1) * m + j];
@@ -1853,19 +1927,22 @@ __global__ void k_gm_givens(GmView gv, int j, double rtol, int* ctl, int* err) {
   const double den = hypot(hjj, hj1);
   ctl[kCtlIters] += 1;
   gv.misc[1] = j + 1;
+  bool stop = false;
   if (!(den > 0.0) || !__builtin_isfinite(den)) {
     if (!__builtin_isfinite(den)) *err |= kErrNonFinite;
-    ctl[kCtlRunning] = 0;
     gv.misc[1] = j;   // nothing usable from this column
-    return;
+    stop = true;
+  } else {
+    gv.cs[j] = hjj / den;
+    gv.sn[j] = hj1 / den;
+    Hc[j * m + j] = den;
+    Hc[(j + 1) * m + j] = 0.0;
+    gv.g[j + 1] = -gv.sn[j] * gv.g[j];
+    gv.g[j] = gv.cs[j] * gv.g[j];
+    stop = fabs(gv.g[j + 1]) <= rtol * gv.misc[0] || hj1 == 0.0;
   }
-  gv.cs[j] = hjj / den;
-  gv.sn[j] = hj1 / den;
-  Hc[j * m + j] = den;
-  Hc[(j + 1) * m + j] = 0.0;
-  gv.g[j + 1] = -gv.sn[j] * gv.g[j];
-  gv.g[j] = gv.cs[j] * gv.g[j];
-  if (fabs(gv.g[j + 1]) <= rtol * gv.misc[0] || hj1 == 0.0) ctl[kCtlRunning] = 0;
+  if (stop) ctl[kCtlRunning] = 0;
+  __hip_atomic_store(progress, stop ? kGmMax + 1 : j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // y = R^-1 g over the inner steps of the cycle (back substitution)
@@ -1898,26 +1975,44 @@ struct OpGmUpdate {
   __device__ void finalize(const double*) const {}
 };
 
+// The host launches a step when the step kGmAhead before it is done (a word in
+// pinned memory that k_gm_givens writes), so that few steps are launched in
+// vain after the last; a stream that has run dry ends the wait.
+constexpr int kGmAhead = 3;
+constexpr int kGmProgressSlot = 48;   // pinned int slot
+void gm_wait(volatile int* progress, int step, hipStream_t s) {
+  while (*progress < step) {
+    if (hipStreamQuery(s) != hipErrorNotReady) break;
+  }
+  (void)hipGetLastError();   // hipErrorNotReady is not an error here
+}
+
 template <typename T>
 int fgmres(Hierarchy& h, const double* b, double rtol, double* x, int* iters, double* relres) {
   Level& l0 = h.levels[0];
   hipStream_t s = h.stream;
   RedCtx rc = red(h);
   const int n = l0.n;
-  const int m = std::max(1, std::min(h.opt.gmres_restart, 64));
+  const int m = std::max(1, std::min(h.opt.gmres_restart, kGmMax));
   Arena ws;
   struct Drain { hipStream_t s; ~Drain() { (void)hipStreamSynchronize(s); } } drain{s};
   double* V = ws.alloc_n<double>((size_t)(m + 1) * n);
   T* Z = ws.alloc_n<T>((size_t)m * n);
-  float* v32 = sizeof(T) == sizeof(float) ? ws.alloc_n<float>(n) : nullptr;
   double* w = ws.alloc_n<double>(n);
-  double* gmem = ws.alloc_n<double>((size_t)(m + 1) * m + 4 * m + 4);
+  double* gmem = ws.alloc_n<double>((size_t)(m + 1) * m + 4 * m + 8);
+  const int nb = std::max(1, std::min(256, n / 2048));   // blocks per dot, of the update
+  const int nu = elem_grid(n, true) < 512 ? elem_grid(n, true) : 512;
+  double* part = ws.alloc_n<double>((size_t)m * nb);
+  double* npart = ws.alloc_n<double>(nu);
   GmView gv = gm_view(gmem, m);
   const int* run = h.d_ctl + kCtlRunning;
   const Act A{run};
   double* xv = h.xint;
   int* hp = static_cast<int*>(h.h_pinned);
   double* hd = reinterpret_cast<double*>(hp + 16);
+  volatile int* progress = hp + kGmProgressSlot;
+  T* rhs = sizeof(T) == sizeof(float) ? static_cast<T*>(h.bz) : reinterpret_cast<T*>(h.r);
+  T* z = static_cast<T*>(h.z);
   launch_fill_double(n, xv, 0.0, s);
   set_ctl(h, kCtlIters, 0);
   int status = AMG_OK;
@@ -1927,24 +2022,23 @@ int fgmres(Hierarchy& h, const double* b, double rtol, double* x, int* iters, do
     const int steps = std::min(m, h.opt.max_iter - done_before);
     launch_level<double>(l0, OpGmInit{Act{nullptr}, b, xv, w, gv, first ? 1 : 0, rtol, h.d_ctl, h.d_err}, rc, s);
     first = false;
-    launch_elem(n, OpGmScale{A, w, V, gv.g}, rc, s);
+    launch_elem(n, OpGmScale<T>{A, w, V, rhs, gv.g}, rc, s);
+    *progress = 0;   // the previous cycle has been waited for
     for (int j = 0; j < steps; ++j) {
-      double* vj = V + (size_t)j * n;
-      T* zj = Z + (size_t)j * n;
-      if constexpr (sizeof(T) == sizeof(float)) {
-        launch_elem(n, OpToFloat{A, vj, v32}, rc, s);
-        cycle<float>(h, 0, v32, reinterpret_cast<float*>(zj), run);
-      } else {
-        cycle<double>(h, 0, vj, reinterpret_cast<double*>(zj), run);
-      }
-      launch_level<double>(l0, OpGmSpmv<T>{A, zj, V, w, gv.H + j}, rc, s);
-      for (int i = 0; i <= j; ++i) {
-        const double* vi = V + (size_t)i * n;
-        const double* vn = i < j ? V + (size_t)(i + 1) * n : nullptr;
-        launch_elem(n, OpGmAxpyDot{A, vi, vn, w, gv.H + (size_t)i * m + j, gv.H + (size_t)(i + 1) * m + j}, rc, s);
-      }
-      launch_elem(n, OpGmScale{A, w, V + (size_t)(j + 1) * n, gv.H + (size_t)(j + 1) * m + j}, rc, s);
-      k_gm_givens<<<1, 1, 0, s>>>(gv, j, rtol, h.d_ctl, h.d_err);
+      gm_wait(progress, j - kGmAhead, s);
+      if (*progress > kGmMax) break;
+      if (!h.g_iter.empty()) AMG_HIP(hipGraphLaunch(h.g_iter[0], s));
+      else precondition<T>(h, run, nullptr, true);
+      launch_level<double>(l0, OpGmSpmv<T>{A, z, Z + (size_t)j * n, w}, rc, s);
+      const dim3 gd(nb, (j + kGmVec) / kGmVec);
+      double* hcol = gv.H + j;
+      k_gm_dots<<<gd, 256, 0, s>>>(n, j + 1, V, (size_t)n, w, part, A);
+      k_gm_update<false><<<nu, 256, 0, s>>>(n, j + 1, V, (size_t)n, w, part, nb, hcol, m, nullptr, A);
+      k_gm_dots<<<gd, 256, 0, s>>>(n, j + 1, V, (size_t)n, w, part, A);
+      k_gm_update<true><<<nu, 256, 0, s>>>(n, j + 1, V, (size_t)n, w, part, nb, hcol, m, npart, A);
+      k_gm_givens<<<1, 256, 0, s>>>(gv, j, rtol, npart, nu, h.d_ctl, h.d_err, const_cast<int*>(progress));
+      if (j + 1 < steps)
+        launch_elem(n, OpGmScale<T>{A, w, V + (size_t)(j + 1) * n, rhs, gv.misc + 2}, rc, s);
     }
     k_gm_trisolve<<<1, 1, 0, s>>>(gv);
     launch_elem(n, OpGmUpdate<T>{Z, (size_t)n, gv, xv}, rc, s);
@@ -2146,14 +2240,21 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
     if (std::getenv("AMG_DEBUG")) std::fprintf(stderr, "amg: level n=%d CSR lanes=%d: %.2f us\n", lv.n, lpr, us);
     if (us < best.us) { best.us = us; best.fmt = 0; best.lpr = lpr; }
   }
+  int csr16_lanes = best.lpr;
+  if (stream_rows(lv.n, lv.nnz)) {   // streamed rows (one lane sums a row)
+    const float us = time_it([&] { launch_stream<T>(lv.n, lv.nnz, lv.rp, lv.ci, vals<T>(lv), op, rc, s); });
+    if (std::getenv("AMG_DEBUG"))
+      std::fprintf(stderr, "amg: level n=%d CSR streamed: %.2f us (best so far %.2f)\n", lv.n, us, best.us);
+    if (us < best.us) { best.us = us; best.fmt = 0; best.lpr = 1; }
+  }
   if (lv.ci16) {   // 16-bit column offsets: 2 bytes less per entry, taken within kPreferFewerBytes of CSR
     // the same rows and lanes as CSR with fewer bytes: timed with CSR's best lanes only
-    const int lpr = best.lpr;
+    const int lpr = csr16_lanes;
     const float us = time_it([&] { launch_rows16<T>(lv.n, lpr, lv.rp, lv.ci16, vals<T>(lv), op, rc, s); });
     if (std::getenv("AMG_DEBUG"))
       std::fprintf(stderr, "amg: level n=%d CSR 16-bit offsets lanes=%d: %.2f us (best so far %.2f)\n", lv.n, lpr,
                    us, best.us);
-    if (us <= kPreferFewerBytes * best.us) { best.us = std::min(us, best.us); best.fmt = 4; }
+    if (us <= kPreferFewerBytes * best.us) { best.us = std::min(us, best.us); best.fmt = 4; best.lpr = lpr; }
   }
   const int off = (lv.sl_ptr && sell_vals<T>(lv)) || dia_vals<T>(lv) ? max_column_offset(h, lv) : 0;
   if (lv.sl_ptr && sell_vals<T>(lv)) {
@@ -2219,7 +2320,7 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
       if (lv.ci16) {
         best.fmt = 4;
         best.sh = 0;
-        if (best.lpr < 2) best.lpr = 4;
+        best.lpr = csr16_lanes;
       }
     } else if (w == "sdia") {
       if (dia_vals<T>(lv)) {
@@ -2316,8 +2417,8 @@ int solve_fcg_impl(Hierarchy& h, const double* b, double rtol, double* x, int* i
   return fcg(h, b, rtol, x, iters, relres);
 }
 
-// Capture one outer iteration and the (re)start sequence into HIP graphs on
-// a private stream; the solve replays them on the caller's stream.  Every
+// Capture one outer iteration and the (re)start sequence (flexible GMRES: one
+// application of the cycle) into HIP graphs on a private stream; the solve replays them on the caller's stream.  Every
 // captured kernel reads its device flag, so one graph serves all branches.
 void build_solve_graphs(Hierarchy& h) {
   hipStream_t user = h.stream;
@@ -2338,12 +2439,25 @@ void build_solve_graphs(Hierarchy& h) {
     // outer iteration, split at the probed kernel when a probe is selected
     h.split_at_probe = h.opt.probe != AMG_PROBE_NONE && h.pev[0];
     AMG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
-    if (mixed) fcg_iteration<float>(h, run);
-    else fcg_iteration<double>(h, run);
+    if (h.opt.krylov == AMG_KRYLOV_FGMRES) {   // one application of the cycle
+      if (mixed) precondition<float>(h, run, nullptr, true);
+      else precondition<double>(h, run);
+    } else if (mixed) {
+      fcg_iteration<float>(h, run);
+    } else {
+      fcg_iteration<double>(h, run);
+    }
     hipGraphExec_t last = nullptr;
     finish(&last);
     h.g_iter.push_back(last);
     h.split_at_probe = false;
+    if (h.opt.krylov == AMG_KRYLOV_FGMRES) {
+      h.stream = user;
+      h.capturing = false;
+      h.cap_stream = nullptr;
+      AMG_HIP(hipStreamDestroy(cs));
+      return;
+    }
     // (re)start sequence
     AMG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed));
     if (mixed) fcg_restart<float>(h, run);
@@ -2504,8 +2618,12 @@ void level_spmv(const Hierarchy& h, int k, const double* x, double* y, hipStream
 // y = A x for a caller's matrix (float64)
 void spmv_f64(int n, int nnz, const int* rp, const int* ci, const double* val, const double* x, double* y,
               int lpr, hipStream_t s) {
-  if (lpr <= 0) lpr = pick_lpr(n, nnz);
   RedCtx rc{nullptr, nullptr};
+  if (lpr <= 0 && n > kFuseCorrectionRows && stream_rows(n, nnz)) {
+    launch_stream<double>(n, nnz, rp, ci, val, OpSpmv<double>{Act{nullptr}, x, y}, rc, s);
+    return;
+  }
+  if (lpr <= 0) lpr = pick_lpr(n, nnz);
   launch_rows<double>(n, lpr, rp, ci, val, OpSpmv<double>{Act{nullptr}, x, y}, rc, s);
 }
 
