@@ -407,290 +407,159 @@ __global__ void k_dense_scatter_batched(const TermInfo* __restrict__ ti, const i
     for (int k = rp[row]; k < rp[row + 1]; ++k) W[(size_t)r * t.n + (ci[k] - t.row0)] = val[k];
   }
 }
-// ---------------------------------------------------------------- SPD, blocked
-// A symmetric positive definite matrix needs no pivoting in Gauss-Jordan
-// elimination: every pivot is a diagonal entry of a Schur complement, hence
-// positive.  Panels of b columns: the panel's b steps run in one workgroup
-// with the panel held in registers (no pivot search, so one step is two
-// barriers and one broadcast of the pivot row); every other column then receives the panel's combined
-// elementary transformation M = I + (Y - E) E^T at once, where Y is the panel
-// after its steps and E the unit columns of the panel's pivot rows:
-// A_J <- A_J + (Y - E) T with T = the panel's pivot rows of A_J before the
-// update.  That rank-b update is a tiled product over all columns of all
-// systems; no grid barrier is needed because panel and update are separate
-// launches.  A non-positive or non-finite pivot raises kErrNotSPD and the
-// caller falls back to the pivoting kernels.
-constexpr int kPanelThreads = 1024;
-constexpr int kUpdTile = 64;
+// ---------------------------------------------------------------- no pivoting, blocked
+// A symmetric positive definite matrix (or a diagonally dominant one) needs no
+// pivoting in Gauss-Jordan elimination: every pivot is a diagonal entry of a
+// Schur complement, hence positive.  One panel K of 32 columns is one launch:
+// with M the inverse of the pivot block and U_J = M A_KJ,
+//   A_KJ <- U_J,  A_iJ <- A_iJ - A_iK U_J,  A_KK <- M,  A_iK <- -A_iK M,
+// every 32 x 32 tile by a workgroup of its own from the matrix before the
+// panel, into a second buffer (the two swap), so nothing is read after it was
+// written and no launch stands between pivot block and update.  The products
+// are FP64 matrix-core steps (each wave one 16 x 16 quarter); the pivot block
+// is inverted by one wave in registers, by every workgroup for itself.  These
+// matrices are small: what bounds the inversion is the chain of panels.  244
+// unknowns: 8 panels of 50 us when pivot block (a workgroup with two barriers
+// per step), its product, and two updates were four launches.
+constexpr int kB = 32;
 
-// The panel: thread t owns rows t, t + 1024, ... (R of them) and keeps their
-// B panel entries in registers (B * R = 32); per step only the pivot row goes
-// through LDS.  In-place Gauss-Jordan step k restricted to the panel:
-// pivot row scaled by 1/p, other rows minus their column-k entry times the
-// scaled pivot row, column k replaced by -a_ik/p (and 1/p at the pivot).
-template <int B, int R>
-__global__ void __launch_bounds__(kPanelThreads) k_gjb_panel_reg(const TermInfo* __restrict__ ti,
-                                                                 double* __restrict__ work,
-                                                                 double* __restrict__ ybuf,
-                                                                 double* __restrict__ tbuf, int K, int* err) {
-  __shared__ double s_row[B];
-  const TermInfo t = ti[blockIdx.x];
-  const int n = t.n, c0 = K * B;
-  if (c0 >= n) return;
-  const int w = min(B, n - c0);
-  double* W = work + t.off;
-  double* Y = ybuf + (size_t)t.row0 * B;
-  double* T = tbuf + (size_t)t.row0 * B;
-  const int tid = threadIdx.x;
-  const int nt = blockDim.x;
-  for (int e = tid; e < w * n; e += nt) {
-    const int j = e / n, J = e - j * n;
-    T[(size_t)j * n + J] = W[(size_t)(c0 + j) * n + J];
-  }
-  double P[R][B];
+// In-place Gauss-Jordan inverse of a 32 x 32 block held by a wave: lane l has
+// row l % 32, columns 16 (l / 32) .. + 15.  Returns whether every pivot was
+// positive and finite.
+__device__ __forceinline__ bool invert_block(double (&a)[16], int lane) {
+  const int row = lane & 31, half = lane >> 5;
+  bool ok = true;
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = tid + r * nt;
-#pragma unroll
-    for (int q = 0; q < B; ++q) P[r][q] = (i < n && q < w) ? W[(size_t)i * n + c0 + q] : 0.0;
-  }
-  // the step loop stays rolled (one copy of the unrolled column loop), so the
-  // pivot column entry is selected with compares instead of a runtime index
-#pragma unroll 1
-  for (int j = 0; j < w; ++j) {
-    const int k = c0 + j;
-    if (tid == k % nt) {
-      const int rk = k / nt;
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (r == rk) {
-#pragma unroll
-          for (int q = 0; q < B; ++q) s_row[q] = P[r][q];
-        }
-    }
-    __syncthreads();
-    const double p = s_row[j];
-    if (tid == 0 && !(p > 0.0 && p < INFINITY)) atomic_or_flag(err, kErrNotSPD);
+  for (int j = 0; j < kB; ++j) {
+    const int oh = j / 16;   // the half that holds column j
+    const double c = __shfl(a[j % 16], row + 32 * oh, kWave);
+    const double p = __shfl(c, j, kWave);
+    ok = ok && p > 0.0 && p < INFINITY;
     const double inv = 1.0 / p;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = tid + r * nt;
-      double c = 0.0;
-#pragma unroll
-      for (int q = 0; q < B; ++q) c = (q == j) ? P[r][q] : c;
-#pragma unroll
-      for (int q = 0; q < B; ++q) {
-        if (q == j) {
-          P[r][q] = (i == k) ? inv : -c * inv;
-        } else {
-          const double rk = s_row[q] * inv;
-          P[r][q] = (i == k) ? rk : P[r][q] - c * rk;
-        }
-      }
+    for (int q = 0; q < 16; ++q) {
+      const double rk = __shfl(a[q], j + 32 * half, kWave) * inv;
+      a[q] = row == j ? rk : a[q] - c * rk;
     }
-    __syncthreads();
+    if (half == oh) a[j % 16] = row == j ? inv : -c * inv;
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = tid + r * nt;
-    if (i >= n) continue;
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
-      if (q < w) {
-        W[(size_t)i * n + c0 + q] = P[r][q];
-        Y[(size_t)i * B + q] = P[r][q];
-      }
-    }
-  }
+  return ok;
 }
 
-// The panel in two launches, so that one workgroup per system only does the
-// b steps on the b x b pivot block.  A step is linear in every non-pivot row:
-// row <- row * E_j, where E_j depends only on the pivot row of step j.  So the
-// pivot block's workgroup also runs the steps on b virtual rows that start as
-// the unit rows, which end as X = E_0 E_1 ... E_{b-1}; every other row of the
-// panel is then row * X, a (n - b) x b x b product done by many workgroups.
-// k_gjb_pivot: one workgroup per system, the 64 x 32 block (32 pivot rows,
-// then the 32 virtual rows) in LDS and every element updated in parallel at
-// each step (two per thread), with the arithmetic of the register panel:
-// pivot row s / p, column j -c / p (1 / p at the pivot), others a - c (s / p).
-__global__ void __launch_bounds__(1024) k_gjb_pivot(const TermInfo* __restrict__ ti, double* __restrict__ work,
-                                                    double* __restrict__ ybuf, double* __restrict__ xbuf, int K,
-                                                    int* err) {
-  constexpr int B = 32, ROWS = 2 * B;
-  __shared__ double M[ROWS][B + 1];
+// the pivot block of panel K: rows and columns c0 .. c0 + w - 1, identity beyond
+__device__ __forceinline__ bool load_and_invert(const double* __restrict__ A, int n, int c0, int w, int lane,
+                                                double (&a)[16]) {
+  const int row = lane & 31, col0 = 16 * (lane >> 5);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int col = col0 + q;
+    a[q] = row < w && col < w ? A[(size_t)(c0 + row) * n + c0 + col] : (row == col ? 1.0 : 0.0);
+  }
+  return invert_block(a, lane);
+}
+
+// Buffer that holds system t before panel K: the swap ends in `inv`.
+__device__ __forceinline__ bool source_is_inv(int n, int K) { return ((n + kB - 1) / kB - K) % 2 == 0; }
+
+// dense copies of the systems' diagonal blocks (32 rows per workgroup)
+__global__ void __launch_bounds__(256) k_gji_init(const TermInfo* __restrict__ ti, const int* __restrict__ rp,
+                                                  const int* __restrict__ ci, const double* __restrict__ val,
+                                                  double* __restrict__ inv, double* __restrict__ work) {
+  const TermInfo t = ti[blockIdx.y];
+  const int r0 = blockIdx.x * kB, rows = min(kB, t.n - r0);
+  if (rows <= 0) return;
+  double* W = (source_is_inv(t.n, 0) ? inv : work) + t.off + (size_t)r0 * t.n;
+  for (int e = threadIdx.x; e < rows * t.n; e += 256) W[e] = 0.0;
+  __syncthreads();   // the zeros are written before the entries
+  const int r = threadIdx.x / 8;
+  if (r >= rows) return;
+  const int i = t.row0 + r0 + r;
+  for (int k = rp[i] + (threadIdx.x & 7); k < rp[i + 1]; k += 8) W[(size_t)r * t.n + (ci[k] - t.row0)] = val[k];
+}
+
+// pivot blocks of panel K, one wave per system, for launches with so many
+// tiles that inverting it in each costs more than a launch
+__global__ void __launch_bounds__(kWave) k_gji_pivot(const TermInfo* __restrict__ ti, const double* __restrict__ inv,
+                                                     const double* __restrict__ work, double* __restrict__ mbuf,
+                                                     int K, int* err) {
   const TermInfo t = ti[blockIdx.x];
-  const int n = t.n, c0 = K * B;
-  if (c0 >= n) return;
-  const int w = min(B, n - c0);
-  double* W = work + t.off;
-  double* Y = ybuf + (size_t)t.row0 * B;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < ROWS * B; e += 1024) {
-    const int i = e / B, q = e % B;
-    M[i][q] = i < B ? ((i < w && q < w) ? W[(size_t)(c0 + i) * n + c0 + q] : 0.0) : (q == i - B ? 1.0 : 0.0);
+  const int c0 = K * kB;
+  if (c0 >= t.n) return;
+  double a[16];
+  const int lane = threadIdx.x;
+  const double* A = (source_is_inv(t.n, K) ? inv : work) + t.off;
+  if (!load_and_invert(A, t.n, c0, min(kB, t.n - c0), lane, a) && lane == 0) atomic_or_flag(err, kErrNotSPD);
+#pragma unroll
+  for (int q = 0; q < 16; ++q)
+    mbuf[(size_t)blockIdx.x * kB * kB + (lane & 31) * kB + 16 * (lane >> 5) + q] = a[q];
+}
+
+template <bool PIVOT>   // the workgroup inverts the pivot block itself (else mbuf)
+__global__ void __launch_bounds__(256) k_gji_panel(const TermInfo* __restrict__ ti, double* __restrict__ inv,
+                                                   double* __restrict__ work, float* __restrict__ inv32,
+                                                   const double* __restrict__ mbuf, int K, int* err) {
+  __shared__ double sM[kB][kB + 1], sA[kB][kB + 1], sT[kB][kB + 1];
+  const TermInfo t = ti[blockIdx.z];
+  const int n = t.n, c0 = K * kB, r0 = blockIdx.y * kB, q0 = blockIdx.x * kB;
+  if (c0 >= n || r0 >= n || q0 >= n) return;
+  const int w = min(kB, n - c0);
+  const bool from_inv = source_is_inv(n, K);
+  const double* A = (from_inv ? inv : work) + t.off;
+  double* D = (from_inv ? work : inv) + t.off;
+  const bool last = c0 + kB >= n;
+  const bool pr = r0 == c0, pc = q0 == c0;   // in the pivot rows / columns
+  const int tid = threadIdx.x, wv = tid / kWave, l = tid & (kWave - 1);
+  if constexpr (PIVOT) {
+    if (wv == 0) {
+      double a[16];
+      const bool ok = load_and_invert(A, n, c0, w, l, a);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) sM[l & 31][16 * (l >> 5) + q] = a[q];
+      if (pr && pc && !ok && l == 0) atomic_or_flag(err, kErrNotSPD);
+    }
+  } else {
+    for (int e = tid; e < kB * kB; e += 256) sM[e / kB][e % kB] = mbuf[(size_t)blockIdx.z * kB * kB + e];
+  }
+  const int first = PIVOT ? kWave : 0, cnt = 256 - first;
+  if (tid >= first) {
+    for (int e = tid - first; e < kB * kB; e += cnt) {
+      const int i = e / kB, j = e % kB;
+      sA[i][j] = !pr && r0 + i < n && j < w ? A[(size_t)(r0 + i) * n + c0 + j] : 0.0;
+      sT[i][j] = !pc && i < w && q0 + j < n ? A[(size_t)(c0 + i) * n + q0 + j] : 0.0;
+    }
   }
   __syncthreads();
-#pragma unroll 1
-  for (int j = 0; j < w; ++j) {
-    const double p = M[j][j];
-    if (tid == 0 && !(p > 0.0 && p < INFINITY)) atomic_or_flag(err, kErrNotSPD);
-    const double inv = 1.0 / p;
-    double nv[2];
+  const int tr = 16 * (wv >> 1), tc = 16 * (wv & 1);   // this wave's quarter
+  f64x4 u = {0.0, 0.0, 0.0, 0.0};
+  if (!pc) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = tid + h * 1024, i = e / B, q = e % B;
-      const double c = M[i][j];
-      if (q == j) {
-        nv[h] = (i == j) ? inv : -c * inv;
-      } else {
-        const double rk = M[j][q] * inv;
-        nv[h] = (i == j) ? rk : M[i][q] - c * rk;
-      }
-    }
+    for (int kk = 0; kk < kB; kk += 4) u = mfma_f64_16x16x4(sM[tr + (l & 15)][kk + (l >> 4)], sT[kk + (l >> 4)][tc + (l & 15)], u);
+    __syncthreads();   // uniform: pc is the block's
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sT[tr + mfma_row(l, i)][tc + mfma_col(l)] = u[i];
     __syncthreads();
+  }
+  const double (*U)[kB + 1] = pc ? sM : sT;
+  f64x4 d;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = tid + h * 1024;
-      M[e / B][e % B] = nv[h];
+  for (int i = 0; i < 4; ++i) {
+    const int row = r0 + tr + mfma_row(l, i), col = q0 + tc + mfma_col(l);
+    if (pr) d[i] = U[tr + mfma_row(l, i)][tc + mfma_col(l)];
+    else d[i] = !pc && row < n && col < n ? A[(size_t)row * n + col] : 0.0;
+  }
+  if (!pr) {
+#pragma unroll
+    for (int kk = 0; kk < kB; kk += 4)
+      d = mfma_f64_16x16x4(-sA[tr + (l & 15)][kk + (l >> 4)], U[kk + (l >> 4)][tc + (l & 15)], d);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = r0 + tr + mfma_row(l, i), col = q0 + tc + mfma_col(l);
+    if (row < n && col < n) {
+      D[(size_t)row * n + col] = d[i];
+      if (last && inv32) inv32[t.off + (size_t)row * n + col] = (float)d[i];
     }
-    __syncthreads();
   }
-  double* X = xbuf + (size_t)blockIdx.x * B * B;
-  for (int e = tid; e < ROWS * B; e += 1024) {
-    const int i = e / B, q = e % B;
-    if (i < B) {
-      if (i < w && q < w) {
-        W[(size_t)(c0 + i) * n + c0 + q] = M[i][q];
-        Y[(size_t)(c0 + i) * B + q] = M[i][q];
-      }
-    } else {
-      X[(i - B) * B + q] = M[i][q];
-    }
-  }
-}
-
-// k_gjb_apply: the non-pivot rows of every system's 32-column panel times X
-// on the FP64 matrix cores (each wave 16 rows x 32 columns: 2 MFMA tiles, 8
-// k-steps).  Work items are (system, block of 256 rows) pairs from the host's
-// table.
-__global__ void __launch_bounds__(256) k_gjb_apply(const TermInfo* __restrict__ ti, const int* __restrict__ items,
-                                                   double* __restrict__ work, double* __restrict__ ybuf,
-                                                   const double* __restrict__ xbuf, int K) {
-  constexpr int B = 32;
-  __shared__ double sX[B][B + 1];
-  const int sys = items[2 * blockIdx.x], rb = items[2 * blockIdx.x + 1];
-  const TermInfo t = ti[sys];
-  const int n = t.n, c0 = K * B;
-  if (c0 >= n) return;
-  const int w = min(B, n - c0);
-  double* W = work + t.off;
-  double* Y = ybuf + (size_t)t.row0 * B;
-  const double* X = xbuf + (size_t)sys * B * B;
-  for (int e = threadIdx.x; e < B * B; e += 256) sX[e / B][e % B] = X[e];
-  __syncthreads();
-  const int wv = threadIdx.x / kWave, l = threadIdx.x & (kWave - 1);
-  for (int R0 = rb * 256 + wv * 16; R0 < min(n, (rb + 1) * 256); R0 += 64) {
-    const int ar = R0 + (l & 15);
-    const bool arow = ar < n && !(ar >= c0 && ar < c0 + w);
-    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-    for (int kk = 0; kk < B; kk += 4) {
-      const int kc = kk + (l >> 4);
-      const double av = (arow && kc < w) ? W[(size_t)ar * n + c0 + kc] : 0.0;
-#pragma unroll
-      for (int sc = 0; sc < 2; ++sc) acc[sc] = mfma_f64_16x16x4(av, sX[kc][16 * sc + (l & 15)], acc[sc]);
-    }
-#pragma unroll
-    for (int sc = 0; sc < 2; ++sc)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = R0 + mfma_row(l, i), col = 16 * sc + mfma_col(l);
-        if (row < n && !(row >= c0 && row < c0 + w) && col < w) {
-          W[(size_t)row * n + c0 + col] = acc[sc][i];
-          Y[(size_t)row * B + col] = acc[sc][i];
-        }
-      }
-  }
-}
-
-// A_J += (Y - E) T for every column J outside the panel: 64 x 64 output tiles
-// on the FP64 matrix cores (each wave a 32 x 32 quadrant = 2 x 2 MFMA tiles,
-// k in steps of 4 over the panel width, zero-padded); the panel's pivot rows
-// get Y T directly.
-// mode 0: every row of the tile, T from tbuf (copied before the panel wrote
-// its pivot rows); mode 1: the rows outside the pivot block only, T read from
-// the pivot rows of A themselves (no launch writes them until mode 2); mode 2:
-// the pivot rows only (tiles (system, column tile), rows from c0), each
-// workgroup reading its columns of the pivot rows before writing them.
-__global__ void __launch_bounds__(256) k_gjb_update(const TermInfo* __restrict__ ti, const int* __restrict__ tiles,
-                                                    double* __restrict__ work, const double* __restrict__ ybuf,
-                                                    const double* __restrict__ tbuf, int K, int b, int mode) {
-  __shared__ double sY[kUpdTile][33];
-  __shared__ double sT[32][kUpdTile + 1];
-  const TermInfo t = ti[tiles[2 * blockIdx.x]];
-  const int n = t.n, c0 = K * b;
-  if (c0 >= n) return;
-  const int w = min(b, n - c0);
-  const int nt = (n + kUpdTile - 1) / kUpdTile;
-  const int tile = tiles[2 * blockIdx.x + 1];
-  const int r0 = mode == 2 ? c0 : (tile / nt) * kUpdTile, q0 = (tile % nt) * kUpdTile;
-  if (q0 >= c0 && q0 + kUpdTile <= c0 + w) return;   // tile entirely inside the panel
-  if (mode == 1 && r0 >= c0 && r0 + kUpdTile <= c0 + w) return;   // pivot rows only: mode 2
-  double* W = work + t.off;
-  const double* Y = ybuf + (size_t)t.row0 * b;
-  const double* T = mode == 0 ? tbuf + (size_t)t.row0 * b : W + (size_t)c0 * n;
-  const int tid = threadIdx.x;
-  const int kw = (w + 3) & ~3;   // panel width padded to the MFMA k step
-  for (int e = tid; e < kUpdTile * kw; e += 256) {
-    const int i = e / kw, j = e - i * kw;
-    sY[i][j] = (r0 + i < n && j < w) ? Y[(size_t)(r0 + i) * b + j] : 0.0;
-  }
-  for (int e = tid; e < kw * kUpdTile; e += 256) {
-    const int j = e / kUpdTile, c = e - j * kUpdTile;
-    sT[j][c] = (q0 + c < n && j < w) ? T[(size_t)j * n + q0 + c] : 0.0;
-  }
-  __syncthreads();
-  const int wv = tid / kWave, l = tid & (kWave - 1);
-  const int qr = (wv >> 1) * 32, qc = (wv & 1) * 32;   // this wave's quadrant
-  f64x4 acc[2][2];
-#pragma unroll
-  for (int sr = 0; sr < 2; ++sr)
-#pragma unroll
-    for (int sc = 0; sc < 2; ++sc)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = r0 + qr + 16 * sr + mfma_row(l, i), col = q0 + qc + 16 * sc + mfma_col(l);
-        const bool pivot_row = row >= c0 && row < c0 + w;
-        acc[sr][sc][i] = (row < n && col < n && !pivot_row) ? W[(size_t)row * n + col] : 0.0;
-      }
-  for (int kk = 0; kk < kw; kk += 4) {
-    double av[2], bv[2];
-#pragma unroll
-    for (int sr = 0; sr < 2; ++sr) av[sr] = sY[qr + 16 * sr + (l & 15)][kk + (l >> 4)];
-#pragma unroll
-    for (int sc = 0; sc < 2; ++sc) bv[sc] = sT[kk + (l >> 4)][qc + 16 * sc + (l & 15)];
-#pragma unroll
-    for (int sr = 0; sr < 2; ++sr)
-#pragma unroll
-      for (int sc = 0; sc < 2; ++sc) acc[sr][sc] = mfma_f64_16x16x4(av[sr], bv[sc], acc[sr][sc]);
-  }
-#pragma unroll
-  for (int sr = 0; sr < 2; ++sr)
-#pragma unroll
-    for (int sc = 0; sc < 2; ++sc)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = r0 + qr + 16 * sr + mfma_row(l, i), col = q0 + qc + 16 * sc + mfma_col(l);
-        const bool pivot_row = row >= c0 && row < c0 + w;
-        const bool mine = mode == 0 || (mode == 1) != pivot_row;
-        if (mine && row < n && col < n && (col < c0 || col >= c0 + w)) W[(size_t)row * n + col] = acc[sr][sc][i];
-      }
-}
-
-__global__ void k_dense_to_float(size_t nn, const double* __restrict__ in, float* __restrict__ out) {
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < nn; e += (size_t)gridDim.x * blockDim.x)
-    out[e] = (float)in[e];
 }
 
 }  // namespace
@@ -772,87 +641,41 @@ void launch_dense_inverse_batched(const Level& lv, int nterm, const TermInfo* d_
 
 namespace amg {
 
-// Inverses of symmetric positive definite diagonal blocks (one per TermInfo)
-// in place in inv (row-major n x n at each TermInfo's offset), blocked
-// Gauss-Jordan without pivoting; inv32 (optional) receives the float copy.
-// Raises kErrNotSPD on a non-positive pivot; the caller then redoes the
-// inversion with pivoting.  Scratch from tmp.
-void launch_dense_inverse_spd(int nterm, const TermInfo* d_term, const TermInfo* h_term, int nrows, const int* rp,
-                              const int* ci, const double* val, double* inv, float* inv32, Arena& tmp, int* err,
-                              hipStream_t s) {
+// Inverses of diagonal blocks (one per TermInfo) in inv (row-major n x n at
+// each TermInfo's offset), blocked Gauss-Jordan without pivoting; inv32
+// (optional) receives the float copy.  Raises kErrNotSPD on a non-positive
+// pivot; the caller then redoes the inversion with pivoting.  Scratch from tmp.
+constexpr int kNoPivotMax = 8192;    // unknowns of a system at most
+constexpr long kPivotTiles = 2048;   // tiles of a launch up to which each inverts the pivot block itself
+void launch_dense_inverse_spd(int nterm, const TermInfo* d_term, const TermInfo* h_term, const int* rp, const int* ci,
+                              const double* val, double* inv, float* inv32, Arena& tmp, int* err, hipStream_t s) {
   if (nterm == 0) return;
   size_t total = 0;
   int nmax = 0;
-  std::vector<int> tiles;
   for (int t = 0; t < nterm; ++t) {
-    const int n = h_term[t].n;
-    total += (size_t)n * n;
-    nmax = std::max(nmax, n);
-    const int nt = (n + kUpdTile - 1) / kUpdTile;
-    for (int q = 0; q < nt * nt; ++q) {
-      tiles.push_back(t);
-      tiles.push_back(q);
-    }
+    total += (size_t)h_term[t].n * h_term[t].n;
+    nmax = std::max(nmax, h_term[t].n);
   }
-  // panel width b and rows per thread R with b * R = 32 register doubles; a
-  // workgroup of just enough waves for the largest system
-  int b = 32, R = 1;
-  while (R * kPanelThreads < nmax) {
-    b /= 2;
-    R *= 2;
-  }
-  const int pth = R > 1 ? kPanelThreads : std::max(kWave, (nmax + kWave - 1) / kWave * kWave);
-  if (b < 4) throw Error(AMG_ECOARSEN, "coarsest system too large for the register panel");
-  launch_fill_double(total, inv, 0.0, s);
-  k_dense_scatter_batched<<<nterm, 256, 0, s>>>(d_term, rp, ci, val, inv);
-  double* ybuf = tmp.alloc_n<double>((size_t)nrows * b);
-  double* tbuf = tmp.alloc_n<double>((size_t)nrows * b);
-  int* d_tiles = tmp.alloc_n<int>(tiles.size());
-  AMG_HIP(hipMemcpyAsync(d_tiles, tiles.data(), tiles.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  const int npanels = (nmax + b - 1) / b;
-  const int ntiles = (int)(tiles.size() / 2);
-  // panels of 32 columns: pivot block + product; narrower panels (systems of
-  // more than 1024 rows) keep the one-workgroup register panel
-  int* d_items = nullptr;
-  int* d_ptiles = nullptr;
-  double* xbuf = nullptr;
-  int nitems = 0, nptiles = 0;
-  if (b == 32) {
-    std::vector<int> items, ptiles;
-    for (int t = 0; t < nterm; ++t) {
-      for (int rb = 0; rb * 256 < h_term[t].n; ++rb) {
-        items.push_back(t);
-        items.push_back(rb);
-      }
-      for (int q = 0; q * kUpdTile < h_term[t].n; ++q) {   // mode-2 tiles: one per column tile
-        ptiles.push_back(t);
-        ptiles.push_back(q);
+  if (nmax > kNoPivotMax) throw Error(AMG_ECOARSEN, "coarsest system too large for the dense inverse");
+  double* work = tmp.alloc_n<double>(total);
+  const int np = (nmax + kB - 1) / kB;
+  // systems per launch within the grid's z (and y) limit
+  constexpr int kZ = 65535;
+  const bool own = (long)np * np * std::min(nterm, kZ) <= kPivotTiles;
+  double* mbuf = own ? nullptr : tmp.alloc_n<double>((size_t)nterm * kB * kB);
+  for (int t0 = 0; t0 < nterm; t0 += kZ) {
+    const int nt = std::min(kZ, nterm - t0);
+    k_gji_init<<<dim3(np, nt), 256, 0, s>>>(d_term + t0, rp, ci, val, inv, work);
+    for (int K = 0; K < np; ++K) {
+      const dim3 g(np, np, nt);
+      if (own) {
+        k_gji_panel<true><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, nullptr, K, err);
+      } else {
+        k_gji_pivot<<<nt, kWave, 0, s>>>(d_term + t0, inv, work, mbuf, K, err);
+        k_gji_panel<false><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, mbuf, K, err);
       }
     }
-    nitems = (int)(items.size() / 2);
-    nptiles = (int)(ptiles.size() / 2);
-    d_items = tmp.alloc_n<int>(items.size());
-    d_ptiles = tmp.alloc_n<int>(ptiles.size());
-    xbuf = tmp.alloc_n<double>((size_t)nterm * 32 * 32);
-    AMG_HIP(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, s));
-    AMG_HIP(hipMemcpyAsync(d_ptiles, ptiles.data(), ptiles.size() * sizeof(int), hipMemcpyHostToDevice, s));
   }
-  for (int K = 0; K < npanels; ++K) {
-    switch (b) {
-      case 32:
-        k_gjb_pivot<<<nterm, 1024, 0, s>>>(d_term, inv, ybuf, xbuf, K, err);
-        k_gjb_apply<<<nitems, 256, 0, s>>>(d_term, d_items, inv, ybuf, xbuf, K);
-        k_gjb_update<<<ntiles, 256, 0, s>>>(d_term, d_tiles, inv, ybuf, nullptr, K, b, 1);
-        k_gjb_update<<<nptiles, 256, 0, s>>>(d_term, d_ptiles, inv, ybuf, nullptr, K, b, 2);
-        continue;
-      case 16: k_gjb_panel_reg<16, 2><<<nterm, pth, 0, s>>>(d_term, inv, ybuf, tbuf, K, err); break;
-      case 8: k_gjb_panel_reg<8, 4><<<nterm, pth, 0, s>>>(d_term, inv, ybuf, tbuf, K, err); break;
-      default: k_gjb_panel_reg<4, 8><<<nterm, pth, 0, s>>>(d_term, inv, ybuf, tbuf, K, err); break;
-    }
-    k_gjb_update<<<ntiles, 256, 0, s>>>(d_term, d_tiles, inv, ybuf, tbuf, K, b, 0);
-  }
-  if (inv32) k_dense_to_float<<<(int)std::min<size_t>((total + 255) / 256, 4096), 256, 0, s>>>(total, inv, inv32);
-  AMG_HIP(hipStreamSynchronize(s));   // the host tile table is read before it goes away
 }
 
 }  // namespace amg

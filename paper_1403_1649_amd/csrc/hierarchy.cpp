@@ -646,7 +646,7 @@ static void coarse_inverse(Hierarchy& h, Arena& tmp, Sync& sy) {
     const TermInfo t{0, 0, cl.n, 0, 0};
     TermInfo* dt = tmp.alloc_n<TermInfo>(1);
     AMG_HIP(hipMemcpyAsync(dt, &t, sizeof(TermInfo), hipMemcpyHostToDevice, s));
-    launch_dense_inverse_spd(1, dt, &t, cl.n, cl.rp, cl.ci, cl.val, h.cinv, h.cinv32, tmp, h.d_err, s);
+    launch_dense_inverse_spd(1, dt, &t, cl.rp, cl.ci, cl.val, h.cinv, h.cinv32, tmp, h.d_err, s);
     inverted = !sy.take_not_spd();
   }
   if (!inverted) launch_dense_inverse(cl.n, cl.rp, cl.ci, cl.val, work, h.cinv, h.cinv32, gj_sync, h.d_err, s);
@@ -1321,7 +1321,7 @@ void build_batch_hierarchy(Hierarchy& h, const amg_csr& A, const int* sys_off) {
     AMG_HIP(hipMemcpyAsync(lv.d_term, ti.data(), nt * sizeof(TermInfo), hipMemcpyHostToDevice, s));
     AMG_HIP(hipMemcpyAsync(lv.tblk, tb.data(), tb.size() * sizeof(int), hipMemcpyHostToDevice, s));
     Arena work;
-    launch_dense_inverse_spd(nt, lv.d_term, ti.data(), lv.n, lv.rp, lv.ci, lv.val, lv.tinv, lv.tinv32, work,
+    launch_dense_inverse_spd(nt, lv.d_term, ti.data(), lv.rp, lv.ci, lv.val, lv.tinv, lv.tinv32, work,
                              h.d_err, s);
     if (sy.take_not_spd()) {   // some system is not SPD: eliminate all of them with pivoting
       double* wk = work.alloc_n<double>(2 * (size_t)off);
