@@ -35,7 +35,7 @@ enum : int { fRun = 0, fIters, fK0, fWords = fK0 + 2 * 24 };   // K-level k: fK0
 // words over all systems
 enum : int { aRun = 0, aK0 = 1, aWords = 1 + 24 };
 
-constexpr int kBNV = 3;   // largest number of fused reductions
+constexpr int kBNV = 6;   // largest number of fused reductions
 
 // ---------------------------------------------------------------- skeletons
 struct Mask {
@@ -62,7 +62,7 @@ __device__ __forceinline__ void write_part(double (&acc)[NV], double* part, int 
 }
 
 // Op: NV, Mask m, T x(int j), row(int i, int s, T ax, double* acc),
-//     finalize(int s, const double* v), skip(int s), finalize_all()
+//     finalize(int s, const double* v), skip(int s)
 template <typename T, int LPR, class Op>
 __global__ void __launch_bounds__(kBlock) k_brows(const int* __restrict__ blk, int nb, const int* __restrict__ rp,
                                                   const int* __restrict__ ci, const T* __restrict__ av, Op op,
@@ -106,39 +106,75 @@ __global__ void __launch_bounds__(kBlock) k_belem(const int* __restrict__ blk, i
   if constexpr (Op::NV > 0) write_part<Op::NV>(acc, part, nb, lb);
 }
 
-// per-system totals: one wave per system (lanes stride over its blocks, then
-// a fixed shuffle tree), so the sum order is fixed; masked-off systems get
-// skip()
-constexpr int kFinThreads = 1024;
+// per-system totals: a block per system (threads stride over its blocks, then
+// a fixed tree), so the sum order is fixed; masked-off systems get skip().
+// Operations that also keep a word over all systems (OpAny: flag(s), set_any)
+// take it in the last block to arrive (a ticket, after a release fence of the
+// few words each block wrote).  On 64 systems 4.6 to 8.2 us; one workgroup that
+// walked all systems took 8 to 18.
+constexpr int kFinThreads = 256;
+constexpr int kFinBlocks = 2048;
+
+template <class Op, class = void>
+struct OpAny : std::false_type {};
+template <class Op>
+struct OpAny<Op, std::void_t<decltype(&Op::set_any)>> : std::true_type {};
 
 template <class Op>
 __global__ void __launch_bounds__(kFinThreads) k_bfinal(Op op, const double* __restrict__ part, int nb,
-                                                        const int* __restrict__ blk_sys, int nsys) {
+                                                        const int* __restrict__ blk_sys, int nsys, unsigned* ticket) {
   if (!op.m.active()) return;
   constexpr int NV = Op::NV;
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  for (int s = wv; s < nsys; s += kFinThreads / kWave) {
+  __shared__ double red[NV * (kFinThreads / kWave)];
+  for (int s = blockIdx.x; s < nsys; s += gridDim.x) {
     if (!op.m.on(s)) {
-      if (lane == 0) op.skip(s);
+      if (threadIdx.x == 0) op.skip(s);
       continue;
     }
     double v[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       double t = 0.0;
-      for (int b = blk_sys[s] + lane; b < blk_sys[s + 1]; b += kWave) t += part[(size_t)k * nb + b];
-      v[k] = wave_sum(t);
+      for (int b = blk_sys[s] + threadIdx.x; b < blk_sys[s + 1]; b += kFinThreads) t += part[(size_t)k * nb + b];
+      v[k] = t;
     }
-    if (lane == 0) op.finalize(s, v);
+    block_sum<NV>(v, red);
+    if (threadIdx.x == 0) op.finalize(s, v);
   }
-  __syncthreads();
-  if (threadIdx.x == 0) op.finalize_all();
+  if constexpr (OpAny<Op>::value) {
+    __shared__ int s_last, s_any;
+    if (threadIdx.x == 0) {
+      __threadfence();
+      s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+      s_any = 0;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    int any = 0;
+    for (int s = threadIdx.x; s < nsys; s += kFinThreads)
+      any |= __hip_atomic_load(op.flag(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (any) s_any = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      op.set_any(s_any);
+      *ticket = 0u;
+    }
+  }
 }
 
 struct BCtx {
   int nsys;
   double* part;
+  unsigned* ticket;
 };
+
+template <class Op>
+void bfinal(const Level& tab, const BCtx& c, const Op& op, hipStream_t s) {
+  if constexpr (Op::NV > 0)
+    k_bfinal<Op><<<std::min(c.nsys, kFinBlocks), kFinThreads, 0, s>>>(op, c.part, tab.nblk, tab.blk_sys, c.nsys,
+                                                                      c.ticket);
+}
 
 // rows of a CSR matrix (rp, ci, av) whose rows are those of the level `tab`
 // (A_k itself, or R_k = P_k^T over the rows of level k+1)
@@ -155,7 +191,7 @@ void brows_on(const Level& tab, int lpr, const int* rp, const int* ci, const T* 
     case 32: k_brows<T, 32, Op><<<g, kBlock, 0, s>>>(tab.blk, g, rp, ci, av, op, c.part); break;
     default: k_brows<T, 64, Op><<<g, kBlock, 0, s>>>(tab.blk, g, rp, ci, av, op, c.part); break;
   }
-  if constexpr (Op::NV > 0) k_bfinal<Op><<<1, kFinThreads, 0, s>>>(op, c.part, g, tab.blk_sys, c.nsys);
+  bfinal(tab, c, op, s);
 }
 
 template <typename T, class Op>
@@ -213,6 +249,81 @@ __global__ void __launch_bounds__(kBlock) k_bsell(const int* __restrict__ blk, i
   if constexpr (Op::NV > 0) write_part<Op::NV>(acc, part, nb, lb);
 }
 
+// Products with T_k (short CSR rows), streamed through LDS as k_stream: a wave
+// takes 64 rows of its block's range at a time, its loads run ahead by one
+// group of rows, and a group of more than 64 Q entries is summed row by row by
+// the whole wave.  Bound by bytes (T's entries, y, out, q); 64 2-D systems of
+// 5.7 M rows in FP32: 54 us with z'q, in place of the second product with A_k
+// (71 us), the prolongation and a pass for z'q.
+template <typename T, int Q, class Op>
+__global__ void __launch_bounds__(kBlock) k_bstream(const int* __restrict__ blk, int nb, const int* __restrict__ rp,
+                                                    const int* __restrict__ ci, const T* __restrict__ av, Op op,
+                                                    double* part) {
+  if (!op.m.active()) return;
+  constexpr int NV = Op::NV > 0 ? Op::NV : 1;
+  __shared__ T s_prod[kBlock / kWave][kWave * Q];
+  const int lb = logical_block();
+  const int sys = blk[3 * lb], r0 = blk[3 * lb + 1], r1 = blk[3 * lb + 2];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  T* prod = s_prod[wv];
+  double acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+  if (sys >= 0 && op.m.on(sys)) {
+    struct Rows { int beg, end; };
+    struct Ents { int c[Q]; T v[Q]; };
+    auto rows_of = [&](int r) {   // past the range: an empty run at its end
+      const int i = min(r + lane, r1);
+      return Rows{rp[i], rp[min(i + 1, r1)]};
+    };
+    auto ents_of = [&](const Rows& w) {
+      Ents t;
+      const int base = __builtin_amdgcn_readfirstlane(w.beg);
+      const int last = max(__builtin_amdgcn_readlane(w.end, kWave - 1) - 1, 0);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int k = min(base + q * kWave + lane, last);
+        t.c[q] = ci[k];
+        t.v[q] = av[k];
+      }
+      return t;
+    };
+    int r = r0 + wv * kWave;
+    Rows w0 = rows_of(r);
+    Ents e0 = ents_of(w0);
+    for (; r < r1; r += kBlock) {
+      T xv[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) xv[q] = op.x(e0.c[q]);
+      const Rows w1 = rows_of(r + kBlock);
+      const Ents e1 = ents_of(w1);
+      const int base = __builtin_amdgcn_readfirstlane(w0.beg);
+      const int total = __builtin_amdgcn_readlane(w0.end, kWave - 1) - base;
+      T sum = T(0);
+      if (total <= kWave * Q) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) prod[q * kWave + lane] = e0.v[q] * xv[q];
+        wave_lds_order();
+        for (int k = w0.beg - base; k < w0.end - base; ++k) sum += prod[k];
+        wave_lds_order();
+      } else {
+        for (int i = 0; i < kWave; ++i) {
+          const int b = __builtin_amdgcn_readlane(w0.beg, i), e = __builtin_amdgcn_readlane(w0.end, i);
+          T t = T(0);
+          for (int k = b + lane; k < e; k += kWave) t += av[k] * op.x(ci[k]);
+          t = wave_sum(t);
+          if (lane == i) sum = t;
+        }
+      }
+      const int row = r + lane;
+      if (row < r1) op.row(row, sys, sum, acc);
+      w0 = w1;
+      e0 = e1;
+    }
+  }
+  if constexpr (Op::NV > 0) write_part<Op::NV>(acc, part, nb, lb);
+}
+
 template <typename T> const T* bsv(const Level& l);
 template <> const double* bsv<double>(const Level& l) { return l.sl_val; }
 template <> const float* bsv<float>(const Level& l) { return l.sl_val32; }
@@ -231,7 +342,26 @@ void blevel(const Level& lv, const BCtx& c, const Op& op, hipStream_t s) {
   const int g = lv.nblk;
   k_bsell<T, Op><<<g, kBlock, 0, s>>>(lv.blk, g, lv.d_sys_off, lv.sl_base, lv.sl_ptr, lv.sl_col, bsv<T>(lv), op,
                                       c.part);
-  if constexpr (Op::NV > 0) k_bfinal<Op><<<1, kFinThreads, 0, s>>>(op, c.part, g, lv.blk_sys, c.nsys);
+  bfinal(lv, c, op, s);
+}
+
+template <typename T> const T* btv(const Level& l);
+template <> const double* btv<double>(const Level& l) { return l.tv; }
+template <> const float* btv<float>(const Level& l) { return l.tv32; }
+
+// T_k = (I - W A) P applied by a row operation
+template <typename T, class Op>
+void bpost(const Level& lv, const BCtx& c, const Op& op, hipStream_t s) {
+  if (lv.nblk == 0) return;
+  if (lv.tlpr > 0) {
+    brows_on<T>(lv, lv.tlpr, lv.tp, lv.tc, btv<T>(lv), c, op, s);
+    return;
+  }
+  if (lv.tlpr == -4)
+    k_bstream<T, 4, Op><<<lv.nblk, kBlock, 0, s>>>(lv.blk, lv.nblk, lv.tp, lv.tc, btv<T>(lv), op, c.part);
+  else
+    k_bstream<T, 8, Op><<<lv.nblk, kBlock, 0, s>>>(lv.blk, lv.nblk, lv.tp, lv.tc, btv<T>(lv), op, c.part);
+  bfinal(lv, c, op, s);
 }
 
 template <class Op>
@@ -239,13 +369,12 @@ void belem(const Level& lv, const BCtx& c, const Op& op, hipStream_t s) {
   if (lv.nblk == 0) return;
   const int g = lv.nblk;
   k_belem<Op><<<g, kBlock, 0, s>>>(lv.blk, g, op, c.part);
-  if constexpr (Op::NV > 0) k_bfinal<Op><<<1, kFinThreads, 0, s>>>(op, c.part, g, lv.blk_sys, c.nsys);
+  bfinal(lv, c, op, s);
 }
 
 #define B_NOFIN                                                   \
   __device__ void finalize(int, const double*) const {}          \
-  __device__ void skip(int) const {}                             \
-  __device__ void finalize_all() const {}
+  __device__ void skip(int) const {}
 
 // ---------------------------------------------------------------- setup ops
 struct BLocalBase {
@@ -320,7 +449,6 @@ struct BArnStart {
   }
   __device__ void finalize(int s, const double* v) const { sc[bArnNorm * nsys + s] = sqrt(v[0]); }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 struct BDivide {
@@ -333,47 +461,51 @@ struct BDivide {
   B_NOFIN
 };
 
+// step j: w = D^-1 A q_j with ||w||^2 and the projections q_k'w, k <= j, in the
+// same pass (classical Gram-Schmidt, as the single-system Arnoldi)
 struct BArnSpmv {
-  static constexpr int NV = 2;
+  static constexpr int NV = 1 + kArnMax;
   Mask m;
   const double* q;
-  const double* q0;
+  const double* Q;
   const double* diag;
   double* w;
   double* sc;
-  int nsys, j;
+  int nsys, j, n;
   __device__ double x(int c) const { return q[c]; }
   __device__ void row(int i, int, double ax, double* acc) const {
     const double t = (1.0 / diag[i]) * ax;
     w[i] = t;
     acc[0] += t * t;
-    acc[1] += q0[i] * t;
+#pragma unroll
+    for (int k = 0; k < kArnMax; ++k)
+      if (k <= j) acc[1 + k] += Q[(size_t)k * n + i] * t;
   }
   __device__ void finalize(int s, const double* v) const {
     sc[(bArn + 48 + j) * nsys + s] = sqrt(v[0]);
-    sc[(bArn + j) * nsys + s] = v[1];
+    for (int k = 0; k <= j; ++k) sc[(bArn + 8 * k + j) * nsys + s] = v[1 + k];
   }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
-// modified Gram-Schmidt: w -= H[i][j] q_i, then q_{i+1}'w (or ||w|| last)
-struct BArnAxpyDot {
+// w -= sum_k h_kj q_k and h_{j+1,j} = ||w||
+struct BArnUpdate {
   static constexpr int NV = 1;
   Mask m;
-  const double* qi;
-  const double* qn;
+  const double* Q;
   double* w;
-  const double* h;     // per system
-  double* out;         // per system
+  double* sc;
+  int nsys, j, n;
   __device__ void elem(int i, int s, double* acc) const {
-    const double t = w[i] - h[s] * qi[i];
+    double t = w[i];
+#pragma unroll
+    for (int k = 0; k < kArnMax; ++k)
+      if (k <= j) t -= sc[(bArn + 8 * k + j) * nsys + s] * Q[(size_t)k * n + i];
     w[i] = t;
-    acc[0] += (qn ? qn[i] : t) * t;
+    acc[0] += t * t;
   }
-  __device__ void finalize(int s, const double* v) const { out[s] = qn ? v[0] : sqrt(v[0]); }
+  __device__ void finalize(int s, const double* v) const { sc[(bArn + 8 * (j + 1) + j) * nsys + s] = sqrt(v[0]); }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 // ---------------------------------------------------------------- cycle ops
@@ -385,11 +517,53 @@ struct BPresmoothResid {
   const T* wd;
   T* xt;
   T* r;
+  bool two;   // the iterate after both smoothing steps (levels that post-smooth by T)
   __device__ T x(int j) const { return wd[j] * b[j]; }
   __device__ void row(int i, int, T ax, double*) const {
-    const T bi = b[i];
-    xt[i] = wd[i] * bi;
-    r[i] = bi - ax;
+    const T bi = b[i], wi = wd[i], ri = bi - ax;
+    xt[i] = two ? wi * bi + wi * ri : wi * bi;
+    r[i] = ri;
+  }
+  B_NOFIN
+};
+
+// correction and post-smoothing by T: x_out = y + T e (DOT: with z'q per system)
+template <typename T, bool DOT>
+struct BPostT {
+  static constexpr int NV = DOT ? 1 : 0;
+  Mask m;
+  const T* y;
+  T* xo;
+  const T* e;
+  const double* q;
+  double* sc;
+  int nsys;
+  __device__ T x(int J) const { return e[J]; }
+  __device__ void row(int i, int, T te, double* acc) const {
+    const T z = y[i] + te;
+    xo[i] = z;
+    if (DOT) acc[0] += (double)z * q[i];
+  }
+  __device__ void finalize(int s, const double* v) const {
+    if (DOT) sc[bBeta * nsys + s] = -v[0] / sc[bPQ * nsys + s];
+  }
+  __device__ void skip(int) const {}
+};
+
+// the K-cycle's combination per system, in place: c <- coef_c c (+ coef_d d)
+template <typename T>
+struct BCombine {
+  static constexpr int NV = 0;
+  Mask m;
+  T* cc;
+  const T* d;
+  const double* K;
+  const int* F;
+  int nsys;
+  __device__ void elem(int i, int s, double*) const {
+    T t = (T)K[kKCoefC * nsys + s] * cc[i];
+    if (F[nsys + s]) t += (T)K[kKCoefD * nsys + s] * d[i];
+    cc[i] = t;
   }
   B_NOFIN
 };
@@ -407,24 +581,15 @@ struct BResidSmooth {
   B_NOFIN
 };
 
-template <typename T, bool DOT>
+template <typename T>
 struct BRestrict {   // rows of R = P^T (aggregates, the rows of the next level)
-  static constexpr int NV = DOT ? 1 : 0;
+  static constexpr int NV = 0;
   Mask m;
   const T* r;
   T* rcv;
-  double* K;   // K slots of this level: slot q of system s at K[q * nsys + s]
-  int nsys;
   __device__ T x(int j) const { return r[j]; }
-  __device__ void row(int I, int, T s, double* acc) const {
-    rcv[I] = s;
-    if (DOT) acc[0] += (double)s * (double)s;
-  }
-  __device__ void finalize(int s, const double* v) const {
-    if (DOT) K[kKRcRc * nsys + s] = v[0];
-  }
-  __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
+  __device__ void row(int I, int, T s, double*) const { rcv[I] = s; }
+  B_NOFIN
 };
 
 template <typename T>
@@ -442,77 +607,80 @@ struct BProlong {
   B_NOFIN
 };
 
+// first inner step: v = A c, rho1, alpha1 and the per-system branch of
+// Algorithm 5 in the same reduction (||r~||^2 = r_c'r_c - 2 a v'r_c + a^2 v'v
+// with a = alpha1 / rho1, as the single-system cycle); a system whose next
+// level is its coarsest takes the V-cycle step (coefficient 1, no second
+// step), as it would alone
 template <typename T>
 struct BKDots1 {
-  static constexpr int NV = 2;
+  static constexpr int NV = 5;
   Mask m;
   const T* cc;
   const T* rcv;
   T* v;
-  double* K;
-  int nsys;
-  __device__ T x(int j) const { return cc[j]; }
-  __device__ void row(int i, int, T ax, double* acc) const {
-    v[i] = ax;
-    acc[0] += (double)cc[i] * (double)ax;
-    acc[1] += (double)cc[i] * (double)rcv[i];
-  }
-  __device__ void finalize(int s, const double* v2) const {
-    K[kKRho1 * nsys + s] = v2[0];
-    K[kKAlpha1 * nsys + s] = v2[1];
-  }
-  __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
-};
-
-// r~ = r_c - (alpha1/rho1) v and the per-system branch of Algorithm 5; a
-// system whose next level is its coarsest takes the V-cycle step (coefficient
-// 1, no second step), as it would alone
-template <typename T>
-struct BRtilde {
-  static constexpr int NV = 1;
-  Mask m;
-  const T* rcv;
-  const T* v;
-  T* rt;
   double* K;
   int* F;        // F[s]: second step; F[nsys + s]: use d
   int* any2;
   const int* kv;
   double t;
   int nsys;
-  __device__ void elem(int i, int s, double* acc) const {
-    const T ar = (T)(K[kKAlpha1 * nsys + s] / K[kKRho1 * nsys + s]);
-    const T u = rcv[i] - ar * v[i];
-    rt[i] = u;
-    acc[0] += (double)u * (double)u;
+  __device__ T x(int j) const { return cc[j]; }
+  __device__ void row(int i, int, T ax, double* acc) const {
+    v[i] = ax;
+    const double av = (double)ax, rr = (double)rcv[i], ci = (double)cc[i];
+    acc[0] += ci * av;
+    acc[1] += ci * rr;
+    acc[2] += rr * rr;
+    acc[3] += av * av;
+    acc[4] += av * rr;
   }
-  __device__ void finalize(int s, const double* v2) const {
+  __device__ void finalize(int s, const double* s2) const {
     F[nsys + s] = 0;
+    F[s] = 0;
+    const double rho1 = s2[0], alpha1 = s2[1];
+    K[kKRho1 * nsys + s] = rho1;
+    K[kKAlpha1 * nsys + s] = alpha1;
+    K[kKRcRc * nsys + s] = s2[2];
     if (!kv[s]) {
       K[kKCoefC * nsys + s] = 1.0;
-      F[s] = 0;
       return;
     }
-    const double rho1 = K[kKRho1 * nsys + s];
-    K[kKRtRt * nsys + s] = v2[0];
     if (rho1 > 0.0) {
-      K[kKCoefC * nsys + s] = K[kKAlpha1 * nsys + s] / rho1;
-      F[s] = (sqrt(v2[0]) <= t * sqrt(K[kKRcRc * nsys + s])) ? 0 : 1;
+      const double ar = alpha1 / rho1;
+      double rt2 = s2[2] - 2.0 * ar * s2[4] + ar * ar * s2[3];
+      rt2 = rt2 > 0.0 ? rt2 : 0.0;
+      K[kKRtRt * nsys + s] = rt2;
+      K[kKCoefC * nsys + s] = ar;
+      F[s] = (sqrt(rt2) <= t * sqrt(s2[2])) ? 0 : 1;
     } else {
+      K[kKRtRt * nsys + s] = s2[2];
       K[kKCoefC * nsys + s] = 0.0;
-      F[s] = 0;
     }
   }
   __device__ void skip(int s) const {
     F[s] = 0;
     F[nsys + s] = 0;
   }
-  __device__ void finalize_all() const {
-    int a = 0;
-    for (int s = 0; s < nsys; ++s) a |= F[s];
-    *any2 = a;
+  __device__ const int* flag(int s) const { return F + s; }
+  __device__ void set_any(int a) const { *any2 = a; }
+};
+
+// r~ = r_c - (alpha1/rho1) v of the systems that take the second step
+template <typename T>
+struct BRtilde {
+  static constexpr int NV = 0;
+  Mask m;
+  const T* rcv;
+  const T* v;
+  T* rt;
+  const double* K;
+  int nsys;
+  __device__ void elem(int i, int s, double*) const {
+    const T ar = (T)(K[kKAlpha1 * nsys + s] / K[kKRho1 * nsys + s]);
+    rt[i] = rcv[i] - ar * v[i];
   }
+  B_NOFIN
 };
 
 template <typename T>
@@ -544,7 +712,6 @@ struct BKDots2 {
     }
   }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 template <typename T>
@@ -620,11 +787,8 @@ struct BFcgInit {
     }
   }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {
-    int a = 0;
-    for (int s = 0; s < nsys; ++s) a |= fl[fRun * nsys + s];
-    any[aRun] = a;
-  }
+  __device__ const int* flag(int s) const { return fl + fRun * nsys + s; }
+  __device__ void set_any(int a) const { any[aRun] = a; }
 };
 
 struct BFcgSpmv {
@@ -653,7 +817,6 @@ struct BFcgSpmv {
     }
   }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 struct BFcgUpdate {
@@ -687,11 +850,8 @@ struct BFcgUpdate {
     }
   }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {
-    int a = 0;
-    for (int s = 0; s < nsys; ++s) a |= fl[fRun * nsys + s];
-    any[aRun] = a;
-  }
+  __device__ const int* flag(int s) const { return fl + fRun * nsys + s; }
+  __device__ void set_any(int a) const { any[aRun] = a; }
 };
 
 struct BToFloat {
@@ -714,7 +874,6 @@ struct BDotZQ {
   __device__ void elem(int i, int, double* acc) const { acc[0] += (double)z[i] * q[i]; }
   __device__ void finalize(int s, const double* v) const { sc[bBeta * nsys + s] = -v[0] / sc[bPQ * nsys + s]; }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 template <typename T>
@@ -747,7 +906,6 @@ struct BTrueResid {
   }
   __device__ void finalize(int s, const double* v) const { sc[bTrue * nsys + s] = v[0]; }
   __device__ void skip(int) const {}
-  __device__ void finalize_all() const {}
 };
 
 struct BCopy {
@@ -783,7 +941,7 @@ template <typename T> const T* btinv(const Level& l);
 template <> const double* btinv<double>(const Level& l) { return l.tinv; }
 template <> const float* btinv<float>(const Level& l) { return l.tinv32; }
 
-BCtx bctx(const Hierarchy& h) { return BCtx{h.nsys, h.b_part}; }
+BCtx bctx(const Hierarchy& h) { return BCtx{h.nsys, h.b_part, h.d_ticket + 32}; }
 
 // ------------------------------------------------------------------ cycle
 template <typename T>
@@ -792,15 +950,17 @@ void term_solve(Hierarchy& h, const Level& lv, const T* b, T* x, Mask m) {
   k_term_gemv<T><<<lv.ntblk, kBlock, 0, h.stream>>>(lv.tblk, lv.d_term, btinv<T>(lv), b, x, m);
 }
 
+// xo = M_k b.  fuse_q: z'q per system (the FCG beta) in the post-smoothing, where
+// no system ends on level k; returns whether it was computed.
 template <typename T>
-void cycle_b(Hierarchy& h, int k, const T* b, T* xo, Mask m) {
+bool cycle_b(Hierarchy& h, int k, const T* b, T* xo, Mask m, const double* fuse_q = nullptr) {
   hipStream_t s = h.stream;
   const BCtx c = bctx(h);
   const int L = h.L();
   Level& lv = h.levels[k];
   if (k == L) {   // every system present here ends here
     term_solve<T>(h, lv, b, xo, m);
-    return;
+    return false;
   }
   const int nsys = h.nsys;
   T* xt = static_cast<T*>(lv.xt);
@@ -810,12 +970,12 @@ void cycle_b(Hierarchy& h, int k, const T* b, T* xo, Mask m) {
   const T* wd = bwd<T>(lv);
   const T* pv = bpv<T>(lv);
   Level& lc = h.levels[k + 1];
-  blevel<T>(lv, c, BPresmoothResid<T>{m, b, wd, xt, r}, s);
-  const T* rv = brv<T>(lv);
+  const bool byT = lv.tp != nullptr;   // post-smoothing by T = (I - W A) P
+  blevel<T>(lv, c, BPresmoothResid<T>{m, b, wd, xt, r, byT}, s);
+  brows_on<T>(lc, lv.rlpr, lv.agg_ptr, lv.agg_rows, brv<T>(lv), c, BRestrict<T>{m, r, rcv}, s);
+  cycle_b<T>(h, k + 1, rcv, cc, m);
   if (!lv.kcyc) {
-    brows_on<T>(lc, lv.rlpr, lv.agg_ptr, lv.agg_rows, rv, c, BRestrict<T, false>{m, r, rcv, nullptr, nsys}, s);
-    cycle_b<T>(h, k + 1, rcv, cc, m);
-    belem(lv, c, BProlong<T>{m, lv.agg, pv, cc, xt}, s);
+    if (!byT) belem(lv, c, BProlong<T>{m, lv.agg, pv, cc, xt}, s);
   } else {
     double* K = h.b_sc + (size_t)(bK0 + 16 * k) * nsys;
     int* F = h.b_fl + (size_t)(fK0 + 2 * k) * nsys;
@@ -824,28 +984,31 @@ void cycle_b(Hierarchy& h, int k, const T* b, T* xo, Mask m) {
     T* rt = static_cast<T*>(lv.rt);
     T* d = static_cast<T*>(lv.d);
     T* w = static_cast<T*>(lv.w);
-    brows_on<T>(lc, lv.rlpr, lv.agg_ptr, lv.agg_rows, rv, c, BRestrict<T, true>{m, r, rcv, K, nsys}, s);
-    cycle_b<T>(h, k + 1, rcv, cc, m);
-    blevel<T>(lc, c, BKDots1<T>{m, cc, rcv, v, K, nsys}, s);
-    belem(lc, c, BRtilde<T>{m, rcv, v, rt, K, F, any2, lv.kv, h.opt.kcycle_t, nsys}, s);
+    blevel<T>(lc, c, BKDots1<T>{m, cc, rcv, v, K, F, any2, lv.kv, h.opt.kcycle_t, nsys}, s);
     const Mask m2{any2, F};
+    belem(lc, c, BRtilde<T>{m2, rcv, v, rt, K, nsys}, s);
     cycle_b<T>(h, k + 1, rt, d, m2);
     blevel<T>(lc, c, BKDots2<T>{m2, d, v, rt, w, K, F, nsys}, s);
-    belem(lv, c, BProlongK<T>{m, lv.agg, pv, cc, d, xt, K, F, nsys}, s);
+    if (byT) belem(lc, c, BCombine<T>{m, cc, d, K, F, nsys}, s);
+    else belem(lv, c, BProlongK<T>{m, lv.agg, pv, cc, d, xt, K, F, nsys}, s);
   }
-  blevel<T>(lv, c, BResidSmooth<T>{m, b, xt, wd, xo}, s);
+  const bool dot = byT && fuse_q && lv.ntblk == 0;
+  if (dot) bpost<T>(lv, c, BPostT<T, true>{m, xt, xo, cc, fuse_q, h.b_sc, nsys}, s);
+  else if (byT) bpost<T>(lv, c, BPostT<T, false>{m, xt, xo, cc, nullptr, nullptr, nsys}, s);
+  else blevel<T>(lv, c, BResidSmooth<T>{m, b, xt, wd, xo}, s);
   term_solve<T>(h, lv, b, xo, m);   // systems whose coarsest level is this one
+  return dot;
 }
 
 template <typename T>
-void precondition_b(Hierarchy& h, Mask m, bool r32_ready) {
+bool precondition_b(Hierarchy& h, Mask m, bool r32_ready, const double* fuse_q = nullptr) {
   const Level& l0 = h.levels[0];
   if constexpr (sizeof(T) == sizeof(float)) {
     if (!r32_ready) belem(l0, bctx(h), BToFloat{m, h.r, static_cast<float*>(h.bz)}, h.stream);
-    cycle_b<float>(h, 0, static_cast<const float*>(h.bz), static_cast<float*>(h.z), m);
+    return cycle_b<float>(h, 0, static_cast<const float*>(h.bz), static_cast<float*>(h.z), m, fuse_q);
   } else {
     (void)r32_ready;
-    cycle_b<double>(h, 0, h.r, static_cast<double*>(h.z), m);
+    return cycle_b<double>(h, 0, h.r, static_cast<double*>(h.z), m, fuse_q);
   }
 }
 
@@ -859,8 +1022,8 @@ void iteration_b(Hierarchy& h) {
   float* r32 = sizeof(T) == sizeof(float) ? static_cast<float*>(h.bz) : nullptr;
   blevel<double>(l0, c, BFcgSpmv{m, h.p, h.r, h.q, h.b_sc, h.b_fl, h.d_err, nsys}, s);
   belem(l0, c, BFcgUpdate{m, h.p, h.q, h.xint, h.r, r32, h.b_sc, h.b_fl, h.b_any, h.d_err, nsys}, s);
-  precondition_b<T>(h, m, r32 != nullptr);
-  belem(l0, c, BDotZQ<T>{m, static_cast<const T*>(h.z), h.q, h.b_sc, nsys}, s);
+  if (!precondition_b<T>(h, m, r32 != nullptr, h.q))
+    belem(l0, c, BDotZQ<T>{m, static_cast<const T*>(h.z), h.q, h.b_sc, nsys}, s);
   belem(l0, c, BPUpdate<T>{m, static_cast<const T*>(h.z), h.p, h.b_sc, nsys, 0}, s);
 }
 
@@ -919,7 +1082,7 @@ void batch_blocks(Hierarchy& h, Level& lv) {
 }
 
 void batch_local_base(const Level& lv, int* lbase, hipStream_t s) {
-  BCtx c{0, nullptr};
+  BCtx c{0, nullptr, nullptr};
   belem(lv, c, BLocalBase{Mask{nullptr, nullptr}, lv.d_sys_off, lbase}, s);
 }
 
@@ -1010,7 +1173,7 @@ void batch_build_sell(Hierarchy& h, Arena& tmp, Level& lv) {
 }
 
 void batch_check_blocks(const Level& lv, int* err, hipStream_t s) {
-  BCtx c{0, nullptr};
+  BCtx c{0, nullptr, nullptr};
   belem(lv, c, BCheckBlocks{Mask{nullptr, nullptr}, lv.d_sys_off, lv.rp, lv.ci, err}, s);
 }
 
@@ -1019,17 +1182,17 @@ void batch_gather(int m, const int* src, const int* idx, int* dst, hipStream_t s
 }
 
 void batch_remap_agg(const Level& lv, const int* cont, const int* shift, int* agg, hipStream_t s) {
-  BCtx c{0, nullptr};
+  BCtx c{0, nullptr, nullptr};
   belem(lv, c, BRemapAgg{Mask{nullptr, nullptr}, cont, shift, agg}, s);
 }
 
 void batch_jacobi_weights(const Level& lv, const double* omega_sys, double* wdinv, float* wdinv32,
                           hipStream_t s) {
-  BCtx c{0, nullptr};
+  BCtx c{0, nullptr, nullptr};
   belem(lv, c, BJacobi{Mask{nullptr, nullptr}, omega_sys, lv.diag, wdinv, wdinv32}, s);
 }
 
-// Per-system Arnoldi (m steps, modified Gram-Schmidt) on the systems enabled
+// Per-system Arnoldi (m steps) on the systems enabled
 // by mask; H_out receives, per system, H[i][j] at [s*64 + 8i + j] and the
 // norms ||D^-1 A q_j|| at [s*64 + 48 + j].
 void batch_arnoldi(Hierarchy& h, Level& lv, int m, uint32_t stream, const int* mask, double* Q, double* w,
@@ -1043,15 +1206,8 @@ void batch_arnoldi(Hierarchy& h, Level& lv, int m, uint32_t stream, const int* m
   belem(lv, c, BDivide{mk, Q, Q, sc + (size_t)bArnNorm * nsys}, s);
   for (int j = 0; j < m; ++j) {
     const double* qj = Q + (size_t)j * n;
-    blevel<double>(lv, c, BArnSpmv{mk, qj, Q, lv.diag, w, sc, nsys, j}, s);
-    for (int i = 0; i <= j; ++i) {
-      const double* qi = Q + (size_t)i * n;
-      const double* qn = i < j ? Q + (size_t)(i + 1) * n : nullptr;
-      belem(lv, c,
-            BArnAxpyDot{mk, qi, qn, w, sc + (size_t)(bArn + i * 8 + j) * nsys,
-                        sc + (size_t)(bArn + (i + 1) * 8 + j) * nsys},
-            s);
-    }
+    blevel<double>(lv, c, BArnSpmv{mk, qj, Q, lv.diag, w, sc, nsys, j, n}, s);
+    belem(lv, c, BArnUpdate{mk, Q, w, sc, nsys, j, n}, s);
     belem(lv, c, BDivide{mk, w, Q + (size_t)(j + 1) * n, sc + (size_t)(bArn + (j + 1) * 8 + j) * nsys}, s);
   }
   std::vector<double> hs((size_t)64 * nsys);

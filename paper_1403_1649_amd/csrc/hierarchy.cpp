@@ -271,7 +271,7 @@ void tsmooth_patterns(Hierarchy& h, Arena& tmp, Sync& sy) {
       }
       const size_t m = (size_t)std::max(lv.tnnz, 1);
       lv.tlpr = post_lanes(lv.n, lv.tnnz, fl);
-      if (lv.tlpr < 0 && !(fl & kTFar)) {
+      if (lv.tlpr < 0 && !(fl & kTFar) && h.nsys == 0) {   // (a batch's blocks of rows start anywhere)
         lv.tc16 = h.arena.alloc_n<int16_t>(m);
         lv.tbase = h.arena.alloc_n<int>(((size_t)lv.n + 63) / 64);
       } else {
@@ -1345,7 +1345,9 @@ void build_batch_hierarchy(Hierarchy& h, const amg_csr& A, const int* sys_off) {
     sy.wait_and_check();
   }
   if (h.mixed()) make_float_copies(h);
+  tsmooth_patterns(h, tmp, sy);
   alloc_solve_vectors(h);
+  tsmooth_values(h);
   sy.wait_and_check();
   if (!(o.flags & AMG_FLAG_NO_GRAPH)) build_batch_graphs(h);
 }
