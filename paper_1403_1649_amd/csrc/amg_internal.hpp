@@ -170,6 +170,22 @@ struct Level {
   float* tv32 = nullptr;
   int tnnz = 0;
   int tlpr = 4;                // lanes per row of the product with T_k; < 0: streamed, -tlpr per lane
+  // levels of at most kTsmoothRows rows: the pre-smoothing and restriction in
+  // one operator, r_c = S_k b with S_k = P_k^T (I - A_k W_k) in CSR over the
+  // aggregates; y = W b + W (b - A W b) is then formed by the post-smoothing
+  int* sp = nullptr;
+  int* sc = nullptr;
+  double* sv = nullptr;
+  float* sv32 = nullptr;
+  int slpr = 8;
+  // the level above the coarsest: its whole cycle as a dense matrix M_k (rows
+  // padded to mld), or the coarse correction e = (C S_k) b (rows padded to gld)
+  double* mop = nullptr;
+  float* mop32 = nullptr;
+  int mld = 0;
+  double* gop = nullptr;
+  float* gop32 = nullptr;
+  int gld = 0;
   double omega = 0.0, rho = 0.0;
   double* wdinv = nullptr;     // omega / a_ii (or omega_i / a_ii with learned weights)
   int learned = 0;             // learned weights in use on this level
@@ -440,13 +456,14 @@ void launch_dense_inverse(int n, const int* rp, const int* ci, const double* val
 
 // smooth_interp.hip: the post-smoothing operator T = (I - W A) P
 // cnt: row lengths; *flags: what a level's T has, shifted by `shift`
-constexpr int kTFlagBits = 5;
+constexpr int kTFlagBits = 6;
 enum : int {
   kTLongRow = 1,    // a row too long to build
   kTFar = 2,        // a column beyond 16 bits of its 64-row group's base
   kTGroup256 = 4,   // a 64-row group of more than 256 entries
   kTGroup320 = 8,
   kTGroup512 = 16,
+  kSLongRow = 32,   // an aggregate with too many entries to build its row of S
 };
 void launch_tsmooth_count(int n, const int* rp, const int* ci, const int* agg, int* cnt, int* flags, int shift,
                           hipStream_t s);
@@ -454,6 +471,16 @@ void launch_tsmooth_count(int n, const int* rp, const int* ci, const int* agg, i
 // only they are streamed by the post-smoothing
 constexpr int kTsmoothRows = 65536;
 void launch_tsmooth_fill(const Level& lv, hipStream_t s);
+// the pre-smoothing restriction S = P^T (I - A W) of a level: row lengths, then
+// (sp known) columns and values
+void launch_ssmooth_count(const Level& lv, int* cnt, int* flags, int shift, hipStream_t s);
+void launch_ssmooth_fill(const Level& lv, hipStream_t s);
+
+// dense_cycle.hip: the last level's cycle as dense operators
+constexpr int kDenseCycleRows = 2048;        // M_k (n x n): 32 MB in FP64, what the eight L2s hold
+constexpr size_t kDenseCoarse = 1u << 20;    // C S (n_c x n) entries
+bool dense_cycle_wanted(const Level& lv, int nc, int k);
+void launch_dense_cycle(const Level& lv, const double* cinv, Arena& tmp, hipStream_t s);
 
 // arnoldi / reductions (solve_kernels.hip)
 // Reduction context of the solve-phase kernels: per-block partials and the

@@ -239,12 +239,45 @@ bool jacobi_smoothed(const Hierarchy& h) {
   return h.opt.smoother != AMG_SMOOTHER_CHEBYSHEV && h.opt.smoother != AMG_SMOOTHER_MCSGS;
 }
 
+// Whether the level also takes its pre-smoothing and restriction as one
+// operator S_k: small levels, where a launch costs more than the work.  On
+// large ones S_k would be read beside A_k's rows, more bytes than the residual
+// written and read in between.  (A probe times level 0's pre-smoothing by
+// itself, and the one-launch tail has its own.)
+bool restrict_smoothed(const Hierarchy& h, int k) {
+  return h.nsys == 0 && h.levels[k].n <= kTsmoothRows && !(h.opt.flags & AMG_FLAG_PERSISTENT_TAIL) &&
+         (k > 0 || h.opt.probe == AMG_PROBE_NONE);
+}
+
+// S_k's entries (at most A_k's), and the dense operators of the last level
+void alloc_restrict_smoothed(Hierarchy& h, int k) {
+  Level& lv = h.levels[k];
+  const size_t m = (size_t)std::max(lv.nnz, 1);
+  lv.sc = h.arena.alloc_n<int>(m);
+  if (h.mixed()) lv.sv32 = h.arena.alloc_n<float>(m);
+  else lv.sv = h.arena.alloc_n<double>(m);
+  lv.slpr = pick_lanes_per_row(lv.nc, lv.tnnz);
+  if (k + 1 != h.L() || !dense_cycle_wanted(lv, lv.nc, k)) return;
+  const int ld = (lv.n + 3) & ~3;
+  auto dense = [&](size_t rows, double*& d, float*& f) {
+    if (h.mixed()) f = h.arena.alloc_n<float>(rows * ld);
+    else d = h.arena.alloc_n<double>(rows * ld);
+  };
+  if (k > 0 && lv.n <= kDenseCycleRows) {
+    lv.mld = ld;
+    dense(lv.n, lv.mop, lv.mop32);
+  } else {
+    lv.gld = ld;
+    dense(lv.nc, lv.gop, lv.gop32);
+  }
+}
+
 // The pattern of every level's T_k: row lengths, their scan, and the sizes
 // read back together; the values wait for the Jacobi weights (tsmooth_values).
 void tsmooth_patterns(Hierarchy& h, Arena& tmp, Sync& sy) {
   if (!jacobi_smoothed(h)) return;
   const int L = h.L();
-  constexpr int kBatch = 6;   // levels per read-back: their sizes and one word of flags
+  constexpr int kBatch = 5;   // levels per read-back: their sizes and one word of flags
   int* flags = tmp.alloc_n<int>(std::max(L, 1));
   launch_fill_int(L, flags, 0, h.stream);
   for (int k0 = 0; k0 < L; k0 += kBatch) {
@@ -256,6 +289,12 @@ void tsmooth_patterns(Hierarchy& h, Arena& tmp, Sync& sy) {
       lv.tp = h.arena.alloc_n<int>((size_t)lv.n + 1);
       scan_to_ptr(cnt, lv.tp, lv.n, h.scan, h.stream);
       sy.fetch(lv.tp + lv.n, k - k0);
+      if (restrict_smoothed(h, k)) {
+        int* scnt = tmp.alloc_n<int>(std::max(lv.nc, 1));
+        launch_ssmooth_count(lv, scnt, flags + k0, kTFlagBits * (k - k0), h.stream);
+        lv.sp = h.arena.alloc_n<int>((size_t)lv.nc + 1);
+        scan_to_ptr(scnt, lv.sp, lv.nc, h.scan, h.stream);
+      }
     }
     sy.fetch(flags + k0, kBatch);
     sy.wait_and_check();
@@ -266,9 +305,11 @@ void tsmooth_patterns(Hierarchy& h, Arena& tmp, Sync& sy) {
       if (std::getenv("AMG_DEBUG"))
         std::fprintf(stderr, "amg: level %d T nnz=%d of A %d, flags %d\n", k, lv.tnnz, lv.nnz, fl);
       if (fl & kTLongRow) {
-        lv.tp = nullptr;
+        lv.tp = lv.sp = nullptr;
         continue;
       }
+      if (fl & kSLongRow) lv.sp = nullptr;
+      if (lv.sp) alloc_restrict_smoothed(h, k);
       const size_t m = (size_t)std::max(lv.tnnz, 1);
       lv.tlpr = post_lanes(lv.n, lv.tnnz, fl);
       if (lv.tlpr < 0 && !(fl & kTFar) && h.nsys == 0) {   // (a batch's blocks of rows start anywhere)
@@ -483,9 +524,13 @@ void make_float_copies(Hierarchy& h) {
 }  // namespace
 
 // The values of every T_k for the current Jacobi weights.
-static void tsmooth_values(Hierarchy& h) {
-  for (int k = 0; k < h.L(); ++k)
-    if (h.levels[k].tp) launch_tsmooth_fill(h.levels[k], h.stream);
+static void tsmooth_values(Hierarchy& h, Arena& tmp) {
+  for (int k = 0; k < h.L(); ++k) {
+    const Level& lv = h.levels[k];
+    if (lv.tp) launch_tsmooth_fill(lv, h.stream);
+    if (lv.sp) launch_ssmooth_fill(lv, h.stream);
+    if (lv.mld || lv.gld) launch_dense_cycle(lv, h.cinv, tmp, h.stream);
+  }
 }
 
 // Aggregate segments: members of aggregate I at agg_rows[agg_ptr[I]..agg_ptr[I+1]),
@@ -741,7 +786,7 @@ static void judge_learned(Hierarchy& h, Arena& tmp) {
     Level& lv = h.levels[k];
     if (lv.learned) launch_jacobi_weights(lv.n, lv.omega, lv.diag, lv.wdinv, lv.wdinv32, s);
   }
-  tsmooth_values(h);
+  tsmooth_values(h, tmp);
   probe(&h.judge_it_plain, &h.judge_rel_plain);
   const bool keep = h.judge_it_learned < h.judge_it_plain ||
                     (h.judge_it_learned == h.judge_it_plain && h.judge_rel_learned < h.judge_rel_plain);
@@ -757,7 +802,7 @@ static void judge_learned(Hierarchy& h, Arena& tmp) {
     if (keep32[k])
       AMG_HIP(hipMemcpyAsync(lv.wdinv32, keep32[k], (size_t)lv.n * sizeof(float), hipMemcpyDeviceToDevice, s));
   }
-  if (keep) tsmooth_values(h);
+  if (keep) tsmooth_values(h, tmp);
   AMG_HIP(hipStreamSynchronize(s));
 }
 
@@ -996,7 +1041,7 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
     if (h.levels[k].nslices == 0) build_sell(h, tmp, h.levels[k]);
   if (h.L() == 0 || !jacobi_smoothed(h)) sy.wait_and_check();   // else tsmooth_patterns has waited
   take_arnoldi();
-  tsmooth_values(h);
+  tsmooth_values(h, tmp);
   using clk = std::chrono::steady_clock;
   const auto t_tune = clk::now();
   if (!(o.flags & AMG_FLAG_NO_TUNE)) autotune_levels(h);
@@ -1071,8 +1116,8 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
     arnoldi(h, lv, m, o.seed + 1, Q, w, Hh, wn);
     set_jacobi_weight(h, lv, m, Hh, wn);
   }
-  tsmooth_values(h);
   coarse_inverse(h, tmp, sy);
+  tsmooth_values(h, tmp);
   sy.wait_and_check();
   if (repoint) h.multi.reset();   // the kept block workspace's graphs read level 0's old values
   if (repoint && !h.g_iter.empty()) {
@@ -1347,7 +1392,7 @@ void build_batch_hierarchy(Hierarchy& h, const amg_csr& A, const int* sys_off) {
   if (h.mixed()) make_float_copies(h);
   tsmooth_patterns(h, tmp, sy);
   alloc_solve_vectors(h);
-  tsmooth_values(h);
+  tsmooth_values(h, tmp);
   sy.wait_and_check();
   if (!(o.flags & AMG_FLAG_NO_GRAPH)) build_batch_graphs(h);
 }

@@ -973,6 +973,15 @@ template <> const float* pvals<float>(const Level& l) { return l.pval32; }
 template <typename T> const T* tvals(const Level& l);
 template <> const double* tvals<double>(const Level& l) { return l.tv; }
 template <> const float* tvals<float>(const Level& l) { return l.tv32; }
+template <typename T> const T* svals(const Level& l);
+template <> const double* svals<double>(const Level& l) { return l.sv; }
+template <> const float* svals<float>(const Level& l) { return l.sv32; }
+template <typename T> const T* mop(const Level& l);
+template <> const double* mop<double>(const Level& l) { return l.mop; }
+template <> const float* mop<float>(const Level& l) { return l.mop32; }
+template <typename T> const T* gop(const Level& l);
+template <> const double* gop<double>(const Level& l) { return l.gop; }
+template <> const float* gop<float>(const Level& l) { return l.gop32; }
 template <typename T> const T* cinv(const Hierarchy& h);
 template <> const double* cinv<double>(const Hierarchy& h) { return h.cinv; }
 template <> const float* cinv<float>(const Hierarchy& h) { return h.cinv32; }
@@ -1465,6 +1474,135 @@ void post_smooth_t(Hierarchy& h, const Level& lv, int k, Act A, const T* y, T* x
   }
 }
 
+// Levels with S_k = P^T (I - A W) (Level::sp): the post-smoothing forms y too,
+//   x_out = y + T e,  y = W b + W (b - A W b),
+// row i of A and of T by the same lanes, so a cycle takes one launch less on
+// its way down and no vector between the two.  Bound by the chain row pointers
+// -> columns -> gathers and the launch.  57,680 rows, 942,652 entries: S b 6.0
+// us and this 7.0, where pre-smoothing with the restriction took 13.0 and the
+// post-smoothing 5.6; 7,475 rows: 5.5 and 4.2 against 7.2 and 4.4.  Half the
+// lanes take 11.4 us, twice as many 11.0 (both with two gathers per entry: 8.5
+// at these lanes).  DOT: with z'q for the FCG beta.
+template <typename T, class Coarse, bool DOT, bool X0>
+struct OpPostBoth {
+  static constexpr int NV = DOT ? 1 : 0;
+  Act a;
+  const T* b;
+  const T* wd;
+  const T* x0;   // w .* b, where the right-hand side's kernel has written it (X0): one gather less per entry
+  T* xo;
+  Coarse e;
+  const double* q;
+  double* sc;
+  __device__ bool active() const { return a.on(); }
+  __device__ void idle() const {}
+  __device__ T x(int j) const { return X0 ? x0[j] : wd[j] * b[j]; }
+  __device__ void finalize(const double* s) const {
+    if (DOT) sc[kScBeta] = -s[0] / sc[kScPQ];
+  }
+};
+template <typename T, int LPR, class Op>
+__global__ void __launch_bounds__(kBlock) k_post_both(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                      const T* __restrict__ av, const int* __restrict__ tp,
+                                                      const int* __restrict__ tc, const T* __restrict__ tv, Op op,
+                                                      RedCtx rc) {
+  if (!op.active()) return;
+  op.e.begin();
+  constexpr int RPB = kBlock / LPR;
+  const int lane = threadIdx.x & (LPR - 1);
+  double acc[1] = {0.0};
+  const int groups = (n + RPB - 1) / RPB;
+  const int per = (groups + gridDim.x - 1) / gridDim.x;
+  const int g0 = xcd_logical_block() * per, g1 = min(groups, g0 + per);
+  for (int g = g0; g < g1; ++g) {
+    const int row = g * RPB + threadIdx.x / LPR;
+    T ax = T(0), te = T(0), bi = T(0), wi = T(0);
+    double qi = 0.0;
+    if (row < n) {
+      const int s = rp[row], e = rp[row + 1], ts = tp[row], t1 = tp[row + 1];
+      bi = op.b[row];
+      wi = op.wd[row];
+      if constexpr (Op::NV > 0) qi = op.q[row];
+      const int kt = ts + lane;
+      const int ct = kt < t1 ? tc[kt] : -1;
+      const T vt = kt < t1 ? tv[kt] : T(0);
+      for (int k0 = s + lane; k0 < e; k0 += 4 * LPR) {
+        int c[4];
+        T v[4], x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = k0 + q * LPR;
+          c[q] = k < e ? ci[k] : row;
+          v[q] = k < e ? av[k] : T(0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = k0 + q * LPR < e ? op.x(c[q]) : T(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (k0 + q * LPR < e) ax += v[q] * x[q];
+      }
+      if (ct >= 0) te = vt * op.e.at(ct);
+      for (int k = kt + LPR; k < t1; k += LPR) te += tv[k] * op.e.at(tc[k]);
+    }
+    ax = group_sum<LPR>(ax);
+    te = group_sum<LPR>(te);
+    if (row < n && lane == 0) {
+      const T z = two_steps(wi, bi, bi - ax) + te;
+      op.xo[row] = z;
+      if constexpr (Op::NV > 0) acc[0] += (double)z * qi;
+    }
+  }
+  if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
+}
+
+template <typename T, class Coarse>
+void post_both(Hierarchy& h, const Level& lv, Act A, const T* b, const T* wd, const T* x0, T* xo, Coarse e,
+               const double* fuse_q, RedCtx rc) {
+  auto go = [&](const auto& op) {
+    using Op = std::decay_t<decltype(op)>;
+    with_lanes(pick_lpr(lv.n, lv.nnz), [&](auto l) {
+      constexpr int LPR = decltype(l)::value;
+      const int groups = (lv.n + kBlock / LPR - 1) / (kBlock / LPR);
+      const int g = Op::NV > 0 ? std::min(rows_grid(lv.n, LPR, true), resident_blocks(k_post_both<T, LPR, Op>) & ~7)
+                               : groups > 8 ? (groups + 7) & ~7 : groups;
+      const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
+      k_post_both<T, LPR, Op><<<g, kBlock, 0, h.stream>>>(lv.n, lv.rp, lv.ci, vals<T>(lv), lv.tp, lv.tc, tvals<T>(lv),
+                                                          op, RedCtx{rc.part, tail ? rc.ticket : nullptr});
+      if constexpr (Op::NV > 0)
+        if (!tail) k_finalize<Op><<<1, kFinBlock, 0, h.stream>>>(op, rc.part, g);
+    });
+  };
+  if (fuse_q) go(OpPostBoth<T, Coarse, true, false>{A, b, wd, nullptr, xo, e, fuse_q, h.d_sc});   // level 0
+  else if (x0) go(OpPostBoth<T, Coarse, false, true>{A, b, wd, x0, xo, e, nullptr, nullptr});
+  else go(OpPostBoth<T, Coarse, false, false>{A, b, wd, nullptr, xo, e, nullptr, nullptr});
+}
+
+// y = A x for a dense operator of padded rows (16-byte loads; the pad is
+// zero and x is not read there), a block per row.  Bound by reading A where the
+// L2s do not hold it.  779 rows 4.2 us, 1,545 rows 5.4, for three launches of
+// 13.9 us; 244 rows of 2,321 entries 2.9.
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_dense_apply(int n, int ld, const T* __restrict__ A,
+                                                        const T* __restrict__ x, T* __restrict__ y, Act a) {
+  if (!a.on()) return;
+  constexpr int V = 16 / sizeof(T);
+  typedef T Pack __attribute__((ext_vector_type(V)));
+  __shared__ T red[kBlock / kWave];
+  const T* row = A + (size_t)blockIdx.x * ld;
+  T s = T(0);
+#pragma unroll 4
+  for (int j = V * threadIdx.x; j < n; j += V * kBlock) {
+    const Pack m = *reinterpret_cast<const Pack*>(row + j);
+#pragma unroll
+    for (int q = 0; q < V; ++q) s += m[q] * x[min(j + q, n - 1)];
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) y[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+
 // Whether cycle(k) pre-smooths with the row kernel of its level from a zero
 // guess (damped Jacobi, a level that is not the coarsest and does not take the
 // fused pre-smoothing + restriction of small V-cycle levels): then whoever
@@ -1474,7 +1612,7 @@ bool plain_presmooth(const Hierarchy& h, int k) {
   if (k <= 0 || k >= L || h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV || h.opt.smoother == AMG_SMOOTHER_MCSGS)
     return false;
   const bool kcyc = k < h.opt.kcycle_levels && k + 1 < L;
-  return kcyc || h.levels[k].n > kFuseCorrectionRows;
+  return !h.levels[k].mld && (kcyc || h.levels[k].sp || h.levels[k].n > kFuseCorrectionRows);
 }
 
 // cycle(k): x_out = M_k b with a zero initial guess (Algorithm 5 on the top
@@ -1500,13 +1638,19 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
   const T* pv = pvals<T>(lv);
   const int L = h.L();
   const Act A{act};
+  if (lv.mld) {
+    k_dense_apply<T><<<lv.n, kBlock, 0, s>>>(lv.n, lv.mld, mop<T>(lv), b, xo, A);
+    return;
+  }
 
   const bool kcyc = k < h.opt.kcycle_levels && k + 1 < L;
+  const bool both = lv.sp != nullptr;   // r_c = S b, and y in the post-smoothing
   const bool cheb = h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV;
   const bool sgs = h.opt.smoother == AMG_SMOOTHER_MCSGS;
   const bool byT = lv.tp != nullptr;   // post-smoothing by T = (I - W A) P
   const T* y = xt;                     // then the iterate after both smoothing steps
-  if (cheb || sgs) {
+  if (both) {
+  } else if (cheb || sgs) {
     if (cheb) {
       cheb_pre<T>(h, lv, k, A, b, xt, r);
     } else {   // from x = 0, then the residual
@@ -1542,13 +1686,21 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
   const bool nx0 = k + 1 < L && plain_presmooth(h, k + 1);
   const T* wdn = nx0 ? wdinv<T>(h.levels[k + 1]) : nullptr;
   T* xtn = nx0 ? static_cast<T*>(h.levels[k + 1].xt) : nullptr;
-  if (!kcyc && !(!cheb && !sgs && k > 0 && lv.n <= kFuseCorrectionRows))
-    launch_rows<T>(lv.nc, lv.rlpr, lv.agg_ptr, lv.agg_rows, rvals<T>(lv), OpRestrict<T>{A, r, rcv, wdn, xtn}, rc,
-                   s);
+  auto restrict_down = [&] {
+    if (both)
+      launch_rows<T>(lv.nc, lv.slpr, lv.sp, lv.sc, svals<T>(lv), OpRestrict<T>{A, b, rcv, wdn, xtn}, rc, s);
+    else
+      launch_rows<T>(lv.nc, lv.rlpr, lv.agg_ptr, lv.agg_rows, rvals<T>(lv), OpRestrict<T>{A, r, rcv, wdn, xtn}, rc, s);
+  };
+  const bool direct = lv.gld != 0;   // e = (C S) b
+  if (!kcyc && !direct && (both || cheb || sgs || k == 0 || lv.n > kFuseCorrectionRows)) restrict_down();
   if (!kcyc) {
-    if (k + 1 == L) coarse_solve<T>(h, rcv, c, act);
+    if (direct) k_dense_apply<T><<<lv.nc, kBlock, 0, s>>>(lv.n, lv.gld, gop<T>(lv), b, c, A);
+    else if (k + 1 == L) coarse_solve<T>(h, rcv, c, act);
     else cycle<T>(h, k + 1, rcv, c, act, nullptr, nx0);
-    if (byT) {
+    if (both) {
+      post_both<T>(h, lv, A, b, wd, x0 ? xt : nullptr, xo, CoarseV<T>{c}, fuse_q, rc);
+    } else if (byT) {
       post_smooth_t<T>(h, lv, k, A, y, xo, CoarseV<T>{c}, fuse_q, rc);
     } else if (lv.n <= kFuseCorrectionRows) {
       post_smooth<T>(h, lv, k, A, b, xt, wd, xo, CorrV<T>{lv.agg, pv, c}, fuse_q, rc);
@@ -1565,14 +1717,15 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
     T* d = static_cast<T*>(lv.d);
     T* w = static_cast<T*>(lv.w);
     const int gm = h.opt.krylov == AMG_KRYLOV_FGMRES ? 1 : 0;
-    launch_rows<T>(lv.nc, lv.rlpr, lv.agg_ptr, lv.agg_rows, rvals<T>(lv), OpRestrict<T>{A, r, rcv, wdn, xtn}, rc,
-                   s);
+    restrict_down();
     cycle<T>(h, k + 1, rcv, c, act, nullptr, nx0);                     // first inner iteration
     launch_level<T>(lc, OpKDots1<T>{A, c, rcv, v, K, F, gm, h.opt.kcycle_t}, rc, s);
     launch_elem(lc.n, OpRtilde<T>{Act{F}, rcv, v, rt, K, wdn, xtn}, rc, s);
     cycle<T>(h, k + 1, rt, d, F, nullptr, nx0);                        // second inner iteration
     launch_level<T>(lc, OpKDots2<T>{Act{F}, d, v, rt, w, K, F, gm}, rc, s);
-    if (byT && lv.tlpr <= 0) {
+    if (both) {
+      post_both<T>(h, lv, A, b, wd, x0 ? xt : nullptr, xo, CoarseK<T>{c, d, K, F, T(0), T(0), false}, fuse_q, rc);
+    } else if (byT && lv.tlpr <= 0) {
       launch_elem(lc.n, OpCombine<T>{A, c, d, K, F, T(0), T(0), false}, rc, s);
       post_smooth_t<T>(h, lv, k, A, y, xo, CoarseV<T>{c}, fuse_q, rc);
     } else if (byT) {
