@@ -53,6 +53,13 @@ def sdia_diagonals(A) -> int:
     return int(np.unique(key).size)
 
 
+def sym_dia_bytes(A, vectors: int) -> int:
+    """Symmetric diagonals: the offsets col - row >= 0, a value per row each, and
+    `vectors` float64 vectors."""
+    up = A.col - np.repeat(np.arange(A.n), np.diff(A.row_ptr))
+    return 8 * A.n * (int(np.unique(up[up >= 0]).size) + vectors)
+
+
 def sdia_bytes(n, ndiag, vectors, val_bytes=8):
     """Compulsory bytes of a sliced-diagonal kernel: the stored values (64 per
     diagonal and slice), the offsets and slice pointers, and `vectors` n-long
@@ -109,6 +116,10 @@ def kernel_name(fmt: int, lpr: int, op: str) -> str:
         return f"k_sdia<double,{op}> (sliced diagonals, 64-row slices, no column indices)"
     if fmt == 2:
         return f"k_sell<double,{op},true,{h}> (sliced ELL in {h}-row slices, 16-bit column offsets)"
+    if fmt == 5:
+        return f"k_sym_dia_rows<double,{op}> (symmetric diagonals: the main one and those above it)"
+    if fmt == 0 and lpr == 1:
+        return f"k_stream<double,{op}> (CSR rows streamed through LDS)"
     return f"k_sell<double,{op},false,{h}>" if fmt == 1 else f"k_rows<double,{lpr},{op}>"
 
 
@@ -674,8 +685,9 @@ def main():
         tuned = {"kernel": kernel_name(fmt0, lpr0, "OpSpmv<double>"), "us": round(t_lvl * 1e6, 2),
                  "gb_s": round(nbytes / t_lvl / 1e9, 1), "bytes": nbytes,
                  "frac": round(nbytes / t_lvl / 1e9 / PEAK_HBM_GBS, 4), "cache": "flushed before each launch"}
-        if fmt0 in (2, 3):
+        if fmt0 in (2, 3, 5):
             fb = (10 * A.nnz + 4 * ((A.n + 63) // 64 + 1) + 16 * A.n if fmt0 == 2
+                  else sym_dia_bytes(A, 2) if fmt0 == 5
                   else sdia_bytes(A.n, sdia_diagonals(A), 2))
             tuned["format_bytes"] = fb
             tuned["format_gb_s"] = round(fb / t_lvl / 1e9, 1)
@@ -691,13 +703,14 @@ def main():
         ach = pbytes / (probe_ms * 1e-3) / 1e9
         line["roofline"] = {"bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                             "frac": round(ach / PEAK_HBM_GBS, 4), "traffic": measured_traffic(args.workload),
-                            "kernel": (kernel_name(probe_fmt[0], probe_fmt[1], "OpPresmoothResid<double>")
-                                       if probe_fmt else "level-0 OpPresmoothResid<double>")
+                            "kernel": (kernel_name(probe_fmt[0], probe_fmt[1], "OpPresmooth2<double>")
+                                       if probe_fmt else "level-0 OpPresmooth2<double>")
                                       + " (level-0 pre-smoothing + residual, inside the solve)",
                             "bytes_per_launch": pbytes, "avg_us": round(probe_ms * 1e3, 2),
                             "samples": probe_n}
-        if probe_fmt and probe_fmt[0] in (2, 3):
+        if probe_fmt and probe_fmt[0] in (2, 3, 5):
             fb = (presmooth_bytes_offsets16(A.n, A.nnz) if probe_fmt[0] == 2
+                  else sym_dia_bytes(A, 4) if probe_fmt[0] == 5
                   else sdia_bytes(A.n, sdia_diagonals(A), 4))
             line["roofline"]["format_bytes_per_launch"] = fb
             line["roofline"]["format_gb_s"] = round(fb / (probe_ms * 1e-3) / 1e9, 1)

@@ -237,7 +237,10 @@ int32_t amg_setup_batched(const amg_csr* A, int32_t nsys, const int32_t* sys_off
  * indices; built for levels whose slices have few diagonals, as on
  * structured grids; *lanes_per_row = 1), 4 = CSR with its columns as 16-bit
  * offsets col - row (levels whose offsets all fit; *lanes_per_row lanes per
- * row); for the sliced ELL,
+ * row), 5 = symmetric diagonals (the main diagonal and those above it over all
+ * rows; structured levels whose operator equals its transpose bit for bit;
+ * *lanes_per_row = 1; a re-setup to other values goes back to 3 or 0); CSR with
+ * *lanes_per_row = 1 streams its rows through LDS; for the sliced ELL,
  * *lanes_per_row = 64 / slice height (1: 64-row slices; 2 or 4: the level's
  * copy in 32- or 16-row slices, built where rows vary in length);
  * us (host, may be NULL) = its timed duration (0 if the level was not timed).

@@ -79,6 +79,8 @@ struct ScanCtx {
 // ---------------------------------------------------------------- records
 struct TermInfo;
 
+constexpr int kSymDiaMin = 3, kSymDiaMax = 5;   // stored diagonals of a level in symmetric diagonals
+
 struct Level {
   // A_k (float64, device); val32 is the float32 copy used by the mixed cycle
   int n = 0, nnz = 0;
@@ -128,6 +130,17 @@ struct Level {
     float* val32 = nullptr;
   } dia;
   std::shared_ptr<Arena> dia_mem;
+  // symmetric diagonals (levels from structured grids whose operator is
+  // symmetric bit for bit): the diagonal and the diagonals above it, each as a
+  // vector over the rows; a_{i, i-d} is read as a_{i-d, i}
+  struct SymDia {
+    int u = 0;                   // stored diagonals, the main one first
+    int off[kSymDiaMax] = {};    // their offsets, ascending (off[0] = 0)
+    long ld = 0;                 // values per diagonal (n rounded up to slices)
+    double* val = nullptr;       // [u][ld], zero where a row has no entry
+    float* val32 = nullptr;
+  } sym;
+  std::shared_ptr<Arena> sym_mem;
   // the CSR columns as 16-bit offsets col - row (2 bytes per entry instead of
   // 4), for the row kernels on levels whose offsets all fit (those with the
   // 16-bit sliced ELL); built for the autotuner, kept while it is chosen
@@ -135,7 +148,8 @@ struct Level {
   std::shared_ptr<Arena> ci16_mem;
   // kernel choice per arithmetic type (autotuned): fmt 0 = CSR with lpr lanes
   // per row, fmt 1 = sliced ELL, fmt 2 = sliced ELL with 16-bit column offsets,
-  // fmt 3 = sliced diagonals, fmt 4 = CSR with 16-bit column offsets
+  // fmt 3 = sliced diagonals, fmt 4 = CSR with 16-bit column offsets,
+  // fmt 5 = symmetric diagonals
   // pz: schedule of the slice kernels (0 contiguous, -1 XCD sweep, > 0
   // plane-ordered over that many steps)
   // tile: columns per pass of the block kernels (several right-hand sides)
@@ -429,6 +443,13 @@ void launch_window_order(int n, const int* rp, int* perm, hipStream_t s);
 // ci16[k] = ci[k] - row for the entries of each row (offsets known to fit)
 void launch_ci16(int n, const int* rp, const int* ci, int16_t* ci16, hipStream_t s);
 void launch_sdia_count(int n, const int* rp, const int* ci, int cap, int* cnt, int* over, hipStream_t s);
+// distinct offsets col - row > 0 into list[0 .. kSymDiaMax), zero where free;
+// *over: more than fit
+void launch_upper_offsets(int n, const int* rp, const int* ci, int* list, int* over, hipStream_t s);
+// the stored diagonals' values; check: *asym raised unless every entry below
+// the diagonal equals its mirror image
+void launch_sym_dia_fill(const Level& lv, hipStream_t s);
+void launch_sym_dia_check(const Level& lv, int* asym, hipStream_t s);
 void launch_sdia_fill(int n, const int* rp, const int* ci, const double* val, const int* dg_ptr, int* dg_off,
                       double* dg_val, float* dg_val32, hipStream_t s);
 
@@ -560,11 +581,13 @@ void launch_rs_fill(const Level& lv, const Level& lc, int* cur, int* tf, int* ti
 void launch_rs_values(const Level& lv, Level& lc, hipStream_t s);
 void launch_rs_diag(const Level& lv, hipStream_t s);
 void launch_rs_sell_values(const Level& lv, hipStream_t s);
+void launch_rs_sym_dia(const Level& lv, int* asym, hipStream_t s);
 // the short-slice copy of a level, when it pays (slice_h = 0) or in slices of
 // slice_h = 32 or 16 rows (hierarchy.cpp)
 void build_short_sell(Hierarchy& h, Level& lv, int slice_h);
 // the sliced-diagonal copy of a level, when its slices have few diagonals
 void build_sdia(Hierarchy& h, Level& lv);
+void build_sym_dia(Hierarchy& h, Level& lv);
 void launch_set16(double* dst, const double* host16, hipStream_t s);
 // coloring.hip: first-fit colouring by node-hash priority in synchronous rounds
 void launch_color_round(int n, const int* rp, const int* ci, uint32_t stream, const int* cin, int* cout, int* left,

@@ -506,6 +506,47 @@ void build_sdia(Hierarchy& h, Level& lv) {
   lv.dia_mem = mem;
 }
 
+// The symmetric diagonals of a level: built when the offsets above the
+// diagonal are kSymDiaMin - 1 to kSymDiaMax - 1 (five-, seven- and nine-point
+// grids), their padding is at most kSdiaPad, and the operator equals its
+// transpose bit for bit.
+void build_sym_dia(Hierarchy& h, Level& lv) {
+  lv.sym = Level::SymDia{};
+  lv.sym_mem.reset();
+  if (lv.n <= 0 || lv.nnz <= 0) return;
+  auto mem = std::make_shared<Arena>();
+  int* list = mem->alloc_n<int>(kSymDiaMax + 1);   // and the overflow word
+  launch_fill_int(kSymDiaMax + 1, list, 0, h.stream);
+  launch_upper_offsets(lv.n, lv.rp, lv.ci, list, list + kSymDiaMax, h.stream);
+  Sync sy{h};
+  for (int t = 0; t <= kSymDiaMax; ++t) sy.fetch(list + t, t);
+  sy.wait_and_check();
+  Level::SymDia q;
+  for (int t = 0; t < kSymDiaMax && sy.hp()[t]; ++t) {
+    if (q.u == kSymDiaMax - 1) return;
+    q.off[++q.u] = sy.hp()[t];
+  }
+  ++q.u;
+  if (sy.hp()[kSymDiaMax] || q.u < kSymDiaMin) return;
+  std::sort(q.off, q.off + q.u);
+  if ((2.0 * q.u - 1.0) * lv.n > (1.0 + kSdiaPad) * (double)lv.nnz) return;
+  q.ld = ((long)lv.n + kSdiaRows - 1) / kSdiaRows * kSdiaRows;
+  q.val = mem->alloc_n<double>((size_t)q.u * q.ld);
+  if (h.mixed()) q.val32 = mem->alloc_n<float>((size_t)q.u * q.ld);
+  lv.sym = q;
+  launch_sym_dia_fill(lv, h.stream);
+  launch_sym_dia_check(lv, list + kSymDiaMax, h.stream);
+  sy.fetch(list + kSymDiaMax, 0);
+  sy.wait_and_check();
+  if (std::getenv("AMG_DEBUG"))
+    std::fprintf(stderr, "amg: symmetric diagonals n=%d: %d stored%s\n", lv.n, q.u, sy.hp()[0] ? ", not symmetric" : "");
+  if (sy.hp()[0]) {
+    lv.sym = Level::SymDia{};
+    return;
+  }
+  lv.sym_mem = mem;
+}
+
 namespace {
 
 void make_float_copies(Hierarchy& h) {
@@ -1058,6 +1099,18 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
 }
 
 
+// A level leaves its symmetric diagonals for the sliced ones (or, where those
+// would be padded too far, for CSR).
+static void drop_sym_dia(Hierarchy& h, Level& lv) {
+  if (!lv.sym.u) return;
+  AMG_HIP(hipStreamSynchronize(h.stream));
+  lv.sym = Level::SymDia{};
+  lv.sym_mem.reset();
+  if (!lv.dia.ptr) build_sdia(h, lv);
+  for (Level::Tune* t : {&lv.t64, &lv.t32})
+    if (t->fmt == 5) t->fmt = lv.dia.ptr ? 3 : 0;
+}
+
 // Numeric re-setup on the fixed pattern (Section 3.1, index reuse): new
 // values of A_0; every level keeps its strength, MIS(2), aggregates and P_k;
 // A_{k+1} is replayed from the stored term lists (built by the first call),
@@ -1105,7 +1158,15 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
     launch_rs_sell_values(lv, s);
     if (h.mixed()) launch_to_float(lv.nnz, lv.val, lv.val32, s);
   }
+  int* asym = tmp.alloc_n<int>(1);   // raised when a level's new values are not symmetric any more
+  launch_fill_int(1, asym, 0, s);
+  for (int k = 0; k < L; ++k) launch_rs_sym_dia(h.levels[k], asym, s);
+  sy.fetch(asym, 0);
   sy.wait_and_check();
+  if (sy.hp()[0]) {
+    for (int k = 0; k < L; ++k) drop_sym_dia(h, h.levels[k]);
+    repoint = true;   // the captured kernels read that copy
+  }
   for (int k = 0; k < L; ++k) {
     Level& lv = h.levels[k];
     const int m = std::min(o.arnoldi_m, lv.n);

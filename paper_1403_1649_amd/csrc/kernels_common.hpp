@@ -406,6 +406,55 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, int nslices, const int* 
   if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
 }
 
+// Symmetric diagonals: the main diagonal and those above it, one vector over
+// the rows each (offsets d, ascending, the same for every row); row i takes
+// a_{i, i-d} from where row i-d stores it, off every other XCD's path in the
+// sweep (L2 while the sweep's window of the largest offset fits, 2 MB at
+// 25,600 rows).  A structured seven-point level moves 32 bytes of values per
+// row instead of 56 (sliced diagonals) from memory.  Products are summed in
+// ascending columns, as in the other layouts.
+template <int U>
+struct SymOff {
+  int d[U];
+};
+template <typename T, int U, class Op>
+__global__ void __launch_bounds__(kBlock) k_sym_dia_rows(int n, long ld, SymOff<U> off, const T* __restrict__ val,
+                                                         Op op, RedCtx rc, int pstep) {
+  if (!op.active()) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
+    return;
+  }
+  double acc[Op::NV > 0 ? Op::NV : 1];
+#pragma unroll
+  for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
+  const int steps = (int)((ld + kBlock - 1) / kBlock);
+  for (Steps st = block_steps(steps, pstep); st.u < st.end; st.u += st.inc) {
+    const int row = st.step() * kBlock + (int)threadIdx.x;
+    if (row >= n) continue;
+    T lo[U], up[U], xl[U], xu[U];
+#pragma unroll
+    for (int t = 0; t < U; ++t) {
+      up[t] = val[t * ld + row];
+      const int j = row - off.d[t];
+      lo[t] = t > 0 ? val[t * ld + (j < 0 ? 0 : j)] : T(0);
+    }
+#pragma unroll
+    for (int t = 0; t < U; ++t) {   // past either end: a zero value, or not taken
+      const int j = row - off.d[t], k = row + off.d[t];
+      xu[t] = op.x(k < n ? k : n - 1);
+      xl[t] = t > 0 ? op.x(j < 0 ? 0 : j) : T(0);
+    }
+    T sum = T(0);
+#pragma unroll
+    for (int t = U - 1; t > 0; --t)
+      if (row >= off.d[t]) sum += lo[t] * xl[t];
+#pragma unroll
+    for (int t = 0; t < U; ++t) sum += up[t] * xu[t];
+    op.row(row, sum, acc);
+  }
+  if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
+}
+
 // Sliced diagonals: slices of 64 rows (one wave), each with its own short
 // list of diagonal offsets d (col = row + d, ascending): slice s holds
 // offsets dg_off[dg_ptr[s] .. dg_ptr[s+1]) and, for the q-th of them, the
@@ -629,6 +678,27 @@ void launch_sell(int n, int nslices, const int* sl_ptr, const int* sl_col, const
     else if (slice_h == 16) launch_sell_h<T, Op, false, 16>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
     else launch_sell_h<T, Op, false, 64>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
   }
+}
+
+template <typename T, class Op>
+void launch_sym_dia(int n, const Level::SymDia& q, const T* val, const Op& op, RedCtx rc, hipStream_t s,
+                    int pstep = 0) {
+  const int steps = (int)(q.ld / kBlock) + (q.ld % kBlock != 0);
+  auto go = [&](auto u) {
+    constexpr int U = decltype(u)::value;
+    SymOff<U> o;
+    for (int t = 0; t < U; ++t) o.d[t] = q.off[t];
+    const int g = step_grid(steps, resident_blocks(k_sym_dia_rows<T, U, Op>));
+    const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
+    k_sym_dia_rows<T, U, Op><<<g, kBlock, 0, s>>>(n, q.ld, o, val, op, RedCtx{rc.part, tail ? rc.ticket : nullptr},
+                                                  pstep);
+    if constexpr (Op::NV > 0)
+      if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
+  };
+  static_assert(kSymDiaMin == 3 && kSymDiaMax == 5, "one kernel per number of stored diagonals");
+  if (q.u == 3) go(std::integral_constant<int, 3>());
+  else if (q.u == 4) go(std::integral_constant<int, 4>());
+  else go(std::integral_constant<int, 5>());
 }
 
 template <typename T, class Op>

@@ -168,4 +168,10 @@ void launch_rs_sell_values(const Level& lv, hipStream_t s) {
   }
 }
 
+void launch_rs_sym_dia(const Level& lv, int* asym, hipStream_t s) {
+  if (!lv.sym.u) return;
+  launch_sym_dia_fill(lv, s);
+  launch_sym_dia_check(lv, asym, s);
+}
+
 }  // namespace amg

@@ -651,6 +651,97 @@ __global__ void __launch_bounds__(256) k_sdia_build(int n, int nslices, const in
   if (!FILL && lane == 0) cnt[sl] = q;
 }
 
+// Symmetric diagonals.  The offsets above the diagonal: each block collects its
+// rows' in LDS, then adds those that the list does not hold yet (every thread
+// going to the list took 15 ms in compare-and-swaps on one word).
+__device__ __forceinline__ bool add_offset(int* list, int d, bool shared) {
+  for (int t = 0; t < kSymDiaMax; ++t) {
+    int k = shared ? *(volatile int*)&list[t] : __hip_atomic_load(list + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (k == 0) k = atomicCAS(list + t, 0, d);
+    if (k == 0 || k == d) return true;
+  }
+  return false;
+}
+__global__ void __launch_bounds__(256) k_upper_offsets(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                       int* list, int* over) {
+  __shared__ int own[kSymDiaMax];
+  __shared__ int s_over;
+  if (threadIdx.x < kSymDiaMax) own[threadIdx.x] = 0;
+  if (threadIdx.x == 0) s_over = __hip_atomic_load(over, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_over) return;
+  bool full = false;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n && !full; i += gridDim.x * 256) {
+    const int b = rp[i];
+    for (int e = rp[i + 1] - 1; e >= b && !full; --e) {
+      const int d = ci[e] - i;
+      if (d <= 0) break;
+      full = !add_offset(own, d, true);
+    }
+  }
+  if (full) s_over = 1;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int t = 0; t < kSymDiaMax && own[t] && !s_over; ++t) s_over = !add_offset(list, own[t], false);
+  if (s_over) atomicOr(over, 1);
+}
+
+// A wave per 64 rows, whose entries (one run of A) come coalesced into LDS
+// when they fit; then each lane walks its row.  FILL: the stored diagonals'
+// values, zero where the row has no entry.  Otherwise the entries below the
+// diagonal are compared with their mirror images.
+constexpr int kSymCap = 640;   // ten entries a row
+template <bool FILL>
+__global__ void __launch_bounds__(256) k_sym_dia(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                 const double* __restrict__ val, Level::SymDia q, int* asym) {
+  __shared__ int s_c[4][kSymCap];
+  __shared__ double s_v[4][kSymCap];
+  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+  const int row0 = (blockIdx.x * 4 + wv) * kWave;
+  if (row0 >= n) return;   // the whole wave; nothing below waits for the block
+  const int row = row0 + lane;
+  const int beg = row < n ? rp[row] : 0, end = row < n ? rp[row + 1] : 0;
+  const int base = __builtin_amdgcn_readfirstlane(beg);
+  const int total = rp[min(row0 + kWave, n)] - base;
+  const bool staged = total <= kSymCap;
+  if (staged) {
+    for (int k = lane; k < total; k += kWave) {
+      s_c[wv][k] = ci[base + k];
+      s_v[wv][k] = val[base + k];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  auto col = [&](int e) { return staged ? s_c[wv][e - base] : ci[e]; };
+  auto value = [&](int e) { return staged ? s_v[wv][e - base] : val[e]; };
+  if constexpr (FILL) {
+    int e = beg;
+    while (e < end && col(e) < row) ++e;
+    for (int t = 0; t < q.u; ++t) {
+      double v = 0.0;
+      if (e < end && col(e) - row == q.off[t]) v = value(e++);
+      q.val[(size_t)t * q.ld + row] = v;
+      if (q.val32) q.val32[(size_t)t * q.ld + row] = (float)v;
+    }
+  } else {
+    bool differs = false;
+    for (int e = beg; e < end; ++e) {
+      const int d = row - col(e);
+      if (d <= 0) break;
+      double m = 0.0;
+      bool known = false;
+      for (int t = 1; t < q.u; ++t)
+        if (q.off[t] == d) {
+          m = q.val[(size_t)t * q.ld + row - d];
+          known = true;
+        }
+      differs |= !known || !(m == value(e));
+    }
+    if (__any(differs) && lane == 0) atomicOr(asym, 1);
+  }
+}
+
 // The row order of the copies in shorter slices: within each window of 256
 // rows, rows by decreasing length (ties by index), a bitonic sort of
 // (length, index) keys in LDS.  perm has a whole number of windows; its slots
@@ -991,6 +1082,16 @@ void launch_sdia_fill(int n, const int* rp, const int* ci, const double* val, co
   if (nsl > 0)
     k_sdia_build<true><<<g, 256, 0, s>>>(n, nsl, rp, ci, val, 0, nullptr, dg_ptr, dg_off, dg_val, dg_val32,
                                          nullptr);
+}
+void launch_upper_offsets(int n, const int* rp, const int* ci, int* list, int* over, hipStream_t s) {
+  if (n > 0) k_upper_offsets<<<std::min((n + 255) / 256, 1024), 256, 0, s>>>(n, rp, ci, list, over);
+}
+void launch_sym_dia_fill(const Level& lv, hipStream_t s) {
+  if (lv.n > 0)
+    k_sym_dia<true><<<(lv.n + 255) / 256, 256, 0, s>>>(lv.n, lv.rp, lv.ci, lv.val, lv.sym, nullptr);
+}
+void launch_sym_dia_check(const Level& lv, int* asym, hipStream_t s) {
+  if (lv.n > 0) k_sym_dia<false><<<(lv.n + 255) / 256, 256, 0, s>>>(lv.n, lv.rp, lv.ci, lv.val, lv.sym, asym);
 }
 // the CSR columns as 16-bit offsets, one thread per row
 __global__ void k_ci16(int n, const int* __restrict__ rp, const int* __restrict__ ci, int16_t* __restrict__ ci16) {

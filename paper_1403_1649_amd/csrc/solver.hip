@@ -1000,6 +1000,9 @@ template <> const float* short_vals<float>(const Level& l) { return l.sh.val32; 
 template <typename T> const T* dia_vals(const Level& l);
 template <> const double* dia_vals<double>(const Level& l) { return l.dia.val; }
 template <> const float* dia_vals<float>(const Level& l) { return l.dia.val32; }
+template <typename T> const T* sym_vals(const Level& l);
+template <> const double* sym_vals<double>(const Level& l) { return l.sym.val; }
+template <> const float* sym_vals<float>(const Level& l) { return l.sym.val32; }
 
 // A row operation on A_k with the level's tuned kernel (CSR, sliced ELL in
 // 64-row slices or in the level's shorter slices, or sliced diagonals).
@@ -1008,6 +1011,8 @@ void launch_level(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
   const Level::Tune& t = tune_of<T>(lv);
   if (t.fmt == 4 && lv.ci16)
     launch_rows16<T>(lv.n, t.lpr, lv.rp, lv.ci16, vals<T>(lv), op, rc, s);
+  else if (t.fmt == 5 && sym_vals<T>(lv))
+    launch_sym_dia<T>(lv.n, lv.sym, sym_vals<T>(lv), op, rc, s, t.pz);
   else if (t.fmt == 3 && dia_vals<T>(lv))
     launch_sdia<T>(lv.n, lv.dia.nslices, lv.dia.ptr, lv.dia.off, dia_vals<T>(lv), op, rc, s, t.pz);
   else if (t.fmt >= 1 && t.sh > 0 && t.sh == lv.sh.h && short_vals<T>(lv))
@@ -2335,7 +2340,7 @@ std::vector<int> schedules(int nslices, int off) {
 // Time the pre-smoothing kernel for CSR with 2..32 lanes per row (with 32-
 // and 16-bit columns) and for sliced ELL with 32- and 16-bit columns (in the
 // schedules above); keep the fastest (AMG_TUNE_FORCE = csr, csr16, sell,
-// sell16 or sdia pins the format where the level has it, for tests).  Results are cached per level shape (n, nnz,
+// sell16, sdia or symdia pins the format where the level has it, for tests).  Results are cached per level shape (n, nnz,
 // sliced-ELL size) and value size for the process and, when AMG_TUNE_CACHE
 // names a file, across processes (one JSON object per line).
 template <typename T>
@@ -2409,7 +2414,7 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
                    us, best.us);
     if (us <= kPreferFewerBytes * best.us) { best.us = std::min(us, best.us); best.fmt = 4; best.lpr = lpr; }
   }
-  const int off = (lv.sl_ptr && sell_vals<T>(lv)) || dia_vals<T>(lv) ? max_column_offset(h, lv) : 0;
+  const int off = (lv.sl_ptr && sell_vals<T>(lv)) || dia_vals<T>(lv) || sym_vals<T>(lv) ? max_column_offset(h, lv) : 0;
   if (lv.sl_ptr && sell_vals<T>(lv)) {
     for (int p : schedules(lv.nslices, off)) {
       const float us = time_it([&] {
@@ -2457,7 +2462,17 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
       if (us < best.us || over_sell) { best.us = us; best.fmt = 3; best.lpr = lv.lpr; best.pz = p; best.sh = 0; }
     }
   }
-  if (force) {   // "csr", "csr16", "sell", "sell16" or "sdia", the sliced ELL optionally ":32" or ":16" (slice height)
+  if (sym_vals<T>(lv)) {   // fewer bytes again
+    for (int p : schedules((int)(lv.sym.ld / kWave), off)) {
+      const float us = time_it([&] { launch_sym_dia<T>(lv.n, lv.sym, sym_vals<T>(lv), op, rc, s, p); });
+      if (std::getenv("AMG_DEBUG"))
+        std::fprintf(stderr, "amg: level n=%d symmetric diagonals pz=%d: %.2f us (best so far %.2f)\n", lv.n, p, us,
+                     best.us);
+      const bool over_sliced = best.fmt >= 1 && best.fmt <= 3 && best.sh == 0 && us <= kPreferFewerBytes * best.us;
+      if (us < best.us || over_sliced) { best.us = us; best.fmt = 5; best.lpr = lv.lpr; best.pz = p; best.sh = 0; }
+    }
+  }
+  if (force) {   // "csr", "csr16", "sell", "sell16", "sdia" or "symdia", the sliced ELL optionally ":32" or ":16" (slice height)
     std::string w(force);
     int fh = 0;
     const size_t colon = w.find(':');
@@ -2480,6 +2495,11 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
         best.fmt = 3;
         best.sh = 0;
       }
+    } else if (w == "symdia") {
+      if (sym_vals<T>(lv)) {
+        best.fmt = 5;
+        best.sh = 0;
+      }
     } else if (w == "sell" && lv.sl_ptr) {
       best.fmt = 1;
       best.sh = short_ok ? fh : 0;
@@ -2489,7 +2509,7 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
     }
     if (best.sh) best.pz = 0;
     else if (best.fmt != 0 && std::getenv("AMG_TUNE_SCHEDULE"))
-      best.pz = schedules(best.fmt == 3 ? lv.dia.nslices : lv.nslices, off).front();
+      best.pz = schedules(best.fmt == 5 ? (int)(lv.sym.ld / kWave) : best.fmt == 3 ? lv.dia.nslices : lv.nslices, off).front();
     return best;   // not cached
   }
   if (!std::getenv("AMG_TUNE_SLICE") && !std::getenv("AMG_TUNE_SCHEDULE")) tune_cache_put(key, best);
@@ -2509,6 +2529,7 @@ void autotune_levels(Hierarchy& h) {
     // decisions of this level shape use neither
     bool need_sh = lv.n > kFuseCorrectionRows && lv.sl_ptr;
     bool need_dia = need_sh;
+    bool need_sym = need_sh;
     bool need_c16 = need_sh && lv.sl_dcol;   // the offsets fit in 16 bits
     if (need_sh && !pinned) {
       TuneKey key;
@@ -2524,11 +2545,15 @@ void autotune_levels(Hierarchy& h) {
       if (h32 && h64) {
         need_sh = (h.mixed() && c32.sh > 0) || (use64 && c64.sh > 0);
         need_dia = (h.mixed() && c32.fmt == 3) || (use64 && c64.fmt == 3);
+        need_sym = (h.mixed() && c32.fmt == 5) || (use64 && c64.fmt == 5);
         need_c16 = need_c16 && ((h.mixed() && c32.fmt == 4) || (use64 && c64.fmt == 4));
       }
     }
     if (need_sh) build_short_sell(h, lv, force_h ? std::atoi(force_h) : 0);
-    if (need_dia) build_sdia(h, lv);
+    if (need_sym) build_sym_dia(h, lv);
+    // (another matrix of the cached shape may be nonsymmetric)
+    const bool lost_sym = need_sym && !lv.sym.u;
+    if (need_dia || lost_sym) build_sdia(h, lv);
     if (need_c16 && !lv.ci16) {
       auto mem = std::make_shared<Arena>();
       lv.ci16 = mem->alloc_n<int16_t>((size_t)std::max(lv.nnz, 1));
@@ -2544,6 +2569,13 @@ void autotune_levels(Hierarchy& h) {
     if (lv.sh.ptr && lv.t64.sh != lv.sh.h && lv.t32.sh != lv.sh.h) {   // not chosen: release it
       lv.sh = Level::ShortSell{};
       lv.sh_mem.reset();
+    }
+    if (lost_sym)
+      for (Level::Tune* t : {&lv.t64, &lv.t32})
+        if (t->fmt == 5) t->fmt = lv.dia.ptr ? 3 : 0;
+    if (lv.sym.u && lv.t64.fmt != 5 && lv.t32.fmt != 5) {
+      lv.sym = Level::SymDia{};
+      lv.sym_mem.reset();
     }
     if (lv.dia.ptr && lv.t64.fmt != 3 && lv.t32.fmt != 3) {
       lv.dia = Level::Sdia{};
