@@ -1047,11 +1047,10 @@ void probe_point(Hierarchy& h, bool selected, std::function<void(hipStream_t)> f
 }
 
 // ------------------------------------------------------------ V-cycle tail, one launch
-// The V-cycle levels below the K-cycle that take the fused small-level path,
-// with the coarse solve, run as one persistent launch instead of one kernel
-// per step: the steps are phases (pre-smoothing + restriction per level down,
-// the coarse product, residual + post-smoothing + prolongation per level up),
-// each cut into work items.  Blocks take items in one global order from a
+// The V-cycle levels below the K-cycle that hold S and T, with the coarse
+// solve, run as one persistent launch instead of one kernel per step: the steps
+// are phases (S b per level down, the last level's dense operator or the coarse
+// product, the post-smoothing per level up), each cut into work items.  Blocks take items in one global order from a
 // ticket counter and an item waits until every item of the previous phase is
 // done (a per-phase counter).  A block only ever waits for items with smaller
 // tickets, which blocks already running hold, so the launch cannot deadlock
@@ -1067,128 +1066,173 @@ void probe_point(Hierarchy& h, bool selected, std::function<void(hipStream_t)> f
 // counters' device-scope atomics and the release fence per item cost more
 // than the launch gaps saved.
 constexpr int kTailMax = 8;            // levels in one tail launch
-constexpr int kTailAggPerItem = 16;    // aggregates per pre-smoothing item
-constexpr int kTailGroupsPerItem = 16; // row groups per post-smoothing item
+constexpr int kTailGroupsPerItem = 16; // row groups per item
+constexpr int kTailDenseRows = 4;      // rows of the dense operator per item
 constexpr int kTailGrid = 256;
 constexpr long kTailSpin = 1L << 22;   // bound of a wait (an error, not a hang, if ever reached)
 
+// y = A x for a dense operator of padded rows (16-byte loads; the pad is
+// zero and x is not read there), a block per row.  Bound by reading A where the
+// L2s do not hold it.  779 rows 4.2 us, 1,545 rows 5.4, for three launches of
+// 13.9 us; 244 rows of 2,321 entries 2.9.
+template <typename T>
+__device__ __forceinline__ T dense_row(int n, const T* __restrict__ row, const T* x, T* red) {
+  constexpr int V = 16 / sizeof(T);
+  typedef T Pack __attribute__((ext_vector_type(V)));
+  T s = T(0);
+#pragma unroll 4
+  for (int j = V * threadIdx.x; j < n; j += V * kBlock) {
+    const Pack m = *reinterpret_cast<const Pack*>(row + j);
+#pragma unroll
+    for (int q = 0; q < V; ++q) s += m[q] * x[min(j + q, n - 1)];
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_dense_apply(int n, int ld, const T* __restrict__ A,
+                                                        const T* __restrict__ x, T* __restrict__ y, Act a) {
+  if (!a.on()) return;
+  __shared__ T red[kBlock / kWave];
+  const T s = dense_row(n, A + (size_t)blockIdx.x * ld, x, red);
+  if (threadIdx.x == 0) y[blockIdx.x] = s;
+}
+
+// A lane's share of row `row` of A x and of T e (k_post_both)
+template <typename T, int LPR, class X, class E>
+__device__ __forceinline__ void both_sums(int row, int lane, const int* __restrict__ rp, const int* __restrict__ ci,
+                                          const T* __restrict__ av, const int* __restrict__ tp,
+                                          const int* __restrict__ tc, const T* __restrict__ tv, X x, E e, T& ax, T& te) {
+  const int s = rp[row], end = rp[row + 1], ts = tp[row], t1 = tp[row + 1];
+  const int kt = ts + lane;
+  const int ct = kt < t1 ? tc[kt] : -1;
+  const T vt = kt < t1 ? tv[kt] : T(0);
+  for (int k0 = s + lane; k0 < end; k0 += 4 * LPR) {
+    int c[4];
+    T v[4], xv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + q * LPR;
+      c[q] = k < end ? ci[k] : row;
+      v[q] = k < end ? av[k] : T(0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) xv[q] = k0 + q * LPR < end ? x(c[q]) : T(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (k0 + q * LPR < end) ax += v[q] * xv[q];
+  }
+  if (ct >= 0) te = vt * e(ct);
+  for (int k = kt + LPR; k < t1; k += LPR) te += tv[k] * e(tc[k]);
+}
+
 template <typename T>
 struct TailLevel {
-  int n, nc, lpr;
+  int n, nc, slpr, lpr;
   const int* rp;
   const int* ci;
   const T* av;
-  const int* agg_ptr;
-  const int* agg_rows;
-  const T* rv;
+  const int* sp;    // S = P^T (I - A W)
+  const int* sc;
+  const T* sv;
   const int* tp;    // T = (I - W A) P
   const int* tc;
   const T* tv;
-  int tlpr;
   const T* wd;
   const T* b;   // right-hand side (written in this launch except on the first level)
-  T* xt;        // iterate after both smoothing steps
-  T* rc;        // restricted residual = right-hand side of the next level
+  T* rc;        // right-hand side of the next level
   T* c;         // correction = iterate of the next level
   T* xo;        // smoothed output
 };
 
+// What a phase computes: S b, a dense operator's rows (the last level's whole
+// cycle or its coarse correction), the coarse product, the post-smoothing.
+enum TailKind : int { kTailDown, kTailDense, kTailCoarse, kTailUp };
+
 template <typename T>
 struct TailArgs {
-  int nlev, nphase, ncoarse;
+  int nphase, ncoarse;
   const T* cinv;
   unsigned* ctl;   // [0] ticket, [1] blocks that left, [2 + p] items done in phase p
   int* err;
+  const T* dense;  // rows x dense_n (padded to dense_ld), of the last level
+  int dense_rows, dense_n, dense_ld;
+  const T* dense_b;
+  T* dense_x;
+  int kind[2 * kTailMax + 1], level[2 * kTailMax + 1];
   int start[2 * kTailMax + 2];   // first item of each phase; start[nphase] = all items
   TailLevel<T> lv[kTailMax];
 };
 
-// a value written by another block of this launch: a vector load (the
-// addresses differ across lanes) after the acquire fence of the wait
-template <typename T>
-__device__ __forceinline__ T tail_ld(const T* p) {
-  return *p;
-}
-template <typename T>
-__device__ __forceinline__ T tail_ldb(const T* p, bool first) {
-  return first ? *p : tail_ld(p);
-}
-
-// aggregates [I0, I1) of a level: the arithmetic of k_presmooth_restrict
+// row groups [g0, g1) of S: the arithmetic of k_rows with OpRestrict<T>
 template <typename T, int LPR>
-__device__ void tail_presmooth(const TailLevel<T>& L, bool first, int I0, int I1, T* part) {
-  constexpr int MPB = 256 / LPR;
-  const int slot = threadIdx.x / LPR, lane = threadIdx.x & (LPR - 1);
-  for (int I = I0; I < I1; ++I) {
-    const int s = L.agg_ptr[I], e = L.agg_ptr[I + 1];
-    T acc = T(0);
-    for (int base = s; base < e; base += MPB) {
-      const int k = base + slot;
-      T sum = T(0);
-      int i = -1;
-      if (k < e) {
-        i = L.agg_rows[k];
-        const int r0 = L.rp[i], r1 = L.rp[i + 1];
-        for (int x = r0 + lane; x < r1; x += LPR) {
-          const int j = L.ci[x];
-          sum += L.av[x] * (L.wd[j] * tail_ldb(L.b + j, first));
-        }
-      }
-      sum = group_sum<LPR>(sum);
-      if (lane == 0 && k < e) {
-        const T bi = tail_ldb(L.b + i, first), wi = L.wd[i], ri = bi - sum;
-        L.xt[i] = two_steps(wi, bi, ri);
-        part[slot] = L.rv[k] * ri;
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        const int m = min(MPB, e - base);
-        for (int q = 0; q < m; ++q) acc += part[q];
-      }
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) L.rc[I] = acc;
-  }
-}
-
-// row groups [g0, g1) of a level: the arithmetic of k_rows with OpPostT<T,
-// CoarseV<T>> (x_out = y + T c)
-template <typename T, int LPR>
-__device__ void tail_postsmooth(const TailLevel<T>& L, int g0, int g1) {
+__device__ void tail_down(const TailLevel<T>& L, int g0, int g1) {
   constexpr int RPB = 256 / LPR;
   const int lane = threadIdx.x & (LPR - 1);
   for (int g = g0; g < g1; ++g) {
     const int row = g * RPB + threadIdx.x / LPR;
     T sum = T(0);
-    if (row < L.n) {
-      const int s = L.tp[row], e = L.tp[row + 1];
+    if (row < L.nc) {
+      const int s = L.sp[row], e = L.sp[row + 1];
       for (int k0 = s + lane; k0 < e; k0 += 4 * LPR) {
         int c[4];
         T v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int k = k0 + q * LPR;
-          c[q] = k < e ? L.tc[k] : 0;
-          v[q] = k < e ? L.tv[k] : T(0);
+          c[q] = k < e ? L.sc[k] : 0;
+          v[q] = k < e ? L.sv[k] : T(0);
         }
         T xv[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) xv[q] = k0 + q * LPR < e ? tail_ld(L.c + c[q]) : T(0);
+        for (int q = 0; q < 4; ++q) xv[q] = k0 + q * LPR < e ? L.b[c[q]] : T(0);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           if (k0 + q * LPR < e) sum += v[q] * xv[q];
       }
     }
     sum = group_sum<LPR>(sum);
-    if (row < L.n && lane == 0) L.xo[row] = tail_ld(L.xt + row) + sum;
+    if (row < L.nc && lane == 0) L.rc[row] = sum;
   }
+}
+
+// row groups [g0, g1) of the post-smoothing: the arithmetic of k_post_both
+template <typename T, int LPR>
+__device__ void tail_up(const TailLevel<T>& L, int g0, int g1) {
+  constexpr int RPB = 256 / LPR;
+  const int lane = threadIdx.x & (LPR - 1);
+  for (int g = g0; g < g1; ++g) {
+    const int row = g * RPB + threadIdx.x / LPR;
+    T ax = T(0), te = T(0), bi = T(0), wi = T(0);
+    if (row < L.n) {
+      bi = L.b[row];
+      wi = L.wd[row];
+      both_sums<T, LPR>(row, lane, L.rp, L.ci, L.av, L.tp, L.tc, L.tv, [&](int j) { return L.wd[j] * L.b[j]; },
+                        [&](int J) { return L.c[J]; }, ax, te);
+    }
+    ax = group_sum<LPR>(ax);
+    te = group_sum<LPR>(te);
+    if (row < L.n && lane == 0) L.xo[row] = two_steps(wi, bi, bi - ax) + te;
+  }
+}
+
+template <class F>
+__device__ __forceinline__ void tail_lanes(int lpr, F f) {
+  if (lpr == 2) f(std::integral_constant<int, 2>());
+  else if (lpr == 4) f(std::integral_constant<int, 4>());
+  else if (lpr == 8) f(std::integral_constant<int, 8>());
+  else if (lpr == 16) f(std::integral_constant<int, 16>());
+  else if (lpr == 32) f(std::integral_constant<int, 32>());
+  else f(std::integral_constant<int, 64>());
 }
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_vtail(TailArgs<T> a, Act act) {
   if (!act.on()) return;
   __shared__ int s_item;
-  __shared__ T part[32];
+  __shared__ T red[kBlock / kWave];
   const int total = a.start[a.nphase];
   int ready = 0;   // leading phases known to be complete
   while (true) {
@@ -1216,32 +1260,36 @@ __global__ void __launch_bounds__(256) k_vtail(TailArgs<T> a, Act act) {
       ready = p;
     }
     const int it = t - a.start[p];
-    if (p < a.nlev) {                       // pre-smoothing + restriction, down
-      const TailLevel<T>& L = a.lv[p];
-      const int I0 = it * kTailAggPerItem, I1 = min(L.nc, I0 + kTailAggPerItem);
-      if (L.lpr == 8) tail_presmooth<T, 8>(L, p == 0, I0, I1, part);
-      else if (L.lpr == 16) tail_presmooth<T, 16>(L, p == 0, I0, I1, part);
-      else tail_presmooth<T, 32>(L, p == 0, I0, I1, part);
-    } else if (p == a.nlev) {               // coarse product, one wave per row
-      const TailLevel<T>& L = a.lv[a.nlev - 1];
+    const TailLevel<T>& L = a.lv[a.level[p]];
+    if (a.kind[p] == kTailDown) {
+      tail_lanes(L.slpr, [&](auto l) {
+        constexpr int LPR = decltype(l)::value;
+        const int groups = (L.nc + 256 / LPR - 1) / (256 / LPR);
+        tail_down<T, LPR>(L, it * kTailGroupsPerItem, min(groups, (it + 1) * kTailGroupsPerItem));
+      });
+    } else if (a.kind[p] == kTailDense) {
+      for (int row = it * kTailDenseRows; row < min(a.dense_rows, (it + 1) * kTailDenseRows); ++row) {
+        const T s = dense_row(a.dense_n, a.dense + (size_t)row * a.dense_ld, a.dense_b, red);
+        if (threadIdx.x == 0) a.dense_x[row] = s;
+        __syncthreads();   // red is written again
+      }
+    } else if (a.kind[p] == kTailCoarse) {   // one wave per row
       const int n = a.ncoarse;
       const int row = it * (kBlock / kWave) + threadIdx.x / kWave;
       const int lane = threadIdx.x & (kWave - 1);
       T s = T(0);
       if (row < n) {
         const T* Ar = a.cinv + (size_t)row * n;
-        for (int j = lane; j < n; j += kWave) s += Ar[j] * tail_ld(L.rc + j);
+        for (int j = lane; j < n; j += kWave) s += Ar[j] * L.rc[j];
       }
       s = wave_sum(s);
       if (row < n && lane == 0) L.c[row] = s;
-    } else {                                // residual + post-smoothing + prolongation, up
-      const int q = a.nlev - 1 - (p - a.nlev - 1);
-      const TailLevel<T>& L = a.lv[q];
-      const int rpb = 256 / L.tlpr;
-      const int groups = (L.n + rpb - 1) / rpb;
-      const int g0 = it * kTailGroupsPerItem, g1 = min(groups, g0 + kTailGroupsPerItem);
-      if (L.tlpr == 4) tail_postsmooth<T, 4>(L, g0, g1);
-      else tail_postsmooth<T, 8>(L, g0, g1);
+    } else {
+      tail_lanes(L.lpr, [&](auto l) {
+        constexpr int LPR = decltype(l)::value;
+        const int groups = (L.n + 256 / LPR - 1) / (256 / LPR);
+        tail_up<T, LPR>(L, it * kTailGroupsPerItem, min(groups, (it + 1) * kTailGroupsPerItem));
+      });
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1259,25 +1307,13 @@ __global__ void __launch_bounds__(256) k_vtail(TailArgs<T> a, Act act) {
 }
 
 // The first level of the tail (h.L() when there is none): from there down
-// every level is a V-cycle level on the fused small-level path with 8, 16 or
-// 32 lanes per row and the Jacobi (plain or learned) smoother.
-template <typename T>
+// every level is a V-cycle level that holds S and T (Level::sp).
 int tail_first(const Hierarchy& h) {
   const int L = h.L();
-  if (L == 0 || h.nsys > 0 || !(h.opt.flags & AMG_FLAG_PERSISTENT_TAIL) || h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV ||
-      h.opt.smoother == AMG_SMOOTHER_MCSGS || !h.d_tail)
-    return L;
+  if (L == 0 || h.nsys > 0 || !(h.opt.flags & AMG_FLAG_PERSISTENT_TAIL) || !h.d_tail) return L;
   int k0 = L;
-  while (k0 - 1 >= 1 && k0 - 1 >= h.opt.kcycle_levels) {
-    const Level& lv = h.levels[k0 - 1];
-    const int lpr = tune_of<T>(lv).lpr;
-    if (lv.n > kFuseCorrectionRows || (lpr != 8 && lpr != 16 && lpr != 32) || !lv.tp ||
-        (lv.tlpr != 4 && lv.tlpr != 8))
-      break;
-    --k0;
-  }
-  if (L - k0 > kTailMax) k0 = L - kTailMax;
-  return k0;
+  while (k0 - 1 >= 1 && k0 - 1 >= h.opt.kcycle_levels && h.levels[k0 - 1].sp) --k0;
+  return std::max(k0, L - kTailMax);
 }
 
 // cycle(k0) below the K-cycle as one launch; false when level k0 does not
@@ -1285,45 +1321,63 @@ int tail_first(const Hierarchy& h) {
 template <typename T>
 bool vtail(Hierarchy& h, int k0, const T* b, T* xo, const int* act) {
   const int L = h.L();
-  if (k0 >= L || tail_first<T>(h) != k0) return false;
+  if (k0 >= L || tail_first(h) != k0) return false;
   TailArgs<T> a{};
-  a.nlev = L - k0;
+  const int nlev = L - k0;
   a.ncoarse = h.levels[L].n;
   a.cinv = cinv<T>(h);
   a.ctl = h.d_tail;
   a.err = h.d_err;
   int items = 0, p = 0;
-  auto phase = [&](int n_items) { a.start[p++] = items; items += n_items; };
-  for (int q = 0; q < a.nlev; ++q) {
+  auto phase = [&](TailKind kind, int level, int work, int per) {
+    a.kind[p] = kind;
+    a.level[p] = level;
+    a.start[p++] = items;
+    items += (work + per - 1) / per;
+  };
+  auto groups = [](int rows, int lpr) { return (rows + 256 / lpr - 1) / (256 / lpr); };
+  auto dense = [&](int level, const T* op, int rows, int n, int ld, const T* rhs, T* x) {
+    a.dense = op;
+    a.dense_rows = rows;
+    a.dense_n = n;
+    a.dense_ld = ld;
+    a.dense_b = rhs;
+    a.dense_x = x;
+    phase(kTailDense, level, rows, kTailDenseRows);
+  };
+  int up = nlev;   // levels with a post-smoothing of their own
+  for (int q = 0; q < nlev; ++q) {
     const Level& lv = h.levels[k0 + q];
     TailLevel<T>& t = a.lv[q];
     t.n = lv.n;
     t.nc = lv.nc;
-    t.lpr = tune_of<T>(lv).lpr;
+    t.slpr = lv.slpr;
+    t.lpr = std::min(pick_lpr(lv.n, lv.nnz), 32);   // with_lanes
     t.rp = lv.rp;
     t.ci = lv.ci;
     t.av = vals<T>(lv);
-    t.agg_ptr = lv.agg_ptr;
-    t.agg_rows = lv.agg_rows;
-    t.rv = rvals<T>(lv);
+    t.sp = lv.sp;
+    t.sc = lv.sc;
+    t.sv = svals<T>(lv);
     t.tp = lv.tp;
     t.tc = lv.tc;
     t.tv = tvals<T>(lv);
-    t.tlpr = lv.tlpr;
     t.wd = wdinv<T>(lv);
     t.b = q == 0 ? b : static_cast<const T*>(h.levels[k0 + q - 1].rc);
-    t.xt = static_cast<T*>(lv.xt);
     t.rc = static_cast<T*>(lv.rc);
     t.c = static_cast<T*>(lv.c);
     t.xo = q == 0 ? xo : static_cast<T*>(h.levels[k0 + q - 1].c);
-    phase((lv.nc + kTailAggPerItem - 1) / kTailAggPerItem);
+    if (lv.mld) {
+      dense(q, mop<T>(lv), lv.n, lv.n, lv.mld, t.b, t.xo);
+      up = q;
+    } else if (lv.gld) {
+      dense(q, gop<T>(lv), lv.nc, lv.n, lv.gld, t.b, t.c);
+    } else {
+      phase(kTailDown, q, groups(lv.nc, t.slpr), kTailGroupsPerItem);
+      if (q == nlev - 1) phase(kTailCoarse, q, a.ncoarse, kBlock / kWave);
+    }
   }
-  phase((a.ncoarse + kBlock / kWave - 1) / (kBlock / kWave));
-  for (int q = a.nlev - 1; q >= 0; --q) {
-    const int rpb = 256 / a.lv[q].tlpr;
-    const int groups = (a.lv[q].n + rpb - 1) / rpb;
-    phase((groups + kTailGroupsPerItem - 1) / kTailGroupsPerItem);
-  }
+  for (int q = up - 1; q >= 0; --q) phase(kTailUp, q, groups(a.lv[q].n, a.lv[q].lpr), kTailGroupsPerItem);
   a.nphase = p;
   a.start[p] = items;
   const int grid = std::min(kTailGrid, items);
@@ -1524,30 +1578,11 @@ __global__ void __launch_bounds__(kBlock) k_post_both(int n, const int* __restri
     T ax = T(0), te = T(0), bi = T(0), wi = T(0);
     double qi = 0.0;
     if (row < n) {
-      const int s = rp[row], e = rp[row + 1], ts = tp[row], t1 = tp[row + 1];
       bi = op.b[row];
       wi = op.wd[row];
       if constexpr (Op::NV > 0) qi = op.q[row];
-      const int kt = ts + lane;
-      const int ct = kt < t1 ? tc[kt] : -1;
-      const T vt = kt < t1 ? tv[kt] : T(0);
-      for (int k0 = s + lane; k0 < e; k0 += 4 * LPR) {
-        int c[4];
-        T v[4], x[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = k0 + q * LPR;
-          c[q] = k < e ? ci[k] : row;
-          v[q] = k < e ? av[k] : T(0);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = k0 + q * LPR < e ? op.x(c[q]) : T(0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (k0 + q * LPR < e) ax += v[q] * x[q];
-      }
-      if (ct >= 0) te = vt * op.e.at(ct);
-      for (int k = kt + LPR; k < t1; k += LPR) te += tv[k] * op.e.at(tc[k]);
+      both_sums<T, LPR>(row, lane, rp, ci, av, tp, tc, tv, [&](int jc) { return op.x(jc); },
+                        [&](int J) { return op.e.at(J); }, ax, te);
     }
     ax = group_sum<LPR>(ax);
     te = group_sum<LPR>(te);
@@ -1582,30 +1617,6 @@ void post_both(Hierarchy& h, const Level& lv, Act A, const T* b, const T* wd, co
   else go(OpPostBoth<T, Coarse, false, false>{A, b, wd, nullptr, xo, e, nullptr, nullptr});
 }
 
-// y = A x for a dense operator of padded rows (16-byte loads; the pad is
-// zero and x is not read there), a block per row.  Bound by reading A where the
-// L2s do not hold it.  779 rows 4.2 us, 1,545 rows 5.4, for three launches of
-// 13.9 us; 244 rows of 2,321 entries 2.9.
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_dense_apply(int n, int ld, const T* __restrict__ A,
-                                                        const T* __restrict__ x, T* __restrict__ y, Act a) {
-  if (!a.on()) return;
-  constexpr int V = 16 / sizeof(T);
-  typedef T Pack __attribute__((ext_vector_type(V)));
-  __shared__ T red[kBlock / kWave];
-  const T* row = A + (size_t)blockIdx.x * ld;
-  T s = T(0);
-#pragma unroll 4
-  for (int j = V * threadIdx.x; j < n; j += V * kBlock) {
-    const Pack m = *reinterpret_cast<const Pack*>(row + j);
-#pragma unroll
-    for (int q = 0; q < V; ++q) s += m[q] * x[min(j + q, n - 1)];
-  }
-  s = wave_sum(s);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) y[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
 
 
 // Whether cycle(k) pre-smooths with the row kernel of its level from a zero
