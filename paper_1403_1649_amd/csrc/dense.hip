@@ -417,45 +417,107 @@ __global__ void k_dense_scatter_batched(const TermInfo* __restrict__ ti, const i
 // panel, into a second buffer (the two swap), so nothing is read after it was
 // written and no launch stands between pivot block and update.  The products
 // are FP64 matrix-core steps (each wave one 16 x 16 quarter); the pivot block
-// is inverted by one wave in registers, by every workgroup for itself.  These
+// is inverted by one wave, by every workgroup for itself.  These
 // matrices are small: what bounds the inversion is the chain of panels.  244
 // unknowns: 8 panels of 50 us when pivot block (a workgroup with two barriers
 // per step), its product, and two updates were four launches.
 constexpr int kB = 32;
 
-// In-place Gauss-Jordan inverse of a 32 x 32 block held by a wave: lane l has
-// row l % 32, columns 16 (l / 32) .. + 15.  Returns whether every pivot was
-// positive and finite.
-__device__ __forceinline__ bool invert_block(double (&a)[16], int lane) {
-  const int row = lane & 31, half = lane >> 5;
+// orders a wave's own LDS writes before its lanes' later reads
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// In-place Gauss-Jordan inverse of a 16 x 16 block held by a wave in the layout
+// of a matrix-core result (lane l: column l % 16, rows l / 16 + 4 i).  Returns
+// whether every pivot was positive and finite.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int2 w = __builtin_bit_cast(int2, v);
+  return __builtin_bit_cast(double, int2{__builtin_amdgcn_readlane(w.x, lane), __builtin_amdgcn_readlane(w.y, lane)});
+}
+__device__ __forceinline__ bool invert16(f64x4& a, int lane) {
+  const int col = lane & 15, g = lane >> 4;
   bool ok = true;
 #pragma unroll
-  for (int j = 0; j < kB; ++j) {
-    const int oh = j / 16;   // the half that holds column j
-    const double c = __shfl(a[j % 16], row + 32 * oh, kWave);
-    const double p = __shfl(c, j, kWave);
+  for (int j = 0; j < 16; ++j) {
+    const int ji = j / 4, jg = j % 4;
+    const double p = lane_value(a[ji], 16 * jg + j);
+    const double rj = __shfl(a[ji], 16 * jg + col, kWave);
+    double c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] = __shfl(a[i], 16 * g + j, kWave);
     ok = ok && p > 0.0 && p < INFINITY;
     const double inv = 1.0 / p;
+    const bool here = col == j;
+    const double rk = here ? inv : rj * inv;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const double rk = __shfl(a[q], j + 32 * half, kWave) * inv;
-      a[q] = row == j ? rk : a[q] - c * rk;
+    for (int i = 0; i < 4; ++i) {
+      const double t = __builtin_fma(-c[i], rk, here ? 0.0 : a[i]);
+      a[i] = i == ji && g == jg ? rk : t;
     }
-    if (half == oh) a[j % 16] = row == j ? inv : -c * inv;
   }
   return ok;
 }
 
-// the pivot block of panel K: rows and columns c0 .. c0 + w - 1, identity beyond
+// The inverse of the pivot block of panel K (rows and columns c0 .. c0 + w - 1,
+// identity beyond) into sM by one wave: the leading 16 x 16 block, its Schur
+// complement and that one's inverse, the products on the matrix cores.  The
+// chain of 32 pivots bounds it; holding all 32 columns of a row in two lanes
+// took 15 us of a panel's 20; a panel now takes 13.5 (244 unknowns).
+struct PivotScratch {
+  double p[16][17], q[16][17];
+};
 __device__ __forceinline__ bool load_and_invert(const double* __restrict__ A, int n, int c0, int w, int lane,
-                                                double (&a)[16]) {
-  const int row = lane & 31, col0 = 16 * (lane >> 5);
+                                                double (*sM)[kB + 1], PivotScratch& z) {
+  const int col = lane & 15, g = lane >> 4;
+  f64x4 a, d;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int col = col0 + q;
-    a[q] = row < w && col < w ? A[(size_t)(c0 + row) * n + c0 + col] : (row == col ? 1.0 : 0.0);
+  for (int t = 0; t < 16; ++t) {
+    const int i = 2 * t + (lane >> 5), j = lane & 31;
+    sM[i][j] = i < w && j < w ? A[(size_t)(c0 + i) * n + c0 + j] : (i == j ? 1.0 : 0.0);
   }
-  return invert_block(a, lane);
+  wave_order();
+  // X Y for 16 x 16 operands in LDS, added to u
+  auto product = [&](auto x, auto y, f64x4 u, double sign) {
+#pragma unroll
+    for (int k = 0; k < 16; k += 4) u = mfma_f64_16x16x4(sign * x(col, k + g), y(k + g, col), u);
+    return u;
+  };
+  auto block = [&](int r, int c) { return [=](int i, int j) { return sM[r + i][c + j]; }; };
+  auto zp = [&](int i, int j) { return z.p[i][j]; };
+  auto zq = [&](int i, int j) { return z.q[i][j]; };
+  auto put = [&](auto&& at, const f64x4& u) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at(mfma_row(lane, i), mfma_col(lane)) = u[i];
+  };
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    a[i] = sM[mfma_row(lane, i)][col];
+    d[i] = sM[16 + mfma_row(lane, i)][16 + col];
+  }
+  bool ok = invert16(a, lane);
+  put([&](int i, int j) -> double& { return sM[i][j]; }, a);   // M11 of the leading block
+  wave_order();
+  put([&](int i, int j) -> double& { return z.p[i][j]; }, product(block(16, 0), block(0, 0), zero, 1.0));   // A21 M11
+  put([&](int i, int j) -> double& { return z.q[i][j]; }, product(block(0, 0), block(0, 16), zero, 1.0));   // M11 A12
+  wave_order();
+  d = product(zp, block(0, 16), d, -1.0);   // A22 - A21 M11 A12
+  ok = invert16(d, lane) && ok;
+  wave_order();
+  put([&](int i, int j) -> double& { return sM[16 + i][16 + j]; }, d);
+  wave_order();
+  const f64x4 m12 = product(zq, block(16, 16), zero, -1.0);
+  const f64x4 m21 = product(block(16, 16), zp, zero, -1.0);
+  put([&](int i, int j) -> double& { return sM[i][16 + j]; }, m12);
+  put([&](int i, int j) -> double& { return sM[16 + i][j]; }, m21);
+  wave_order();
+  a = product(block(0, 16), zp, a, -1.0);   // M11 + M11 A12 M22 A21 M11
+  put([&](int i, int j) -> double& { return sM[i][j]; }, a);
+  wave_order();
+  return ok;
 }
 
 // Buffer that holds system t before panel K: the swap ends in `inv`.
@@ -485,13 +547,12 @@ __global__ void __launch_bounds__(kWave) k_gji_pivot(const TermInfo* __restrict_
   const TermInfo t = ti[blockIdx.x];
   const int c0 = K * kB;
   if (c0 >= t.n) return;
-  double a[16];
+  __shared__ double sM[kB][kB + 1];
+  __shared__ PivotScratch z;
   const int lane = threadIdx.x;
   const double* A = (source_is_inv(t.n, K) ? inv : work) + t.off;
-  if (!load_and_invert(A, t.n, c0, min(kB, t.n - c0), lane, a) && lane == 0) atomic_or_flag(err, kErrNotSPD);
-#pragma unroll
-  for (int q = 0; q < 16; ++q)
-    mbuf[(size_t)blockIdx.x * kB * kB + (lane & 31) * kB + 16 * (lane >> 5) + q] = a[q];
+  if (!load_and_invert(A, t.n, c0, min(kB, t.n - c0), lane, sM, z) && lane == 0) atomic_or_flag(err, kErrNotSPD);
+  for (int e = lane; e < kB * kB; e += kWave) mbuf[(size_t)blockIdx.x * kB * kB + e] = sM[e / kB][e % kB];
 }
 
 template <bool PIVOT>   // the workgroup inverts the pivot block itself (else mbuf)
@@ -510,11 +571,9 @@ __global__ void __launch_bounds__(256) k_gji_panel(const TermInfo* __restrict__ 
   const bool pr = r0 == c0, pc = q0 == c0;   // in the pivot rows / columns
   const int tid = threadIdx.x, wv = tid / kWave, l = tid & (kWave - 1);
   if constexpr (PIVOT) {
+    __shared__ PivotScratch z;
     if (wv == 0) {
-      double a[16];
-      const bool ok = load_and_invert(A, n, c0, w, l, a);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) sM[l & 31][16 * (l >> 5) + q] = a[q];
+      const bool ok = load_and_invert(A, n, c0, w, l, sM, z);
       if (pr && pc && !ok && l == 0) atomic_or_flag(err, kErrNotSPD);
     }
   } else {
