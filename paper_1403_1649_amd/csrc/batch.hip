@@ -133,10 +133,10 @@ __global__ void __launch_bounds__(kFinThreads) k_bfinal(Op op, const double* __r
     }
     double v[NV];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      double t = 0.0;
-      for (int b = blk_sys[s] + threadIdx.x; b < blk_sys[s + 1]; b += kFinThreads) t += part[(size_t)k * nb + b];
-      v[k] = t;
+    for (int k = 0; k < NV; ++k) v[k] = 0.0;
+    for (int b = blk_sys[s] + threadIdx.x; b < blk_sys[s + 1]; b += kFinThreads) {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) v[k] += part[(size_t)k * nb + b];
     }
     block_sum<NV>(v, red);
     if (threadIdx.x == 0) op.finalize(s, v);

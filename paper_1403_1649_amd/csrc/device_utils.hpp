@@ -66,11 +66,12 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* red) {
     for (int k = 0; k < NV; ++k) red[k * nw + wid] = v[k];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (wid == 0) {   // a lane per wave, at most 16
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      double s = 0.0;
-      for (int w = 0; w < nw; ++w) s += red[k * nw + w];
+      double s = lane < nw ? red[k * nw + lane] : 0.0;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
       v[k] = s;
     }
   }

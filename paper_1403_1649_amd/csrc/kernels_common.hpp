@@ -61,20 +61,24 @@ __device__ __forceinline__ void write_partials(double (&acc)[NV], RedCtx rc, con
 
 // The one-block finalize reads the partials with 1024 threads (2048 blocks x
 // up to 3 values: a few loads per thread): on the 128^3 Poisson solve, 15
-// finalizes per iteration, 9.51 -> 9.25 ms against 256 threads.
+// finalizes per iteration, 9.51 -> 9.25 ms against 256 threads.  Five values of
+// 2048 blocks: 7.1 us when each value's loads waited for the last one's, 5.6.
 constexpr int kFinBlock = 1024;
 template <class Op>
 __global__ void __launch_bounds__(kFinBlock) k_finalize(Op op, const double* __restrict__ part, int nb) {
   if (!op.active()) return;
   constexpr int NV = Op::NV;
   __shared__ double red[NV * (kFinBlock / kWave)];
-  double v[NV];
+  static_assert(kMaxPartialBlocks <= 2 * kFinBlock, "two loads per thread and value");
+  double v[NV], w[NV];   // all loads in flight together
+  const int b0 = threadIdx.x, b1 = b0 + kFinBlock;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kFinBlock) s += part[k * nb + b];
-    v[k] = s;
+    v[k] = b0 < nb ? part[k * nb + b0] : 0.0;
+    w[k] = b1 < nb ? part[k * nb + b1] : 0.0;
   }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] += w[k];
   block_sum<NV>(v, red);
   if (threadIdx.x == 0) op.finalize(v);
 }
