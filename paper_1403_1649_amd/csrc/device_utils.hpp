@@ -43,6 +43,26 @@ __device__ __forceinline__ int wave_sum_int(int v) {
   return v;
 }
 
+// Minimum over a group of G = 16, 32 or 64 lanes, valid in every lane: rotations
+// within a row of 16 lanes (no LDS round trip as a shuffle takes), then the rows.
+template <int G>
+__device__ __forceinline__ int group_min_int(int v) {
+  static_assert(G == 16 || G == 32 || G == 64, "whole rows of 16 lanes");
+  auto step = [&](int o) { v = o < v ? o : v; };
+  step(__builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false));   // row_ror:8
+  step(__builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false));
+  step(__builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false));
+  if constexpr (G == 32) step(__shfl_xor(v, 16, kWave));
+  if constexpr (G == 64) {
+    const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
+    const int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+    const int e = a < b ? a : b, f = c < d ? c : d;
+    return e < f ? e : f;
+  }
+  return v;
+}
+
 // Sum over a sub-group of G consecutive lanes (G a power of two <= 64);
 // the result is valid in every lane of the group.
 template <int G, typename T>

@@ -6,19 +6,17 @@
 //      (aggregate by aggregate, members ascending, entries in column order),
 //      are numbered by a scan of the row lengths;
 //   2. the terms: every entry (i, j) of a member row is the term
-//      (J = agg(j), (P_iI a_ij) P_jJ) with its number in segment order; the
-//      first reduce pass forms the terms of its rows itself, from A, and
-//      writes those of wider rows to their numbered places;
-//   3. reduce: one wave per coarse row holds the row's terms in registers,
-//      finds the distinct J with an LDS hash, places every term after the
-//      earlier terms of the same J (ballot peeling within a chunk of 64), and
-//      sums each J's terms in segment order; the sorted (J, sum) pairs
-//      overwrite the head of the row's term range;
+//      (J = agg(j), (P_iI a_ij) P_jJ) with its number in segment order; a wave
+//      per coarse row stages its row's terms in LDS;
+//   3. reduce: the wave takes the distinct J in ascending order (its smallest J
+//      above the last one, from registers), then a lane per J sums that J's
+//      terms in segment order; the (J, sum) pairs go to the head of the row's
+//      term range;
 //   4. a scan of the distinct counts makes the row pointers and a copy
 //      compacts the rows.
 // Each coarse entry is the sum of its terms in segment order, so the result
-// does not depend on timing.  Rows with more terms than a wave holds go to a
-// wider wave, and the rare rows beyond that to a block-per-row extraction.
+// does not depend on timing.  Rows with more terms than the first pass holds go
+// to a wider one, and the rare rows beyond that to a block-per-row extraction.
 #include <climits>
 
 #include "amg_internal.hpp"
@@ -28,8 +26,9 @@ namespace amg {
 
 namespace {
 constexpr int kBig = 256;        // threads per block on the extraction path
-constexpr int kSmallC = 2;       // terms per lane of the first reduce pass
-constexpr int kWideC = 8;        // terms per lane of the second
+constexpr int kGalWaves = 2;     // waves per block of the reduce passes
+constexpr int kSmallC = 8;       // terms per lane of the first reduce pass (16 to 64 lanes a row, by the average)
+constexpr int kWideC = 16;       // terms per lane of the second, a wave per row
 constexpr int kMaxWaveTerms = kWave * kWideC;
 
 // Step 1: number of terms of the k-th fine row in segment order (0 beyond the
@@ -56,166 +55,140 @@ struct GalFine {
   const int* agg_rows;
 };
 
-// Step 3 for rows of at most 64*C terms, one wave per row (HS hash slots).
-// Rows with more terms are appended to out_list.  DIRECT: the wave forms its
-// row's terms itself from A (term t of the row: the member k whose term range
-// holds t, found by binary search over the members' offsets staged in LDS,
-// then its entry), instead of reading them from an expand pass; a row with
-// more terms writes its terms to its range for the wider passes.  The terms,
-// their order and their sums are those of the expand pass.
-template <int C, bool LISTED, bool DIRECT = false>
-__global__ void __launch_bounds__(kWave) k_gal_reduce(int nc, const int* __restrict__ agg_ptr,
-                                                      const int* __restrict__ toff, int* __restrict__ tkey,
-                                                      double* __restrict__ tval, int* __restrict__ ucount,
-                                                      const int* __restrict__ in_list,
-                                                      const int* __restrict__ in_count, int* __restrict__ out_list,
-                                                      int* __restrict__ out_count, GalFine fine) {
-  constexpr int CAP = kWave * C;
-  constexpr int HS = CAP;   // U <= CAP, so linear probing always ends
-  constexpr int HB = C == 1 ? 6 : C == 2 ? 7 : C == 4 ? 8 : C == 8 ? 9 : 10;
-  static_assert((1 << HB) == HS, "C must be a power of two up to 16");
-  __shared__ int hkey[HS], hcnt[HS], hrun[HS], hrank[HS];
-  __shared__ int ukey[CAP], skey[CAP], sbase[CAP + 1];
-  __shared__ double sv[CAP];
-  __shared__ int moff[DIRECT ? CAP + 1 : 1];
-  const int lane = threadIdx.x;
-  const uint64_t below = (1ull << lane) - 1;
-  const int count = LISTED ? *in_count : nc;
-  for (int idx = xcd_block_index(); idx < count; idx += gridDim.x) {
-    const int I = LISTED ? in_list[idx] : idx;
-    const int m0 = agg_ptr[I], m1 = agg_ptr[I + 1];
-    const int t0 = toff[m0];
-    const int T = toff[m1] - t0;
-    // term t (0 <= t < T, segment order) of a direct row: (J, (P_i a_ij) P_j)
-    auto term = [&](int t, int& Jt, double& Vt) {
-      int lo = 0, hi = m1 - m0 - 1;   // the last member whose range starts at or before t
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (moff[mid] <= t) lo = mid;
-        else hi = mid - 1;
-      }
-      const int i = fine.agg_rows[m0 + lo];
-      const int x = fine.rp[i] + (t - moff[lo]);
-      const int j = fine.ci[x];
-      Jt = fine.agg[j];
-      Vt = __dmul_rn(__dmul_rn(fine.pval[i], fine.val[x]), fine.pval[j]);
-    };
-    if (DIRECT) {   // the members' term offsets, relative to the row
-      if (T > CAP) {
-        // a wide row: its members may exceed the LDS stage; expand by member
-        for (int k = m0; k < m1; ++k) {
-          const int i = fine.agg_rows[k];
-          const int s0 = fine.rp[i], o = toff[k] - s0;
-          const double pi = fine.pval[i];
-          for (int x = s0 + lane; x < fine.rp[i + 1]; x += kWave) {
-            const int j = fine.ci[x];
-            tkey[o + x] = fine.agg[j];
-            tval[o + x] = __dmul_rn(__dmul_rn(pi, fine.val[x]), fine.pval[j]);
+// Steps 2 and 3 for rows of at most G C terms, G lanes per row.  Rows with more
+// are appended to out_list; LAST (the wide pass) writes their terms to their
+// ranges for the extraction path.  Bound by instruction issue (taking the
+// distinct J one by one, and a lane per J walking all terms), which is why
+// short rows share a wave, and by the chain row pointers
+// -> entries -> aggregates, which four steps of members share.  Level 0 of 160^3
+// 663 -> 456 us, of 128^3 338 -> 242, of 64 2-D systems (5.7 M rows) 866 -> 481,
+// against a wave per row with a hash table of its J, a rank and a scan.
+template <int G, int C, bool LAST>
+__global__ void __launch_bounds__(kGalWaves * kWave) k_gal_rows(int nc, const int* __restrict__ agg_ptr,
+                                                                const int* __restrict__ toff, int* __restrict__ tkey,
+                                                                double* __restrict__ tval, int* __restrict__ ucount,
+                                                                const int* __restrict__ in_list,
+                                                                const int* __restrict__ in_count,
+                                                                int* __restrict__ out_list,
+                                                                int* __restrict__ out_count, GalFine fine) {
+  constexpr int CAP = G * C, R = kWave / G * kGalWaves;   // terms and rows held
+  constexpr int P = CAP + 1;                               // rows start in different LDS banks
+  __shared__ int s_key[R][P];
+  __shared__ double s_v[R][P];
+  __shared__ int s_u[R][P];
+  const int lane = threadIdx.x & (G - 1), grp = threadIdx.x / G;
+  const int part = lane >> 3, l8 = lane & 7;
+  int* key = s_key[grp];
+  double* val = s_v[grp];
+  int* uniq = s_u[grp];
+  auto wave_order = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  const int count = LAST ? *in_count : nc;
+  const long first = (long)xcd_block_index() * R;
+  for (long base = first; base < count; base += (long)gridDim.x * R) {   // the same for the whole wave
+    const bool mine_on = base + grp < count;
+    const int I = !mine_on ? 0 : LAST ? in_list[base + grp] : (int)(base + grp);
+    const int m0 = mine_on ? agg_ptr[I] : 0, m1 = mine_on ? agg_ptr[I + 1] : 0;
+    const int t0 = mine_on ? toff[m0] : 0;
+    int T = mine_on ? toff[m1] - t0 : 0;
+    const bool fits = T <= CAP;
+    if (!fits && lane == 0) out_list[atomicAdd(out_count, 1)] = I;
+    if (fits || LAST) {
+      // G / 8 members at a time, eight lanes each
+      for (int mb = m0; mb < m1; mb += G) {
+        const int q = mb + lane;
+        int beg = 0, len = 0, off = 0;
+        double pi = 0.0;
+        if (q < m1) {
+          const int i = fine.agg_rows[q];
+          beg = fine.rp[i];
+          len = fine.rp[i + 1] - beg;
+          off = toff[q] - t0;
+          pi = fine.pval[i];
+        }
+        const int cnt = min(G, m1 - mb);
+        // four steps' first entries are loaded before any is used
+        for (int sub = 0; sub < cnt; sub += G / 2) {
+          int b[4], n[4], o[4], j[4];
+          double p[4], a[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            const int src = min(sub + x * (G / 8) + part, G - 1);
+            const bool in = sub + x * (G / 8) + part < cnt;   // past cnt: a lane with no entries
+            b[x] = __shfl(beg, src, G);
+            n[x] = __shfl(len, src, G);
+            n[x] = in ? n[x] : 0;
+            o[x] = __shfl(off, src, G);
+            p[x] = __shfl(pi, src, G);
+          }
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            j[x] = l8 < n[x] ? fine.ci[b[x] + l8] : -1;
+            a[x] = l8 < n[x] ? fine.val[b[x] + l8] : 0.0;
+          }
+          int J[4];
+          double pj[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            J[x] = j[x] >= 0 ? fine.agg[j[x]] : 0;
+            pj[x] = j[x] >= 0 ? fine.pval[j[x]] : 0.0;
+          }
+          auto put = [&](int at, int Jt, double v) {
+            if (fits) {
+              key[at] = Jt;
+              val[at] = v;
+            } else {
+              tkey[t0 + at] = Jt;
+              tval[t0 + at] = v;
+            }
+          };
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            if (j[x] >= 0) put(o[x] + l8, J[x], __dmul_rn(__dmul_rn(p[x], a[x]), pj[x]));
+            for (int k = l8 + 8; k < n[x]; k += 8) {
+              const int jk = fine.ci[b[x] + k];
+              put(o[x] + k, fine.agg[jk], __dmul_rn(__dmul_rn(p[x], fine.val[b[x] + k]), fine.pval[jk]));
+            }
           }
         }
-      } else {
-        for (int q = lane; q < m1 - m0; q += kWave) moff[q] = toff[m0 + q] - t0;
       }
-      __syncthreads();
     }
-    if (T > CAP) {
-      if (lane == 0) out_list[atomicAdd(out_count, 1)] = I;
-      continue;
-    }
-    for (int q = lane; q < HS; q += kWave) { hkey[q] = -1; hcnt[q] = 0; hrun[q] = 0; }
-    int J[C], Q[C];
-    double V[C];
+    const bool done = mine_on && fits;
+    if (!fits) T = 0;
+    wave_order();
+    int J[C];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const int t = c * kWave + lane;
-      J[c] = -1; Q[c] = 0; V[c] = 0.0;
-      if (t < T) {
-        if (DIRECT) term(t, J[c], V[c]);
-        else { J[c] = tkey[t0 + t]; V[c] = tval[t0 + t]; }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      if (c * kWave + lane < T) {
-        int q = (int)(((uint32_t)J[c] * 0x9E3779B1u) >> (32 - HB));
-        while (true) {
-          const int prev = atomicCAS(&hkey[q], -1, J[c]);
-          if (prev == -1 || prev == J[c]) break;
-          q = q + 1 == HS ? 0 : q + 1;
-        }
-        atomicAdd(&hcnt[q], 1);
-        Q[c] = q;
-      }
-    }
-    __syncthreads();
-    // the occupied slots, in slot order
+    for (int c = 0; c < C; ++c) J[c] = c * G + lane < T ? key[c * G + lane] : INT_MAX;
     int U = 0;
-    for (int base = 0; base < HS; base += kWave) {
-      const int q = base + lane;
-      const bool occ = hkey[q] != -1;
-      const uint64_t bits = __ballot(occ);
-      if (occ) ukey[U + __popcll(bits & below)] = q;
-      U += __popcll(bits);
-    }
-    __syncthreads();
-    // rank of every distinct J (they are distinct, so ranks are a permutation)
-    for (int u = lane; u < U; u += kWave) {
-      const int q = ukey[u], key = hkey[q];
-      int r = 0;
-      for (int v = 0; v < U; ++v) r += hkey[ukey[v]] < key;
-      hrank[q] = r;
-      skey[r] = key;
-      sbase[r] = hcnt[q];
-    }
-    __syncthreads();
-    // exclusive scan of the per-J term counts, in rank order
-    int run = 0;
-    for (int base = 0; base < U; base += kWave) {
-      const int r = base + lane;
-      const int v = r < U ? sbase[r] : 0;
-      int incl = v;
+    for (int last = -1;;) {
+      int mn = INT_MAX;
 #pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int t = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += t;
+      for (int c = 0; c < C; ++c) mn = J[c] > last && J[c] < mn ? J[c] : mn;
+      mn = group_min_int<G>(mn);
+      if (!__any(mn != INT_MAX)) break;
+      if (mn != INT_MAX) {
+        last = mn;
+        if (lane == 0) uniq[U] = mn;
+        ++U;
       }
-      __syncthreads();
-      if (r < U) sbase[r] = run + incl - v;
-      run += __shfl(incl, kWave - 1, kWave);
-      __syncthreads();
     }
-    if (lane == 0) sbase[U] = run;
-    // place the terms: within a J, in segment order
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      if (c * kWave >= T) break;
-      const bool act = c * kWave + lane < T;
-      const int q = Q[c];
-      uint64_t rem = __ballot(act);
-      int before = 0, lead_add = 0;
-      while (rem) {
-        const int leader = __ffsll((unsigned long long)rem) - 1;
-        const int ql = __shfl(q, leader, kWave);
-        const uint64_t m = __ballot(act && q == ql);
-        if (act && q == ql) before = __popcll(m & below);
-        if (lane == leader) lead_add = __popcll(m);
-        rem &= ~m;
-      }
-      if (act) sv[sbase[hrank[q]] + hrun[q] + before] = V[c];
-      __syncthreads();
-      if (lead_add) hrun[q] += lead_add;
-      __syncthreads();
-    }
-    // sums in segment order; sorted pairs over the head of the term range
-    for (int r = lane; r < U; r += kWave) {
+    wave_order();
+    for (int u = lane; u < U; u += G) {
+      const int mine = uniq[u];
       double s = 0.0;
-      for (int x = sbase[r]; x < sbase[r + 1]; ++x) s = __dadd_rn(s, sv[x]);
-      tkey[t0 + r] = skey[r];
-      tval[t0 + r] = s;
+#pragma unroll 8
+      for (int t = 0; t < T; ++t) {
+        const double v = val[t];
+        s = key[t] == mine ? __dadd_rn(s, v) : s;
+      }
+      tkey[t0 + u] = mine;
+      tval[t0 + u] = s;
     }
-    if (lane == 0) ucount[I] = U;
-    __syncthreads();
+    if (done && lane == 0) ucount[I] = U;
+    wave_order();
   }
 }
 
@@ -310,14 +283,18 @@ void launch_galerkin_stage(const GalerkinScratch& g, int n, int nc, int nnz, con
   int* list1 = g.list;
   int* list2 = g.list + nc;
   launch_fill_int(2, g.ctl, 0, s);
-  // the small-row reduce forms its rows' terms from A and writes the terms of
-  // wider rows for the passes below (before: a separate expand pass over A,
-  // 0.53 ms on C3's level 0, and 0.41 ms of reduce)
-  (void)nnz;
-  k_gal_reduce<kSmallC, false, true><<<nc, kWave, 0, s>>>(nc, agg_ptr, g.toff, g.tkey, g.tval, g.ucount, nullptr,
-                                                          nullptr, list1, g.ctl, fine);
-  k_gal_reduce<kWideC, true><<<2048, kWave, 0, s>>>(nc, agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list1, g.ctl,
-                                                    list2, g.ctl + 1, fine);
+  // the first pass holds half as many terms again as the average row
+  const double avg = (double)nnz / nc;
+  auto first = [&](auto lanes) {
+    constexpr int G = decltype(lanes)::value, R = kWave / G * kGalWaves;
+    k_gal_rows<G, kSmallC, false><<<(nc + R - 1) / R, kGalWaves * kWave, 0, s>>>(
+        nc, agg_ptr, g.toff, g.tkey, g.tval, g.ucount, nullptr, nullptr, list1, g.ctl, fine);
+  };
+  if (avg <= 85) first(std::integral_constant<int, 16>());
+  else if (avg <= 170) first(std::integral_constant<int, 32>());
+  else first(std::integral_constant<int, 64>());
+  k_gal_rows<kWave, kWideC, true><<<std::min(1024, (nc + kGalWaves - 1) / kGalWaves), kGalWaves * kWave, 0, s>>>(
+      nc, agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list1, g.ctl, list2, g.ctl + 1, fine);
   k_gal_big<false><<<256, kBig, 0, s>>>(agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list2, g.ctl + 1, nullptr,
                                         nullptr, nullptr);
 }
