@@ -42,6 +42,7 @@ enum : int {
   kErrCrossSystem = 256,
   kErrNotSPD = 512,
   kErrColors = 1024,
+  kErrRowPtr = 4096,    // row pointers not monotone
   kErrTimeout = 2048,   // a bounded wait of a persistent launch ran out
 };
 
@@ -361,12 +362,13 @@ void scan_to_ptr(const int* counts, int* ptr, int n, ScanCtx& sc, hipStream_t s)
 int scan_blocks_needed(int n);
 
 // setup_kernels.hip
-void launch_check_rowptr(int n, const int* rp, int* err, hipStream_t s);
+void launch_check_rowptr(int n, const int* rp, int* err, hipStream_t s, int bit = kErrBadColumn);
 void launch_check_index(int n, const int* idx, int limit, int* err, hipStream_t s);
 // raises kErrNotSPD where a_ii |B_i| < sum_{j != i} |a_ij| |B_j| (to rounding)
 void launch_check_dominant(int n, const int* rp, const int* ci, const double* val, const double* B, int* err,
                            hipStream_t s);
-void launch_check_matrix(int n, const int* rp, const int* ci, const double* val, int* err, hipStream_t s);
+// (rows outside [0, nnz) are flagged, not read)
+void launch_check_matrix(int n, int nnz, const int* rp, const int* ci, const double* val, int* err, hipStream_t s);
 // Up to 8 device ints copied to host pinned slots (0..62) by one launch,
 // together with the error word (slot 63).
 struct Mailbox {

@@ -203,13 +203,20 @@ struct Sync {
     ++m.n;
   }
   void wait_and_check() {
+    wait();
+    check();
+  }
+  void wait() {
     AMG_HIP(hipGetLastError());   // a failed launch surfaces here
     launch_mailbox(m, h.d_err, hp(), h.stream);
     m.n = 0;
     AMG_HIP(hipStreamSynchronize(h.stream));
     AMG_HIP(hipGetLastError());
+  }
+  void check() {
     const int e = hp()[63];
     if (!e) return;
+    if (e & kErrRowPtr) throw Error(AMG_EINVAL, "column index out of range or not strictly increasing");
     if (e & kErrNonFinite) throw Error(AMG_ENANINF, "non-finite matrix entry");
     if (e & kErrZeroDiag) throw Error(AMG_EINVAL, "zero or missing diagonal entry");
     if (e & kErrBadColumn) throw Error(AMG_EINVAL, "column index out of range or not strictly increasing");
@@ -233,6 +240,19 @@ struct Sync {
     return true;
   }
 };
+
+// The checks of the input matrix, read back together (three waits in turn took
+// 75 us, which counts on small systems).  The row checks do not trust the row
+// pointers: a row outside [0, nnz) is flagged, not read.
+void check_level0(const Level& l0, Hierarchy& h, Sync& sy) {
+  sy.fetch(l0.rp, 0);
+  sy.fetch(l0.rp + l0.n, 1);
+  launch_check_rowptr(l0.n, l0.rp, h.d_err, h.stream, kErrRowPtr);
+  launch_check_matrix(l0.n, l0.nnz, l0.rp, l0.ci, l0.val, h.d_err, h.stream);
+  sy.wait();
+  if (sy.hp()[0] != 0 || sy.hp()[1] != l0.nnz) throw Error(AMG_EINVAL, "row_ptr[0] != 0 or row_ptr[n] != nnz");
+  sy.check();
+}
 
 // Whether the level post-smooths by T_k = (I - W A) P (damped Jacobi weights).
 bool jacobi_smoothed(const Hierarchy& h) {
@@ -629,7 +649,7 @@ void galerkin_standalone(Hierarchy& h, const amg_csr& A, const int* agg, const d
   if (sy0.hp()[0] != 0 || sy0.hp()[1] != A.nnz) throw Error(AMG_EINVAL, "row_ptr[0] != 0 or row_ptr[n] != nnz");
   launch_check_rowptr(A.n, A.row_ptr, h.d_err, h.stream);
   sy0.wait_and_check();
-  launch_check_matrix(A.n, A.row_ptr, A.col_idx, A.val, h.d_err, h.stream);
+  launch_check_matrix(A.n, A.nnz, A.row_ptr, A.col_idx, A.val, h.d_err, h.stream);
   launch_check_index(A.n, agg, nc, h.d_err, h.stream);
   sy0.wait_and_check();
   int* agg_ptr = tmp.alloc_n<int>(nc + 1);
@@ -871,18 +891,10 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
     AMG_HIP(hipMemcpyAsync(l0.ci, A.col_idx, (size_t)A.nnz * sizeof(int), hipMemcpyDeviceToDevice, s));
     AMG_HIP(hipMemcpyAsync(l0.val, A.val, (size_t)A.nnz * sizeof(double), hipMemcpyDeviceToDevice, s));
   }
-  // the row pointers must be consistent before any kernel walks the rows
-  sy.fetch(l0.rp, 0);
-  sy.fetch(l0.rp + A.n, 1);
-  sy.wait_and_check();
-  if (sy.hp()[0] != 0 || sy.hp()[1] != A.nnz) throw Error(AMG_EINVAL, "row_ptr[0] != 0 or row_ptr[n] != nnz");
-  launch_check_rowptr(l0.n, l0.rp, h.d_err, s);   // monotone: every row lies inside [0, nnz)
-  sy.wait_and_check();
-  launch_check_matrix(l0.n, l0.rp, l0.ci, l0.val, h.d_err, s);
+  check_level0(l0, h, sy);
   l0.B = h.arena.alloc_n<double>(A.n);
   launch_fill_double(A.n, l0.B, 1.0, s);   // B_0 = 1, the constant near null space vector
   h.levels.push_back(l0);
-  sy.wait_and_check();
 
   const bool debug = std::getenv("AMG_DEBUG") != nullptr;
   if (o.smoother == AMG_SMOOTHER_LEARNED) {
@@ -1133,7 +1145,7 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
   } else if (val != l0.val) {
     AMG_HIP(hipMemcpyAsync(l0.val, val, (size_t)l0.nnz * sizeof(double), hipMemcpyDeviceToDevice, s));
   }
-  launch_check_matrix(l0.n, l0.rp, l0.ci, l0.val, h.d_err, s);
+  launch_check_matrix(l0.n, l0.nnz, l0.rp, l0.ci, l0.val, h.d_err, s);
   sy.wait_and_check();
   const int L = h.L();
   for (int k = 0; k < L; ++k) {   // term lists in segment order, once per hierarchy
@@ -1216,13 +1228,7 @@ void build_batch_hierarchy(Hierarchy& h, const amg_csr& A, const int* sys_off) {
   AMG_HIP(hipMemcpyAsync(l0.rp, A.row_ptr, (A.n + 1) * sizeof(int), hipMemcpyDeviceToDevice, s));
   AMG_HIP(hipMemcpyAsync(l0.ci, A.col_idx, (size_t)A.nnz * sizeof(int), hipMemcpyDeviceToDevice, s));
   AMG_HIP(hipMemcpyAsync(l0.val, A.val, (size_t)A.nnz * sizeof(double), hipMemcpyDeviceToDevice, s));
-  sy.fetch(l0.rp, 0);
-  sy.fetch(l0.rp + A.n, 1);
-  sy.wait_and_check();
-  if (sy.hp()[0] != 0 || sy.hp()[1] != A.nnz) throw Error(AMG_EINVAL, "row_ptr[0] != 0 or row_ptr[n] != nnz");
-  launch_check_rowptr(l0.n, l0.rp, h.d_err, s);
-  sy.wait_and_check();
-  launch_check_matrix(l0.n, l0.rp, l0.ci, l0.val, h.d_err, s);
+  check_level0(l0, h, sy);
   l0.sys_off.assign(sys_off, sys_off + nsys + 1);
   batch_blocks(h, l0);
   batch_check_blocks(l0, h.d_err, s);

@@ -118,7 +118,7 @@ int galerkin_noalloc(const amg_csr& A, const int* agg, const double* pval, int n
   if (ends[0] != 0 || ends[1] != nnz) throw Error(AMG_EINVAL, "row_ptr[0] != 0 or row_ptr[n] != nnz");
   launch_check_rowptr(n, A.row_ptr, err, s);
   wait_and_check(err, s);
-  launch_check_matrix(n, A.row_ptr, A.col_idx, A.val, err, s);
+  launch_check_matrix(n, A.nnz, A.row_ptr, A.col_idx, A.val, err, s);
   launch_check_index(n, agg, nc, err, s);
   wait_and_check(err, s);
 

@@ -20,13 +20,13 @@ constexpr uint64_t kLow62 = (1ull << 62) - 1;
 // tuple state field (top two bits) = s + 1: 0 non-MIS, 1 undecided, 2 MIS
 __device__ __forceinline__ int tstate(uint64_t t) { return (int)(t >> 62); }
 
-__global__ void k_check_matrix(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+__global__ void k_check_matrix(int n, int nnz, const int* __restrict__ rp, const int* __restrict__ ci,
                                const double* __restrict__ val, int* err) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int s = rp[i], e = rp[i + 1];
   int bits = 0;
-  if (e < s) { atomic_or_flag(err, kErrBadColumn); return; }
+  if (s < 0 || e > nnz || e < s) { atomic_or_flag(err, kErrBadColumn); return; }
   bool have_diag = false;
   int prev = -1;
   for (int k = s; k < e; ++k) {
@@ -41,9 +41,9 @@ __global__ void k_check_matrix(int n, const int* __restrict__ rp, const int* __r
   if (bits) atomic_or_flag(err, bits);
 }
 
-__global__ void k_check_rowptr(int n, const int* __restrict__ rp, int* err) {
+__global__ void k_check_rowptr(int n, const int* __restrict__ rp, int* err, int bit) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n && rp[i] > rp[i + 1]) atomic_or_flag(err, kErrBadColumn);
+  if (i < n && rp[i] > rp[i + 1]) atomic_or_flag(err, bit);
 }
 
 __global__ void k_check_index(int n, const int* __restrict__ idx, int limit, int* err) {
@@ -842,14 +842,14 @@ __global__ void __launch_bounds__(512) k_mailbox(Mailbox m, const int* __restric
 }
 }  // namespace
 
-void launch_check_rowptr(int n, const int* rp, int* err, hipStream_t s) {
-  k_check_rowptr<<<grid_for(n), kT, 0, s>>>(n, rp, err);
+void launch_check_rowptr(int n, const int* rp, int* err, hipStream_t s, int bit) {
+  k_check_rowptr<<<grid_for(n), kT, 0, s>>>(n, rp, err, bit);
 }
 void launch_check_index(int n, const int* idx, int limit, int* err, hipStream_t s) {
   k_check_index<<<grid_for(n), kT, 0, s>>>(n, idx, limit, err);
 }
-void launch_check_matrix(int n, const int* rp, const int* ci, const double* val, int* err, hipStream_t s) {
-  k_check_matrix<<<grid_for(n), kT, 0, s>>>(n, rp, ci, val, err);
+void launch_check_matrix(int n, int nnz, const int* rp, const int* ci, const double* val, int* err, hipStream_t s) {
+  k_check_matrix<<<grid_for(n), kT, 0, s>>>(n, nnz, rp, ci, val, err);
 }
 void launch_mailbox(const Mailbox& m, const int* err, int* host, hipStream_t s) {
   k_mailbox<<<1, 512, 0, s>>>(m, err, host);

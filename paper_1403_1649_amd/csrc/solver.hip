@@ -576,6 +576,10 @@ struct OpTrueResid {
 
 // Arnoldi step j (classical Gram-Schmidt): w = D^-1 A q_j with ||w||^2 and
 // the projections q_k'w, k <= j, in the same pass (the basis q_k at Q + k n)
+// The basis is kept unnormalised (its norms, h_{k,k-1} and the start vector's,
+// are scalars of the recurrence), so no pass divides a vector by its norm.
+__host__ __device__ constexpr int arn_norm(int k) { return kScArn + (k == 0 ? 56 : k * 8 + k - 1); }
+__host__ __device__ constexpr int arn_coef(int k) { return kScArn + 57 + k + (k > 2); }   // h_kj / ||q_k|| of the current step (slot 60 is taken)
 struct OpArnSpmv {
   static constexpr int NV = 1 + kArnMax;
   const double* q;
@@ -589,7 +593,7 @@ struct OpArnSpmv {
   __device__ void idle() const {}
   __device__ double x(int c) const { return q[c]; }
   __device__ void row(int i, double ax, double* acc) const {
-    const double t = (1.0 / diag[i]) * ax;
+    const double t = ax / (diag[i] * sc[arn_norm(j)]);
     w[i] = t;
     acc[0] += t * t;
 #pragma unroll
@@ -598,7 +602,11 @@ struct OpArnSpmv {
   }
   __device__ void finalize(const double* s) const {
     sc[kScArn + 48 + j] = sqrt(s[0]);
-    for (int k = 0; k <= j; ++k) sc[kScArn + k * 8 + j] = s[1 + k];
+    for (int k = 0; k <= j; ++k) {
+      const double nk = sc[arn_norm(k)], hk = s[1 + k] / nk;
+      sc[kScArn + k * 8 + j] = hk;
+      sc[arn_coef(k)] = hk / nk;
+    }
   }
 };
 
@@ -847,25 +855,14 @@ struct OpArnStart {
   __device__ void finalize(const double* s) const { sc[kScArn + 56] = sqrt(s[0]); }
 };
 
-struct OpDivide {
-  static constexpr int NV = 0;
-  const double* in;
-  double* out;
-  const double* den;
-  __device__ bool active() const { return true; }
-  __device__ void idle() const {}
-  __device__ void elem(int i, double*) const { out[i] = in[i] / *den; }
-  __device__ void finalize(const double*) const {}
-};
-
 // the projections off w in one pass, w -= sum_k h_kj q_k (k = 0..j in
 // order), and h_{j+1,j} = ||w||
 struct OpArnUpdate {
   static constexpr int NV = 1;
   const double* Q;
-  double* w;
-  const double* sc;
-  double* out;
+  const double* w;
+  double* next;
+  double* sc;
   int j;
   int n;
   __device__ bool active() const { return true; }
@@ -874,11 +871,11 @@ struct OpArnUpdate {
     double t = w[i];
 #pragma unroll
     for (int k = 0; k < kArnMax; ++k)
-      if (k <= j) t -= sc[kScArn + k * 8 + j] * Q[(size_t)k * n + i];
-    w[i] = t;
+      if (k <= j) t -= sc[arn_coef(k)] * Q[(size_t)k * n + i];
+    next[i] = t;
     acc[0] += t * t;
   }
-  __device__ void finalize(const double* s) const { *out = sqrt(s[0]); }
+  __device__ void finalize(const double* s) const { sc[arn_norm(j + 1)] = sqrt(s[0]); }
 };
 
 struct OpSetCtl {
@@ -2682,7 +2679,6 @@ void arnoldi_enqueue(Hierarchy& h, const Level& lv, int m, uint32_t stream, doub
   (void)h;
   const int n = lv.n;
   launch_elem(n, OpArnStart{Q, sc, stream}, rc, s);
-  launch_elem(n, OpDivide{Q, Q, sc + kScArn + 56}, rc, s);
   for (int j = 0; j < m; ++j) {
     const double* qj = Q + (size_t)j * n;
     const OpArnSpmv op{qj, Q, lv.diag, w, sc, j, n};
@@ -2690,8 +2686,7 @@ void arnoldi_enqueue(Hierarchy& h, const Level& lv, int m, uint32_t stream, doub
       launch_sell<double>(n, lv.nslices, lv.sl_ptr, lv.sl_col, lv.sl_val, op, rc, s, lv.sl_dcol);
     else
       launch_rows<double>(n, lv.lpr, lv.rp, lv.ci, lv.val, op, rc, s);
-    launch_elem(n, OpArnUpdate{Q, w, sc, sc + kScArn + (j + 1) * 8 + j, j, n}, rc, s);
-    launch_elem(n, OpDivide{w, Q + (size_t)(j + 1) * n, sc + kScArn + (j + 1) * 8 + j}, rc, s);
+    launch_elem(n, OpArnUpdate{Q, w, Q + (size_t)(j + 1) * n, sc, j, n}, rc, s);
   }
   AMG_HIP(hipMemcpyAsync(host_out, sc + kScArn, 56 * sizeof(double), hipMemcpyDeviceToHost, s));
 }
