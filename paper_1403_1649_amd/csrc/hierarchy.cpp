@@ -566,6 +566,38 @@ void build_sym_dia(Hierarchy& h, Level& lv) {
   lv.sym_mem = mem;
 }
 
+// A level whose shape was tuned to diagonals gets them here, before its Arnoldi
+// products, and no sliced ELL (on 160^3 a fill of 223 us and products of 127 us
+// against 51).  total: the sliced ELL's elements, part of the decision's key.
+// False: nothing built (no decision, or other layouts).
+static bool diagonals_decided(Hierarchy& h, Level& lv, int k, size_t total) {
+  lv.sl_total = (long)total;
+  if (lv.n <= kTsmoothRows || (h.opt.flags & AMG_FLAG_NO_TUNE) || std::getenv("AMG_TUNE_FORCE") ||
+      std::getenv("AMG_TUNE_SLICE") || std::getenv("AMG_TUNE_SCHEDULE"))
+    return false;
+  TuneKey key;
+  key.n = lv.n;
+  key.nnz = lv.nnz;
+  key.rowstat = lv.sl_total;
+  bool sym = false, sliced = false;
+  auto wants = [&](int bytes, Level::Tune& t) {
+    Level::Tune c;
+    key.bytes = bytes;
+    if (!tune_cache_get(key, &c) || (c.fmt != 3 && c.fmt != 5)) return false;
+    (c.fmt == 5 ? sym : sliced) = true;
+    t.pz = c.pz;
+    return true;
+  };
+  if (h.mixed() && !wants(4, lv.t32)) return false;
+  if ((!h.mixed() || k == 0) && !wants(8, lv.t64)) return false;
+  if (sym) build_sym_dia(h, lv);
+  if (sliced || (sym && !lv.sym.u)) build_sdia(h, lv);
+  if (!lv.sym.u && !lv.dia.ptr) return false;
+  lv.sl_ptr = nullptr;
+  lv.nslices = 0;
+  return true;
+}
+
 namespace {
 
 void make_float_copies(Hierarchy& h) {
@@ -958,7 +990,7 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
     launch_mis_init(n, cnt, o.seed, lv.tuple, M1, h.d_mis, h.d_err, s);
     int round = 0;
     int batch = 8;   // rounds between read-backs: a round after the last exits at entry
-    int nnzg = -1;
+    int nnzg = -1, rounds_run = 0;
     bool arn_due = false;   // the previous level's Hessenberg matrix has arrived
     const int glanes = group_lanes(n, (long)nnz - n);
     MisLists ml{};
@@ -975,12 +1007,15 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
       sy.fetch(h.d_mis + mis_word(round & 1, 0), 0, kMisSlots, mis_word(0, 1));
       sy.fetch(h.d_mis + kMisRoundsWord, 1);
       sy.wait_and_check();
+      const int left = sy.hp()[0];
+      rounds_run = sy.hp()[1];
       if (nnzg < 0) {   // the level's first read-back also brings the sizes of G and of the sliced ELL
         nnzg = sy.hp()[3];
-        sell_finish(h, lv, (size_t)sy.hp()[2], sy, 4);
+        const size_t total = sy.hp()[2];
+        if (!diagonals_decided(h, lv, k, total)) sell_finish(h, lv, total, sy, 4);
         arn_due = true;
       }
-      if (sy.hp()[0] == 0) break;
+      if (left == 0) break;
       if (round > 4096) throw Error(AMG_ECOARSEN, "MIS(2) rounds did not terminate");
       batch = 4;
       if (!lists && mk == 2 && n > kMisListRows) {
@@ -992,7 +1027,7 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
         lists = true;
       }
     }
-    lv.mis_rounds = sy.hp()[1];
+    lv.mis_rounds = rounds_run;
     if (debug) std::fprintf(stderr, "amg: level %d n=%d nnz=%d nnz(G)=%d mis_rounds=%d\n", k, n, nnz, nnzg,
                             lv.mis_rounds);
 
@@ -1090,7 +1125,7 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
   tsmooth_patterns(h, tmp, sy);
   alloc_solve_vectors(h);
   for (int k = 0; k < h.L(); ++k)
-    if (h.levels[k].nslices == 0) build_sell(h, tmp, h.levels[k]);
+    if (h.levels[k].nslices == 0 && !h.levels[k].sym.u && !h.levels[k].dia.ptr) build_sell(h, tmp, h.levels[k]);
   if (h.L() == 0 || !jacobi_smoothed(h)) sy.wait_and_check();   // else tsmooth_patterns has waited
   take_arnoldi();
   tsmooth_values(h, tmp);

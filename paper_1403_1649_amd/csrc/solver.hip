@@ -2578,9 +2578,8 @@ void autotune_levels(Hierarchy& h) {
       lv.sh = Level::ShortSell{};
       lv.sh_mem.reset();
     }
-    if (lost_sym)
-      for (Level::Tune* t : {&lv.t64, &lv.t32})
-        if (t->fmt == 5) t->fmt = lv.dia.ptr ? 3 : 0;
+    for (Level::Tune* t : {&lv.t64, &lv.t32})   // symmetric diagonals were decided on and are not to be had
+      if (t->fmt == 5 && !lv.sym.u) t->fmt = lv.dia.ptr ? 3 : 0;
     if (lv.sym.u && lv.t64.fmt != 5 && lv.t32.fmt != 5) {
       lv.sym = Level::SymDia{};
       lv.sym_mem.reset();
@@ -2669,7 +2668,7 @@ void build_solve_graphs(Hierarchy& h) {
   AMG_HIP(hipStreamDestroy(cs));
 }
 
-// Arnoldi on D^-1 A_k (modified Gram-Schmidt) from the seeded start vector,
+// Arnoldi on D^-1 A_k (classical Gram-Schmidt) from the seeded start vector,
 // enqueued on stream s with scalar slots sc (kScArn .. kScArn + 64) and
 // reduction context rc; the (m+1) x m Hessenberg matrix (row stride 8) and
 // the norms ||D^-1 A q_j|| (at 48 + j) are copied to host_out (pinned, 56
@@ -2682,7 +2681,11 @@ void arnoldi_enqueue(Hierarchy& h, const Level& lv, int m, uint32_t stream, doub
   for (int j = 0; j < m; ++j) {
     const double* qj = Q + (size_t)j * n;
     const OpArnSpmv op{qj, Q, lv.diag, w, sc, j, n};
-    if (lv.nslices > 0 && lv.nnz <= 12L * n)   // short, even rows: sliced ELL
+    if (lv.sym.u)
+      launch_sym_dia<double>(n, lv.sym, lv.sym.val, op, rc, s, lv.t64.pz);
+    else if (lv.dia.ptr)
+      launch_sdia<double>(n, lv.dia.nslices, lv.dia.ptr, lv.dia.off, lv.dia.val, op, rc, s, lv.t64.pz);
+    else if (lv.nslices > 0 && lv.nnz <= 12L * n)   // short, even rows: sliced ELL
       launch_sell<double>(n, lv.nslices, lv.sl_ptr, lv.sl_col, lv.sl_val, op, rc, s, lv.sl_dcol);
     else
       launch_rows<double>(n, lv.lpr, lv.rp, lv.ci, lv.val, op, rc, s);
