@@ -568,7 +568,7 @@ void build_sym_dia(Hierarchy& h, Level& lv) {
 
 // A level whose shape was tuned to diagonals gets them here, before its Arnoldi
 // products, and no sliced ELL (on 160^3 a fill of 223 us and products of 127 us
-// against 51).  total: the sliced ELL's elements, part of the decision's key.
+// against 69).  total: the sliced ELL's elements, part of the decision's key.
 // False: nothing built (no decision, or other layouts).
 static bool diagonals_decided(Hierarchy& h, Level& lv, int k, size_t total) {
   lv.sl_total = (long)total;

@@ -656,8 +656,9 @@ void launch_rows16(int n, int lpr, const int* rp, const int16_t* ci16, const T* 
 
 template <typename T, class Op, bool D16, int H>
 void launch_sell_h(int n, int nslices, const int* sl_ptr, const void* cols, const T* sl_val, const int* perm,
-                   const Op& op, RedCtx rc, hipStream_t s, int pstep) {
-  const int g = step_grid((nslices + kBlock / kWave - 1) / (kBlock / kWave), resident_blocks(k_sell<T, Op, D16, H>));
+                   const Op& op, RedCtx rc, hipStream_t s, int pstep, int cap) {
+  const int g = step_grid((nslices + kBlock / kWave - 1) / (kBlock / kWave),
+                          std::min(cap, resident_blocks(k_sell<T, Op, D16, H>)));
   const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
   const RedCtx r2{rc.part, tail ? rc.ticket : nullptr};
   k_sell<T, Op, D16, H><<<g, kBlock, 0, s>>>(n, nslices, sl_ptr, cols, sl_val, perm, op, r2, pstep);
@@ -670,29 +671,29 @@ void launch_sell_h(int n, int nslices, const int* sl_ptr, const void* cols, cons
 template <typename T, class Op>
 void launch_sell(int n, int nslices, const int* sl_ptr, const int* sl_col, const T* sl_val, const Op& op,
                  RedCtx rc, hipStream_t s, const int16_t* sl_dcol = nullptr, int pstep = 0, int slice_h = kWave,
-                 const int* perm = nullptr) {
+                 const int* perm = nullptr, int cap = kMaxPartialBlocks) {   // cap: blocks at most
   if (slice_h != kWave) pstep = 0;
   const void* cols = sl_dcol ? static_cast<const void*>(sl_dcol) : static_cast<const void*>(sl_col);
   if (sl_dcol) {
-    if (slice_h == 32) launch_sell_h<T, Op, true, 32>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
-    else if (slice_h == 16) launch_sell_h<T, Op, true, 16>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
-    else launch_sell_h<T, Op, true, 64>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
+    if (slice_h == 32) launch_sell_h<T, Op, true, 32>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
+    else if (slice_h == 16) launch_sell_h<T, Op, true, 16>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
+    else launch_sell_h<T, Op, true, 64>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
   } else {
-    if (slice_h == 32) launch_sell_h<T, Op, false, 32>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
-    else if (slice_h == 16) launch_sell_h<T, Op, false, 16>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
-    else launch_sell_h<T, Op, false, 64>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep);
+    if (slice_h == 32) launch_sell_h<T, Op, false, 32>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
+    else if (slice_h == 16) launch_sell_h<T, Op, false, 16>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
+    else launch_sell_h<T, Op, false, 64>(n, nslices, sl_ptr, cols, sl_val, perm, op, rc, s, pstep, cap);
   }
 }
 
 template <typename T, class Op>
 void launch_sym_dia(int n, const Level::SymDia& q, const T* val, const Op& op, RedCtx rc, hipStream_t s,
-                    int pstep = 0) {
+                    int pstep = 0, int cap = kMaxPartialBlocks) {
   const int steps = (int)(q.ld / kBlock) + (q.ld % kBlock != 0);
   auto go = [&](auto u) {
     constexpr int U = decltype(u)::value;
     SymOff<U> o;
     for (int t = 0; t < U; ++t) o.d[t] = q.off[t];
-    const int g = step_grid(steps, resident_blocks(k_sym_dia_rows<T, U, Op>));
+    const int g = step_grid(steps, std::min(cap, resident_blocks(k_sym_dia_rows<T, U, Op>)));
     const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
     k_sym_dia_rows<T, U, Op><<<g, kBlock, 0, s>>>(n, q.ld, o, val, op, RedCtx{rc.part, tail ? rc.ticket : nullptr},
                                                   pstep);
@@ -707,8 +708,9 @@ void launch_sym_dia(int n, const Level::SymDia& q, const T* val, const Op& op, R
 
 template <typename T, class Op>
 void launch_sdia(int n, int nslices, const int* dg_ptr, const int* dg_off, const T* dg_val, const Op& op,
-                 RedCtx rc, hipStream_t s, int pstep = 0) {
-  const int g = step_grid((nslices + kBlock / kWave - 1) / (kBlock / kWave), resident_blocks(k_sdia<T, Op>));
+                 RedCtx rc, hipStream_t s, int pstep = 0, int cap = kMaxPartialBlocks) {
+  const int g = step_grid((nslices + kBlock / kWave - 1) / (kBlock / kWave),
+                          std::min(cap, resident_blocks(k_sdia<T, Op>)));
   const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
   const RedCtx r2{rc.part, tail ? rc.ticket : nullptr};
   k_sdia<T, Op><<<g, kBlock, 0, s>>>(n, nslices, dg_ptr, dg_off, dg_val, op, r2, pstep);

@@ -2677,16 +2677,27 @@ void arnoldi_enqueue(Hierarchy& h, const Level& lv, int m, uint32_t stream, doub
                      RedCtx rc, double* host_out, hipStream_t s) {
   (void)h;
   const int n = lv.n;
+  // short, even rows: the layout the level has.  One schedule and one grid for
+  // all of them, so that a thread and a block hold the same rows: the weights
+  // agree bit for bit whether or not the shape was tuned yet.
+  const bool even = lv.nnz <= 12L * n;
+  int cap = kMaxPartialBlocks;
+  if (even)
+    cap = std::min({resident_blocks(k_sell<double, OpArnSpmv, true, kWave>),
+                    resident_blocks(k_sell<double, OpArnSpmv, false, kWave>), resident_blocks(k_sdia<double, OpArnSpmv>),
+                    resident_blocks(k_sym_dia_rows<double, 3, OpArnSpmv>),
+                    resident_blocks(k_sym_dia_rows<double, 4, OpArnSpmv>),
+                    resident_blocks(k_sym_dia_rows<double, 5, OpArnSpmv>)});
   launch_elem(n, OpArnStart{Q, sc, stream}, rc, s);
   for (int j = 0; j < m; ++j) {
     const double* qj = Q + (size_t)j * n;
     const OpArnSpmv op{qj, Q, lv.diag, w, sc, j, n};
-    if (lv.sym.u)
-      launch_sym_dia<double>(n, lv.sym, lv.sym.val, op, rc, s, lv.t64.pz);
-    else if (lv.dia.ptr)
-      launch_sdia<double>(n, lv.dia.nslices, lv.dia.ptr, lv.dia.off, lv.dia.val, op, rc, s, lv.t64.pz);
-    else if (lv.nslices > 0 && lv.nnz <= 12L * n)   // short, even rows: sliced ELL
-      launch_sell<double>(n, lv.nslices, lv.sl_ptr, lv.sl_col, lv.sl_val, op, rc, s, lv.sl_dcol);
+    if (even && lv.sym.u)
+      launch_sym_dia<double>(n, lv.sym, lv.sym.val, op, rc, s, 0, cap);
+    else if (even && lv.dia.ptr)
+      launch_sdia<double>(n, lv.dia.nslices, lv.dia.ptr, lv.dia.off, lv.dia.val, op, rc, s, 0, cap);
+    else if (lv.nslices > 0 && even)   // short, even rows: sliced ELL
+      launch_sell<double>(n, lv.nslices, lv.sl_ptr, lv.sl_col, lv.sl_val, op, rc, s, lv.sl_dcol, 0, kWave, nullptr, cap);
     else
       launch_rows<double>(n, lv.lpr, lv.rp, lv.ci, lv.val, op, rc, s);
     launch_elem(n, OpArnUpdate{Q, w, Q + (size_t)(j + 1) * n, sc, j, n}, rc, s);
