@@ -1456,7 +1456,8 @@ void cheb_post(Hierarchy& h, const Level& lv, int k, Act A, const T* b, const T*
 template <typename T>
 void sgs_sweeps(Hierarchy& h, const Level& lv, Act A, const T* b, T* x) {
   const int nc = (int)lv.coff.size() - 1;
-  const int lpr = lv.lpr < 2 ? 2 : lv.lpr > 32 ? 32 : lv.lpr;
+  // about one entry per lane: k_sgs_color takes a lane's entries one by one
+  const int lpr = std::min(32, 2 * lv.lpr);
   for (int pass = 0; pass < 2 * nc; ++pass) {
     const int c = pass < nc ? pass : 2 * nc - 1 - pass;
     const int m = lv.coff[c + 1] - lv.coff[c];
