@@ -410,13 +410,15 @@ __global__ void __launch_bounds__(kBlock) k_sell(int n, int nslices, const int* 
   if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);
 }
 
-// Symmetric diagonals: the main diagonal and those above it, one vector over
-// the rows each (offsets d, ascending, the same for every row); row i takes
-// a_{i, i-d} from where row i-d stores it, off every other XCD's path in the
-// sweep (L2 while the sweep's window of the largest offset fits, 2 MB at
-// 25,600 rows).  A structured seven-point level moves 32 bytes of values per
-// row instead of 56 (sliced diagonals) from memory.  Products are summed in
-// ascending columns, as in the other layouts.
+// Symmetric diagonals: the main diagonal and those above it, one vector over the
+// rows each (offsets d, ascending, the same for every row); row i takes
+// a_{i, i-d} from where row i-d stores it, in the L2 or, for the largest offset,
+// mostly in the Infinity Cache (160^3: 423 MB cross the L2s per pre-smoothing,
+// 467 with sliced diagonals; the format's own bytes are 262 MB).  Bound by
+// memory: a structured seven-point level moves 32 bytes of values per row
+// instead of 56 (sliced diagonals).  160^3 in FP64, pre-smoothing 83.7 -> 71.2
+// us, FCG product 75.1 -> 56.4, plain residual 70.5 -> 51.2.  Products are
+// summed in ascending columns, as in the other layouts.
 template <int U>
 struct SymOff {
   int d[U];
