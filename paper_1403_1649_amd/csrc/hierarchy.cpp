@@ -898,6 +898,23 @@ static void judge_learned(Hierarchy& h, Arena& tmp) {
   AMG_HIP(hipStreamSynchronize(s));
 }
 
+// (a probed kernel of flexible GMRES is timed between eager launches)
+static bool wants_solve_graphs(const Hierarchy& h) {
+  return !(h.opt.flags & AMG_FLAG_NO_GRAPH) && (h.opt.krylov == AMG_KRYLOV_FCG || h.opt.probe == AMG_PROBE_NONE);
+}
+
+// Drops the captured solve sequences (and the block workspace's): called
+// before anything they read is released or given up, so that a failure on the
+// way to new ones leaves solves that launch their kernels themselves.
+static void drop_solve_graphs(Hierarchy& h) {
+  AMG_HIP(hipStreamSynchronize(h.stream));
+  h.multi.reset();
+  for (auto& g : h.g_iter) (void)hipGraphExecDestroy(g);
+  h.g_iter.clear();
+  if (h.g_restart) (void)hipGraphExecDestroy(h.g_restart);
+  h.g_restart = nullptr;
+}
+
 void build_hierarchy(Hierarchy& h, const amg_csr& A) {
   hipStream_t s = h.stream;
   const amg_options& o = h.opt;
@@ -1139,22 +1156,24 @@ void build_hierarchy(Hierarchy& h, const amg_csr& A) {
     AMG_HIP(hipEventCreate(&h.pev[0]));
     AMG_HIP(hipEventCreate(&h.pev[1]));
   }
-  // (a probed kernel of flexible GMRES is timed between eager launches)
-  if (!(o.flags & AMG_FLAG_NO_GRAPH) && (o.krylov == AMG_KRYLOV_FCG || o.probe == AMG_PROBE_NONE)) build_solve_graphs(h);
+  if (wants_solve_graphs(h)) build_solve_graphs(h);
   h.capture_ms = std::chrono::duration<double, std::milli>(clk::now() - t_graph).count();
 }
 
 
 // A level leaves its symmetric diagonals for the sliced ones (or, where those
-// would be padded too far, for CSR).
+// would be padded too far, for CSR, its layout until they are built).
 static void drop_sym_dia(Hierarchy& h, Level& lv) {
   if (!lv.sym.u) return;
-  AMG_HIP(hipStreamSynchronize(h.stream));
+  const bool use64 = lv.t64.fmt == 5, use32 = lv.t32.fmt == 5;
+  if (use64) lv.t64.fmt = 0;
+  if (use32) lv.t32.fmt = 0;
   lv.sym = Level::SymDia{};
   lv.sym_mem.reset();
   if (!lv.dia.ptr) build_sdia(h, lv);
-  for (Level::Tune* t : {&lv.t64, &lv.t32})
-    if (t->fmt == 5) t->fmt = lv.dia.ptr ? 3 : 0;
+  if (!lv.dia.ptr) return;
+  if (use64) lv.t64.fmt = 3;
+  if (use32) lv.t32.fmt = 3;
 }
 
 // Numeric re-setup on the fixed pattern (Section 3.1, index reuse): new
@@ -1163,7 +1182,8 @@ static void drop_sym_dia(Hierarchy& h, Level& lv) {
 // then the diagonals, the sliced-ELL values and FP32 copies, each level's
 // Jacobi weight (Arnoldi) and the coarse inverse are formed again.  The
 // autotuned kernels and the captured solve graphs stay; with a borrowed A_0
-// given at a new address the graphs are captured again.
+// given at a new address, or a level that leaves its layout, the graphs are
+// captured again; a call that fails in between leaves none.
 void resetup_hierarchy(Hierarchy& h, const double* val) {
   hipStream_t s = h.stream;
   const amg_options& o = h.opt;
@@ -1171,11 +1191,10 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
   Arena tmp;
   struct Drain { hipStream_t s; ~Drain() { (void)hipStreamSynchronize(s); } } drain{s};
   Level& l0 = h.levels[0];
-  bool repoint = false;
   if (o.flags & AMG_FLAG_BORROW_A) {
-    if (val != l0.val) {
+    if (val != l0.val) {   // the graphs read level 0's values at the old address
+      drop_solve_graphs(h);
       l0.val = const_cast<double*>(val);
-      repoint = true;
     }
   } else if (val != l0.val) {
     AMG_HIP(hipMemcpyAsync(l0.val, val, (size_t)l0.nnz * sizeof(double), hipMemcpyDeviceToDevice, s));
@@ -1210,8 +1229,8 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
   sy.fetch(asym, 0);
   sy.wait_and_check();
   if (sy.hp()[0]) {
+    drop_solve_graphs(h);   // the captured kernels read that copy
     for (int k = 0; k < L; ++k) drop_sym_dia(h, h.levels[k]);
-    repoint = true;   // the captured kernels read that copy
   }
   for (int k = 0; k < L; ++k) {
     Level& lv = h.levels[k];
@@ -1226,14 +1245,7 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
   coarse_inverse(h, tmp, sy);
   tsmooth_values(h, tmp);
   sy.wait_and_check();
-  if (repoint) h.multi.reset();   // the kept block workspace's graphs read level 0's old values
-  if (repoint && !h.g_iter.empty()) {
-    for (auto& g : h.g_iter) (void)hipGraphExecDestroy(g);
-    h.g_iter.clear();
-    if (h.g_restart) (void)hipGraphExecDestroy(h.g_restart);
-    h.g_restart = nullptr;
-    build_solve_graphs(h);
-  }
+  if (wants_solve_graphs(h) && h.g_iter.empty()) build_solve_graphs(h);
 }
 
 
