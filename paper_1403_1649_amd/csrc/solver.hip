@@ -2148,10 +2148,13 @@ struct OpGmUpdate {
 constexpr int kGmAhead = 3;
 constexpr int kGmProgressSlot = 48;   // pinned int slot
 void gm_wait(volatile int* progress, int step, hipStream_t s) {
+  AMG_HIP(hipGetLastError());   // a launch of the steps so far that failed
   while (*progress < step) {
-    if (hipStreamQuery(s) != hipErrorNotReady) break;
+    const hipError_t state = hipStreamQuery(s);
+    if (state == hipSuccess) break;
+    if (state != hipErrorNotReady) AMG_HIP(state);
+    (void)hipGetLastError();   // "not ready" is the answer, not an error
   }
-  (void)hipGetLastError();   // hipErrorNotReady is not an error here
 }
 
 template <typename T>
