@@ -445,17 +445,21 @@ __global__ void __launch_bounds__(kBlock) k_sym_dia_rows(int n, long ld, SymOff<
       lo[t] = t > 0 ? val[t * ld + (j < 0 ? 0 : j)] : T(0);
     }
 #pragma unroll
-    for (int t = 0; t < U; ++t) {   // past either end: a zero value, or not taken
+    for (int t = 0; t < U; ++t) {   // past either end: clamped, and not taken
       const int j = row - off.d[t], k = row + off.d[t];
       xu[t] = op.x(k < n ? k : n - 1);
       xl[t] = t > 0 ? op.x(j < 0 ? 0 : j) : T(0);
     }
+    // where the row has no entry the stored zero is left out, not multiplied:
+    // x there may hold an infinity (the compares cost nothing beside the loads)
     T sum = T(0);
 #pragma unroll
     for (int t = U - 1; t > 0; --t)
-      if (row >= off.d[t]) sum += lo[t] * xl[t];
+      if (row >= off.d[t] && lo[t] != T(0)) sum += lo[t] * xl[t];
+    sum += up[0] * xu[0];
 #pragma unroll
-    for (int t = 0; t < U; ++t) sum += up[t] * xu[t];
+    for (int t = 1; t < U; ++t)
+      if (up[t] != T(0)) sum += up[t] * xu[t];
     op.row(row, sum, acc);
   }
   if constexpr (Op::NV > 0) write_partials<Op::NV>(acc, rc, op, rc.ticket != nullptr);

@@ -1,0 +1,41 @@
+"""Symmetric diagonals at their edges: operands with infinities."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+from synthetic import problems as P
+from tests.gpu_helpers import dev_vec, to_dev
+from tests.test_gpu_sym_diagonals import CASES
+
+pytestmark = pytest.mark.gpu
+
+amg = pytest.importorskip("paper_1403_1649_amd")
+
+
+@pytest.mark.parametrize("sched", ["contiguous", "sweep"])
+@pytest.mark.parametrize("name", CASES)
+def test_infinity_reaches_only_the_rows_that_meet_it(name, sched, monkeypatch):
+    """The rows whose entries meet an infinite x_j become infinite, no others:
+    an offset that a row does not have (past the grid's edge, past either end)
+    adds nothing."""
+    make, dim = CASES[name]
+    A = make()
+    monkeypatch.setenv("AMG_TUNE_FORCE", "symdia")
+    monkeypatch.setenv("AMG_TUNE_SCHEDULE", sched)
+    h = amg.setup(*to_dev(A), amg.Options(dim=dim))
+    assert h.level_format(0)[0] == 5
+    S = A.to_scipy().tocsr()
+    rng = np.random.default_rng(5)
+    for at in ([0, A.n - 1], [255, A.n - 300], list(rng.integers(1000, A.n - 1000, 1))):
+        x = P.exact_solution(A.n, 7)
+        x[at] = np.inf
+        y = h.level_spmv(0, dev_vec(x)).cpu().numpy()
+        ref = S @ x
+        inf = ~np.isfinite(ref)
+        assert inf.sum() == np.unique(S[:, at].tocoo().row).size
+        assert np.array_equal(~np.isfinite(y), inf) and np.array_equal(y[inf], ref[inf])
+        # both sides sum at most five to nine products: each within (count - 1) u of the exact row sum
+        rowlen = np.diff(S.indptr).max()
+        bound = 2.5e-16 * rowlen * (abs(S) @ np.where(np.isfinite(x), np.abs(x), 0.0))
+        assert np.all(np.abs(y[~inf] - ref[~inf]) <= bound[~inf])
+    h.close()
