@@ -430,6 +430,7 @@ __global__ void __launch_bounds__(kBlock) k_sym_dia_rows(int n, long ld, SymOff<
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
+  op_begin(op, 0);
   double acc[Op::NV > 0 ? Op::NV : 1];
 #pragma unroll
   for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
@@ -480,6 +481,7 @@ __global__ void __launch_bounds__(kBlock) k_sdia(int n, int nslices, const int* 
     if (blockIdx.x == 0 && threadIdx.x == 0) op.idle();
     return;
   }
+  op_begin(op, 0);
   double acc[Op::NV > 0 ? Op::NV : 1];
 #pragma unroll
   for (int k = 0; k < (Op::NV > 0 ? Op::NV : 1); ++k) acc[k] = 0.0;
