@@ -689,7 +689,9 @@ __global__ void __launch_bounds__(256) k_upper_offsets(int n, const int* __restr
 // A wave per 64 rows, whose entries (one run of A) come coalesced into LDS
 // when they fit; then each lane walks its row.  FILL: the stored diagonals'
 // values, zero where the row has no entry.  Otherwise the entries below the
-// diagonal are compared with their mirror images.
+// diagonal are compared with their mirror images; none above it lacks one,
+// since the set-up refuses a pattern that is not symmetric (k_graph_count) before
+// any layout is chosen.
 constexpr int kSymCap = 640;   // ten entries a row
 template <bool FILL>
 __global__ void __launch_bounds__(256) k_sym_dia(int n, const int* __restrict__ rp, const int* __restrict__ ci,

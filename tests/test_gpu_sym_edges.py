@@ -1,7 +1,7 @@
-"""Symmetric diagonals at their edges: operands with infinities."""
+"""Symmetric diagonals at their edges: operands with infinities, and operators
+whose entries above the diagonal have no mirror image, or a zero one."""
 import numpy as np
 import pytest
-import scipy.sparse as sp
 
 from synthetic import problems as P
 from tests.gpu_helpers import dev_vec, to_dev
@@ -39,3 +39,25 @@ def test_infinity_reaches_only_the_rows_that_meet_it(name, sched, monkeypatch):
         bound = 2.5e-16 * rowlen * (abs(S) @ np.where(np.isfinite(x), np.abs(x), 0.0))
         assert np.all(np.abs(y[~inf] - ref[~inf]) <= bound[~inf])
     h.close()
+
+
+@pytest.mark.parametrize("krylov", ["fcg", "fgmres"])
+def test_entries_above_without_a_mirror_image(krylov, monkeypatch):
+    """Identity rows on the last grid line, the columns not eliminated.  Stored
+    zeros in those rows: not symmetric, laid out otherwise.  No entries there:
+    the pattern is refused."""
+    B = P.poisson2d(300).to_scipy().tocsr()
+    row = np.repeat(np.arange(B.shape[0]), np.diff(B.indptr))
+    last = row >= B.shape[0] - 300
+    B.data[last] = np.where(B.indices[last] == row[last], 1.0, 0.0)
+    A = P.CSR(B.indptr, B.indices, B.data)
+    monkeypatch.setenv("AMG_TUNE_FORCE", "symdia")
+    h = amg.setup(*to_dev(A), amg.Options(dim=2, krylov=krylov))
+    assert h.level_format(0)[0] != 5
+    x = P.exact_solution(A.n, 9)
+    y = h.level_spmv(0, dev_vec(x)).cpu().numpy()
+    assert np.all(np.abs(y - B @ x) <= 2.5e-16 * 5 * (abs(B) @ np.abs(x)))
+    h.close()
+    B.eliminate_zeros()
+    with pytest.raises(amg.AmgError, match="not structurally symmetric"):
+        amg.setup(*to_dev(P.CSR(B.indptr, B.indices, B.data)), amg.Options(dim=2, krylov=krylov))
