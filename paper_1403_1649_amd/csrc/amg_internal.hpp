@@ -104,6 +104,9 @@ struct Level {
   double* sl_val = nullptr;
   float* sl_val32 = nullptr;
   long sl_total = 0;           // stored sliced-ELL elements (64 x the longest row, summed over slices)
+  // symmetric diagonals fit the level's pattern but not its values (or a
+  // decision for them its pattern): the tuner decides apart (level_key)
+  bool asym = false;
   // a second sliced-ELL copy in shorter slices (h = 32 or 16 rows, 64/h lanes
   // per row) over rows ordered by length within 256-row windows, built for
   // the autotuner on levels whose rows vary in length and kept while it is
@@ -448,6 +451,8 @@ void launch_sdia_count(int n, const int* rp, const int* ci, int cap, int* cnt, i
 // distinct offsets col - row > 0 into list[0 .. kSymDiaMax), zero where free;
 // *over: more than fit
 void launch_upper_offsets(int n, const int* rp, const int* ci, int* list, int* over, hipStream_t s);
+// *over |= 2 when a sampled entry above the diagonal differs from its mirror image
+void launch_sym_sample(int n, const int* rp, const int* ci, const double* val, int* over, hipStream_t s);
 // the stored diagonals' values; check: *asym raised unless every entry below
 // the diagonal equals its mirror image
 void launch_sym_dia_fill(const Level& lv, hipStream_t s);
@@ -529,6 +534,9 @@ struct TuneKey {
   long rowstat = 0;
   bool operator<(const TuneKey& o) const;
 };
+TuneKey level_key(const Level& lv, int bytes);
+// the decisions for level k (of each arithmetic type its cycle uses); false: not all made
+bool level_decisions(const Hierarchy& h, const Level& lv, int k, Level::Tune* t32, Level::Tune* t64);
 bool tune_cache_get(const TuneKey& k, Level::Tune* t);
 void tune_cache_put(const TuneKey& k, const Level::Tune& t);
 int mlp_num_params();
@@ -589,7 +597,7 @@ void launch_rs_sym_dia(const Level& lv, int* asym, hipStream_t s);
 void build_short_sell(Hierarchy& h, Level& lv, int slice_h);
 // the sliced-diagonal copy of a level, when its slices have few diagonals
 void build_sdia(Hierarchy& h, Level& lv);
-void build_sym_dia(Hierarchy& h, Level& lv);
+void build_sym_dia(Hierarchy& h, Level& lv, bool doubtful = false);
 void launch_set16(double* dst, const double* host16, hipStream_t s);
 // coloring.hip: first-fit colouring by node-hash priority in synchronous rounds
 void launch_color_round(int n, const int* rp, const int* ci, uint32_t stream, const int* cin, int* cout, int* left,

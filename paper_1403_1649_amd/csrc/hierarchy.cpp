@@ -528,18 +528,25 @@ void build_sdia(Hierarchy& h, Level& lv) {
 // The symmetric diagonals of a level: built when the offsets above the
 // diagonal are kSymDiaMin - 1 to kSymDiaMax - 1 (five-, seven- and nine-point
 // grids), their padding is at most kSdiaPad, and the operator equals its
-// transpose bit for bit.
-void build_sym_dia(Hierarchy& h, Level& lv) {
+// transpose bit for bit.  lv.asym: only that last condition failed.  doubtful:
+// a sample of the entries is looked at first.
+void build_sym_dia(Hierarchy& h, Level& lv, bool doubtful) {
   lv.sym = Level::SymDia{};
   lv.sym_mem.reset();
+  lv.asym = false;
   if (lv.n <= 0 || lv.nnz <= 0) return;
   auto mem = std::make_shared<Arena>();
   int* list = mem->alloc_n<int>(kSymDiaMax + 1);   // and the overflow word
   launch_fill_int(kSymDiaMax + 1, list, 0, h.stream);
+  if (doubtful) launch_sym_sample(lv.n, lv.rp, lv.ci, lv.val, list + kSymDiaMax, h.stream);
   launch_upper_offsets(lv.n, lv.rp, lv.ci, list, list + kSymDiaMax, h.stream);
   Sync sy{h};
   for (int t = 0; t <= kSymDiaMax; ++t) sy.fetch(list + t, t);
   sy.wait_and_check();
+  if (sy.hp()[kSymDiaMax] & 2) {
+    lv.asym = true;
+    return;
+  }
   Level::SymDia q;
   for (int t = 0; t < kSymDiaMax && sy.hp()[t]; ++t) {
     if (q.u == kSymDiaMax - 1) return;
@@ -561,6 +568,7 @@ void build_sym_dia(Hierarchy& h, Level& lv) {
     std::fprintf(stderr, "amg: symmetric diagonals n=%d: %d stored%s\n", lv.n, q.u, sy.hp()[0] ? ", not symmetric" : "");
   if (sy.hp()[0]) {
     lv.sym = Level::SymDia{};
+    lv.asym = true;
     return;
   }
   lv.sym_mem = mem;
@@ -569,30 +577,40 @@ void build_sym_dia(Hierarchy& h, Level& lv) {
 // A level whose shape was tuned to diagonals gets them here, before its Arnoldi
 // products, and no sliced ELL (on 160^3 a fill of 223 us and products of 127 us
 // against 69).  total: the sliced ELL's elements, part of the decision's key.
-// False: nothing built (no decision, or other layouts).
+// False: no sliced or symmetric diagonals for all its products (no decision, or
+// other layouts).
+// Symmetric diagonals depend on the values, so a shape has two decisions: one
+// for symmetric matrices (and those without such diagonals) and one, lv.asym,
+// for the others.  A shape seen only nonsymmetric so far is looked at again.
 static bool diagonals_decided(Hierarchy& h, Level& lv, int k, size_t total) {
   lv.sl_total = (long)total;
   if (lv.n <= kTsmoothRows || (h.opt.flags & AMG_FLAG_NO_TUNE) || std::getenv("AMG_TUNE_FORCE") ||
       std::getenv("AMG_TUNE_SLICE") || std::getenv("AMG_TUNE_SCHEDULE"))
     return false;
-  TuneKey key;
-  key.n = lv.n;
-  key.nnz = lv.nnz;
-  key.rowstat = lv.sl_total;
-  bool sym = false, sliced = false;
-  auto wants = [&](int bytes, Level::Tune& t) {
-    Level::Tune c;
-    key.bytes = bytes;
-    if (!tune_cache_get(key, &c) || (c.fmt != 3 && c.fmt != 5)) return false;
-    (c.fmt == 5 ? sym : sliced) = true;
-    t.pz = c.pz;
-    return true;
+  Level::Tune c32, c64;
+  const bool use64 = !h.mixed() || k == 0;
+  auto decided = [&](bool asym) {
+    lv.asym = asym;
+    return level_decisions(h, lv, k, &c32, &c64);
   };
-  if (h.mixed() && !wants(4, lv.t32)) return false;
-  if ((!h.mixed() || k == 0) && !wants(8, lv.t64)) return false;
-  if (sym) build_sym_dia(h, lv);
-  if (sliced || (sym && !lv.sym.u)) build_sdia(h, lv);
-  if (!lv.sym.u && !lv.dia.ptr) return false;
+  auto any = [&](int fmt) { return (h.mixed() && c32.fmt == fmt) || (use64 && c64.fmt == fmt); };
+  auto diagonal = [](const Level::Tune& t) { return t.fmt == 3 || t.fmt == 5; };
+  if (decided(false)) {
+    if (any(5)) build_sym_dia(h, lv);
+    if (any(5) && !lv.sym.u && !decided(true)) return false;
+  } else {
+    if (!decided(true)) {
+      lv.asym = false;
+      return false;
+    }
+    build_sym_dia(h, lv, true);
+    if (!lv.asym) return false;
+  }
+  if ((h.mixed() && !diagonal(c32)) || (use64 && !diagonal(c64))) return false;
+  if (any(3)) build_sdia(h, lv);
+  if ((any(3) && !lv.dia.ptr) || (any(5) && !lv.sym.u)) return false;
+  lv.t32.pz = c32.pz;
+  lv.t64.pz = c64.pz;
   lv.sl_ptr = nullptr;
   lv.nslices = 0;
   return true;

@@ -686,6 +686,21 @@ __global__ void __launch_bounds__(256) k_upper_offsets(int n, const int* __restr
   if (s_over) atomicOr(over, 1);
 }
 
+// The last entry of every (n / grid)-th row, if above the diagonal, against its
+// mirror image: a level whose shape was last seen nonsymmetric is looked at here
+// before its diagonals are collected.
+constexpr int kSampleRows = 65536;
+__global__ void __launch_bounds__(256) k_sym_sample(int n, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                    const double* __restrict__ val, int* over) {
+  const long t = (long)blockIdx.x * 256 + threadIdx.x, m = (long)gridDim.x * 256;
+  const int i = (int)(t * n / m);
+  if (rp[i + 1] <= rp[i]) return;
+  const int k = rp[i + 1] - 1, j = ci[k];
+  if (j <= i) return;
+  const int q = find_in_row(ci, rp[j], rp[j + 1], i);
+  if (q < 0 || !(val[q] == val[k])) atomic_or_flag(over, 2);
+}
+
 // A wave per 64 rows, whose entries (one run of A) come coalesced into LDS
 // when they fit; then each lane walks its row.  FILL: the stored diagonals'
 // values, zero where the row has no entry.  Otherwise the entries below the
@@ -1087,6 +1102,9 @@ void launch_sdia_fill(int n, const int* rp, const int* ci, const double* val, co
 }
 void launch_upper_offsets(int n, const int* rp, const int* ci, int* list, int* over, hipStream_t s) {
   if (n > 0) k_upper_offsets<<<std::min((n + 255) / 256, 1024), 256, 0, s>>>(n, rp, ci, list, over);
+}
+void launch_sym_sample(int n, const int* rp, const int* ci, const double* val, int* over, hipStream_t s) {
+  if (n > 0) k_sym_sample<<<std::min((n + 255) / 256, kSampleRows / 256), 256, 0, s>>>(n, rp, ci, val, over);
 }
 void launch_sym_dia_fill(const Level& lv, hipStream_t s) {
   if (lv.n > 0)

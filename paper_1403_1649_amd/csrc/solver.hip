@@ -2269,6 +2269,21 @@ bool TuneKey::operator<(const TuneKey& o) const {
   return std::tie(n, nnz, bytes, nrhs, rowstat) < std::tie(o.n, o.nnz, o.bytes, o.nrhs, o.rowstat);
 }
 
+// (the complement marks a decision for lv.asym, in the cache file too)
+TuneKey level_key(const Level& lv, int bytes) {
+  TuneKey key;
+  key.n = lv.n;
+  key.nnz = lv.nnz;
+  key.bytes = bytes;
+  key.rowstat = lv.asym ? ~lv.sl_total : lv.sl_total;
+  return key;
+}
+
+bool level_decisions(const Hierarchy& h, const Level& lv, int k, Level::Tune* t32, Level::Tune* t64) {
+  return (!h.mixed() || tune_cache_get(level_key(lv, 4), t32)) &&
+         ((h.mixed() && k > 0) || tune_cache_get(level_key(lv, 8), t64));
+}
+
 bool tune_cache_get(const TuneKey& k, Level::Tune* t) {
   std::lock_guard<std::mutex> g(g_tune_mu);
   auto& c = tune_cache();
@@ -2369,12 +2384,7 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
     while (t.lpr < 32 && 2L * t.lpr * lv.n < lv.nnz) t.lpr <<= 1;
     return t;
   }
-  TuneKey key;
-  key.n = lv.n;
-  key.nnz = lv.nnz;
-  key.bytes = (int)sizeof(T);
-  key.nrhs = 1;
-  key.rowstat = lv.sl_total;
+  const TuneKey key = level_key(lv, (int)sizeof(T));
   const char* force = std::getenv("AMG_TUNE_FORCE");
   if (!force && !std::getenv("AMG_TUNE_SLICE") && !std::getenv("AMG_TUNE_SCHEDULE")) {
     Level::Tune t;
@@ -2539,33 +2549,26 @@ void autotune_levels(Hierarchy& h) {
     // candidate copies in shorter slices (rows that vary in length) and in
     // sliced diagonals (structured levels); not built when the cached
     // decisions of this level shape use neither
-    bool need_sh = lv.n > kFuseCorrectionRows && lv.sl_ptr;
-    bool need_dia = need_sh;
-    bool need_sym = need_sh;
-    bool need_c16 = need_sh && lv.sl_dcol;   // the offsets fit in 16 bits
-    if (need_sh && !pinned) {
-      TuneKey key;
-      key.n = lv.n;
-      key.nnz = lv.nnz;
-      key.rowstat = lv.sl_total;
+    const bool large = lv.n > kFuseCorrectionRows && lv.sl_ptr;
+    bool need_sh, need_dia, need_sym, need_c16;
+    auto needs = [&] {   // what the decisions use; undecided: everything
       Level::Tune c32, c64;
-      key.bytes = 4;
-      const bool h32 = !h.mixed() || tune_cache_get(key, &c32);
-      key.bytes = 8;
-      const bool use64 = !h.mixed() || k == 0;
-      const bool h64 = !use64 || tune_cache_get(key, &c64);
-      if (h32 && h64) {
-        need_sh = (h.mixed() && c32.sh > 0) || (use64 && c64.sh > 0);
-        need_dia = (h.mixed() && c32.fmt == 3) || (use64 && c64.fmt == 3);
-        need_sym = (h.mixed() && c32.fmt == 5) || (use64 && c64.fmt == 5);
-        need_c16 = need_c16 && ((h.mixed() && c32.fmt == 4) || (use64 && c64.fmt == 4));
-      }
+      const bool open = pinned || !level_decisions(h, lv, k, &c32, &c64), use64 = !h.mixed() || k == 0;
+      auto uses = [&](auto&& f) { return large && (open || (h.mixed() && f(c32)) || (use64 && f(c64))); };
+      need_sh = uses([](const Level::Tune& t) { return t.sh > 0; });
+      need_dia = uses([](const Level::Tune& t) { return t.fmt == 3; });
+      need_sym = uses([](const Level::Tune& t) { return t.fmt == 5; }) && !lv.asym;
+      need_c16 = uses([](const Level::Tune& t) { return t.fmt == 4; }) && lv.sl_dcol;   // the offsets fit in 16 bits
+      return !open;
+    };
+    const bool decided = needs();
+    if (need_sym && !lv.sym.u) {
+      build_sym_dia(h, lv);
+      if (!lv.sym.u && decided) lv.asym = true;   // a decision for another matrix of this shape
+      if (lv.asym) needs();
     }
     if (need_sh) build_short_sell(h, lv, force_h ? std::atoi(force_h) : 0);
-    if (need_sym) build_sym_dia(h, lv);
-    // (another matrix of the cached shape may be nonsymmetric)
-    const bool lost_sym = need_sym && !lv.sym.u;
-    if (need_dia || lost_sym) build_sdia(h, lv);
+    if (need_dia && !lv.dia.ptr) build_sdia(h, lv);
     if (need_c16 && !lv.ci16) {
       auto mem = std::make_shared<Arena>();
       lv.ci16 = mem->alloc_n<int16_t>((size_t)std::max(lv.nnz, 1));
@@ -2582,8 +2585,6 @@ void autotune_levels(Hierarchy& h) {
       lv.sh = Level::ShortSell{};
       lv.sh_mem.reset();
     }
-    for (Level::Tune* t : {&lv.t64, &lv.t32})   // symmetric diagonals were decided on and are not to be had
-      if (t->fmt == 5 && !lv.sym.u) t->fmt = lv.dia.ptr ? 3 : 0;
     if (lv.sym.u && lv.t64.fmt != 5 && lv.t32.fmt != 5) {
       lv.sym = Level::SymDia{};
       lv.sym_mem.reset();
