@@ -1241,14 +1241,19 @@ void resetup_hierarchy(Hierarchy& h, const double* val) {
     launch_rs_sell_values(lv, s);
     if (h.mixed()) launch_to_float(lv.nnz, lv.val, lv.val32, s);
   }
-  int* asym = tmp.alloc_n<int>(1);   // raised when a level's new values are not symmetric any more
-  launch_fill_int(1, asym, 0, s);
-  for (int k = 0; k < L; ++k) launch_rs_sym_dia(h.levels[k], asym, s);
-  sy.fetch(asym, 0);
+  int* asym = tmp.alloc_n<int>(std::max(L, 1));   // raised where a level's new values are not symmetric any more
+  launch_fill_int(std::max(L, 1), asym, 0, s);
+  for (int k = 0; k < L; ++k) launch_rs_sym_dia(h.levels[k], asym + k, s);
+  sy.fetch(asym, 0, L);
   sy.wait_and_check();
   if (sy.hp()[0]) {
     drop_solve_graphs(h);   // the captured kernels read that copy
-    for (int k = 0; k < L; ++k) drop_sym_dia(h, h.levels[k]);
+    for (int k = 0; k < L; ++k) {
+      if (!h.levels[k].sym.u) continue;
+      sy.fetch(asym + k, 0);
+      sy.wait_and_check();
+      if (sy.hp()[0]) drop_sym_dia(h, h.levels[k]);
+    }
   }
   for (int k = 0; k < L; ++k) {
     Level& lv = h.levels[k];
