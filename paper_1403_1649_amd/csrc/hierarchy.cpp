@@ -353,7 +353,8 @@ void alloc_solve_vectors(Hierarchy& h) {
     lv.xt = h.arena.alloc(n * es);
     lv.rc = h.arena.alloc(nc * es);
     lv.c = h.arena.alloc(nc * es);
-    if (lv.tp) lv.y = h.arena.alloc(n * es);
+    // (a level below the finest whose first smoothing step its right-hand side's kernel writes: cycle)
+    if (lv.tp && !lv.sp && k > 0 && h.nsys == 0) lv.y = h.arena.alloc(n * es);
     if (h.opt.smoother == AMG_SMOOTHER_CHEBYSHEV) {
       lv.cr = h.arena.alloc(n * es);
       lv.cd0 = h.arena.alloc(n * es);
