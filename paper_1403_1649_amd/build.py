@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libamg_hip.so")
-SOURCES = ["scan.hip", "setup_kernels.hip", "galerkin.hip", "smooth_interp.hip", "dense.hip", "dense_cycle.hip", "solver.hip", "solver_multi.hip", "mlp.hip", "batch.hip",
+SOURCES = ["scan.hip", "setup_kernels.hip", "galerkin.hip", "smooth_interp.hip", "dense.hip", "dense_cycle.hip", "solver.hip", "chebyshev.hip", "solver_multi.hip", "mlp.hip", "batch.hip",
            "noalloc.hip", "resetup.hip", "coloring.hip", "hierarchy.cpp", "capi.cpp"]
 ARCH = "gfx950"
 

@@ -242,7 +242,7 @@ struct RowPre<Op, std::void_t<typename Op::Pre>> {
 // Groups go to the XCDs in contiguous eighths, swept by the blocks of the XCD
 // side by side (block_steps, -1).
 // D16: columns as 16-bit offsets from the group's base column gbase[g].
-template <typename T, class Op, int R, int Q, bool D16, bool NT>
+template <typename T, class Op, int R, int Q, bool D16>
 __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict__ rp, const void* __restrict__ cols,
                                                    const int* __restrict__ gbase, const T* __restrict__ av, Op op,
                                                    RedCtx rc) {
@@ -285,8 +285,7 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
       const int k = min(base + q * kWave + lane, last);
       if constexpr (D16) t.c[q] = w.cbase + (int)static_cast<const int16_t*>(cols)[k];
       else t.c[q] = static_cast<const int*>(cols)[k];
-      if constexpr (NT) t.v[q] = __builtin_nontemporal_load(av + k);
-      else t.v[q] = av[k];
+      t.v[q] = av[k];
     }
     return t;
   };
@@ -608,13 +607,13 @@ void launch_rows_l(int n, const int* rp, const void* ci, const T* av, const Op& 
 
 // The streamed kernel (a step is four groups of R rows).  gbase non-null:
 // cols are 16-bit offsets.
-template <typename T, class Op, int R, int Q, bool D16, bool NT>
+template <typename T, class Op, int R, int Q, bool D16>
 void launch_stream_l(int n, const int* rp, const void* cols, const int* gbase, const T* av, const Op& op, RedCtx rc,
                      hipStream_t s) {
   constexpr int rows = R * (kBlock / kWave);
-  const int g = step_grid((n + rows - 1) / rows, resident_blocks(k_stream<T, Op, R, Q, D16, NT>));
+  const int g = step_grid((n + rows - 1) / rows, resident_blocks(k_stream<T, Op, R, Q, D16>));
   const bool tail = Op::NV > 0 && g <= kTailBlocks && rc.ticket != nullptr;
-  k_stream<T, Op, R, Q, D16, NT><<<g, kBlock, 0, s>>>(n, rp, cols, gbase, av, op,
+  k_stream<T, Op, R, Q, D16><<<g, kBlock, 0, s>>>(n, rp, cols, gbase, av, op,
                                                       RedCtx{rc.part, tail ? rc.ticket : nullptr});
   if constexpr (Op::NV > 0)
     if (!tail) k_finalize<Op><<<1, kFinBlock, 0, s>>>(op, rc.part, g);
@@ -627,15 +626,15 @@ inline bool stream_rows(int n, long nnz) { return nnz <= 15L * n; }
 template <typename T, class Op>
 void launch_stream(int n, long nnz, const int* rp, const int* ci, const T* av, const Op& op, RedCtx rc,
                    hipStream_t s) {
-  if (2 * nnz <= 15L * n) launch_stream_l<T, Op, 64, 8, false, false>(n, rp, ci, nullptr, av, op, rc, s);
-  else launch_stream_l<T, Op, 32, 8, false, false>(n, rp, ci, nullptr, av, op, rc, s);
+  if (2 * nnz <= 15L * n) launch_stream_l<T, Op, 64, 8, false>(n, rp, ci, nullptr, av, op, rc, s);
+  else launch_stream_l<T, Op, 32, 8, false>(n, rp, ci, nullptr, av, op, rc, s);
 }
 
+// 2 to 64 lanes per row (one lane: the caller's products alone, spmv_f64)
 template <typename T, class Op>
 void launch_rows(int n, int lpr, const int* rp, const int* ci, const T* av, const Op& op, RedCtx rc,
                  hipStream_t s) {
   switch (lpr) {
-    case 1: launch_rows_l<T, 1>(n, rp, ci, av, op, rc, s); break;
     case 2: launch_rows_l<T, 2>(n, rp, ci, av, op, rc, s); break;
     case 4: launch_rows_l<T, 4>(n, rp, ci, av, op, rc, s); break;
     case 8: launch_rows_l<T, 8>(n, rp, ci, av, op, rc, s); break;

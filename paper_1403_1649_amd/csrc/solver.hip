@@ -15,16 +15,32 @@
 #include <string>
 #include <tuple>
 
-#include "kernels_common.hpp"
+#include "level_ops.hpp"
 
 namespace amg {
 
-namespace {
+// The probed kernel: while the outer iteration is being captured, close the
+// current graph segment and keep the launch for the host to issue between
+// segments; otherwise launch it (between HIP events when a probe is set).
+void probe_point(Hierarchy& h, bool selected, std::function<void(hipStream_t)> fn) {
+  if (selected && h.split_at_probe) {
+    hipGraph_t g = nullptr;
+    hipGraphExec_t e = nullptr;
+    AMG_HIP(hipStreamEndCapture(h.cap_stream, &g));
+    AMG_HIP(hipGraphInstantiate(&e, g, nullptr, nullptr, 0));
+    AMG_HIP(hipGraphDestroy(g));
+    h.g_iter.push_back(e);
+    h.probe_fn = std::move(fn);
+    AMG_HIP(hipStreamBeginCapture(h.cap_stream, hipStreamCaptureModeRelaxed));
+    return;
+  }
+  const bool timed = selected && h.pev[0] && !h.capturing;
+  if (timed) AMG_HIP(hipEventRecord(h.pev[0], h.stream));
+  fn(h.stream);
+  if (timed) AMG_HIP(hipEventRecord(h.pev[1], h.stream));
+}
 
-struct Act {
-  const int* p;
-  __device__ __forceinline__ bool on() const { return p == nullptr || *p != 0; }
-};
+namespace {
 
 // ------------------------------------------------------------------ row ops
 template <typename T>
@@ -118,12 +134,14 @@ struct OpResid2 {
 // the outer iteration with z'q for the FCG beta (q given).
 template <typename T>
 struct CoarseV {
+  static constexpr bool kStreams = true;
   const T* c;
   __device__ void begin() {}
   __device__ T at(int J) const { return c[J]; }
 };
 template <typename T>
-struct CoarseK {
+struct CoarseK {   // gathered on levels whose T is not streamed
+  static constexpr bool kStreams = false;
   const T* c;
   const T* d;
   const double* K;
@@ -140,6 +158,7 @@ struct CoarseK {
 template <typename T, class Coarse>
 struct OpPostT {
   static constexpr int NV = 0;
+  static constexpr bool kStreams = Coarse::kStreams;
   Act a;
   const T* y;
   T* xo;
@@ -157,6 +176,7 @@ struct OpPostT {
 template <typename T, class Coarse>
 struct OpPostTDot {
   static constexpr int NV = 1;
+  static constexpr bool kStreams = Coarse::kStreams;
   Act a;
   const T* y;
   T* xo;
@@ -181,43 +201,6 @@ struct OpPostTDot {
   __device__ void finalize(const double* s) const { sc[kScBeta] = -s[0] / sc[kScPQ]; }
 };
 
-// On small levels (at most kFuseCorrectionRows rows, where a launch costs more
-// than the work) the coarse-grid correction is applied where the
-// post-smoothing reads the iterate, x_j + P_j (correction of aggregate agg_j),
-// so it needs no pass of its own; larger levels run the prolongation as its
-// own pass, which is cheaper than three extra gathers per nonzero.  V-cycle: the correction is c; K-cycle: coef_c c (+ coef_d d when
-// the second inner step was kept).
-constexpr int kFuseCorrectionRows = 65536;
-
-template <typename T>
-struct CorrV {
-  const int* agg;
-  const T* pval;
-  const T* c;
-  __device__ T at(const T* xt, int j) const { return xt[j] + pval[j] * c[agg[j]]; }
-};
-
-template <typename T>
-struct CorrNone {   // correction already applied by a prolongation pass
-  __device__ T at(const T* xt, int j) const { return xt[j]; }
-};
-
-template <typename T>
-struct CorrK {
-  const int* agg;
-  const T* pval;
-  const T* c;
-  const T* d;
-  const double* K;
-  const int* F;
-  __device__ T at(const T* xt, int j) const {
-    const int I = agg[j];
-    T xc = (T)K[kKCoefC] * c[I];
-    if (F[1]) xc += (T)K[kKCoefD] * d[I];
-    return xt[j] + pval[j] * xc;
-  }
-};
-
 // new residual and post-smoothing on the corrected iterate x = xt + P e:
 // r = b - A x, x_out = x + w.*r
 template <typename T, class Corr>
@@ -229,6 +212,7 @@ struct OpResidSmooth {
   const T* wd;
   T* xo;
   Corr corr;
+  static constexpr bool kSmall = Corr::kSmall;
   __device__ bool active() const { return a.on(); }
   __device__ void idle() const {}
   __device__ T x(int j) const { return corr.at(xt, j); }
@@ -246,6 +230,7 @@ struct OpResidSmoothDot {
   const T* wd;
   T* xo;
   Corr corr;
+  static constexpr bool kSmall = Corr::kSmall;
   const double* q;
   double* sc;
   __device__ bool active() const { return a.on(); }
@@ -257,111 +242,6 @@ struct OpResidSmoothDot {
     acc[0] += (double)z * q[i];
   }
   __device__ void finalize(const double* s) const { sc[kScBeta] = -s[0] / sc[kScPQ]; }
-};
-
-// ---- Chebyshev smoothing (the polynomial smoother of Section 5): the
-// three-term Chebyshev recurrence on M = D^-1 A over [a, b].  First step from
-// an iterate x0: r = D^-1 (b - A x0), d = r / theta, x = x0 + d; each later
-// step j: r -= D^-1 A d, d = c1_j d + c2_j r, x += d.  Device coefficients
-// K[0] = 1 / theta, K[2j - 1] = c1_j, K[2j] = c2_j (j >= 1 counts the later
-// steps); dv = 1 / a_ii.
-
-// pre-smoothing from x0 = 0, first and second step in one pass: the gathered
-// d_j = (dv_j b_j) / theta, and at row i the second step's update
-template <typename T>
-struct OpChebPre2 {
-  static constexpr int NV = 0;
-  Act a;
-  const T* b;
-  const T* dv;
-  const double* K;
-  T* r;
-  T* dout;
-  T* xo;
-  __device__ bool active() const { return a.on(); }
-  __device__ void idle() const {}
-  __device__ T x(int j) const { return (T)K[0] * (dv[j] * b[j]); }
-  __device__ void row(int i, T ad, double*) const {
-    const T r0 = dv[i] * b[i];
-    const T d0 = (T)K[0] * r0;
-    const T rr = r0 - dv[i] * ad;
-    const T dn = (T)K[1] * d0 + (T)K[2] * rr;
-    r[i] = rr;
-    dout[i] = dn;
-    xo[i] = d0 + dn;
-  }
-  __device__ void finalize(const double*) const {}
-};
-
-// pre-smoothing of degree one from x0 = 0 with the residual: x = d, r = b - A x
-template <typename T>
-struct OpChebPre1Resid {
-  static constexpr int NV = 0;
-  Act a;
-  const T* b;
-  const T* dv;
-  const double* K;
-  T* xt;
-  T* r;
-  __device__ bool active() const { return a.on(); }
-  __device__ void idle() const {}
-  __device__ T x(int j) const { return (T)K[0] * (dv[j] * b[j]); }
-  __device__ void row(int i, T ax, double*) const {
-    xt[i] = (T)K[0] * (dv[i] * b[i]);
-    r[i] = b[i] - ax;
-  }
-  __device__ void finalize(const double*) const {}
-};
-
-// a later step j (din gathered, dout written: two buffers)
-template <typename T>
-struct OpChebStep {
-  static constexpr int NV = 0;
-  Act a;
-  const T* dv;
-  const T* din;
-  T* dout;
-  T* r;
-  T* xo;
-  const double* K;
-  int j;
-  __device__ bool active() const { return a.on(); }
-  __device__ void idle() const {}
-  __device__ T x(int c) const { return din[c]; }
-  __device__ void row(int i, T ad, double*) const {
-    const T rr = r[i] - dv[i] * ad;
-    const T dn = (T)K[2 * j - 1] * din[i] + (T)K[2 * j] * rr;
-    r[i] = rr;
-    dout[i] = dn;
-    xo[i] += dn;
-  }
-  __device__ void finalize(const double*) const {}
-};
-
-// first post-smoothing step on the corrected iterate x0 = xt + P e
-template <typename T, class Corr>
-struct OpChebPost1 {
-  static constexpr int NV = 0;
-  Act a;
-  const T* b;
-  const T* xt;
-  const T* dv;
-  const double* K;
-  T* r;
-  T* dout;
-  T* xo;
-  Corr corr;
-  __device__ bool active() const { return a.on(); }
-  __device__ void idle() const {}
-  __device__ T x(int j) const { return corr.at(xt, j); }
-  __device__ void row(int i, T ax, double*) const {
-    const T rr = dv[i] * (b[i] - ax);
-    const T d = (T)K[0] * rr;
-    r[i] = rr;
-    dout[i] = d;
-    xo[i] = corr.at(xt, i) + d;
-  }
-  __device__ void finalize(const double*) const {}
 };
 
 // residual of a given iterate: r = b - A x
@@ -955,12 +835,6 @@ __global__ void __launch_bounds__(256) k_presmooth_restrict(int nc, const int* _
   }
 }
 
-template <typename T> const T* vals(const Level& l);
-template <> const double* vals<double>(const Level& l) { return l.val; }
-template <> const float* vals<float>(const Level& l) { return l.val32; }
-template <typename T> const T* wdinv(const Level& l);
-template <> const double* wdinv<double>(const Level& l) { return l.wdinv; }
-template <> const float* wdinv<float>(const Level& l) { return l.wdinv32; }
 template <typename T> const T* rvals(const Level& l);
 template <> const double* rvals<double>(const Level& l) { return l.rval; }
 template <> const float* rvals<float>(const Level& l) { return l.rval32; }
@@ -982,66 +856,6 @@ template <> const float* gop<float>(const Level& l) { return l.gop32; }
 template <typename T> const T* cinv(const Hierarchy& h);
 template <> const double* cinv<double>(const Hierarchy& h) { return h.cinv; }
 template <> const float* cinv<float>(const Hierarchy& h) { return h.cinv32; }
-
-inline RedCtx red(Hierarchy& h) { return RedCtx{h.d_part, h.d_ticket}; }
-
-template <typename T> const Level::Tune& tune_of(const Level& l);
-template <> const Level::Tune& tune_of<double>(const Level& l) { return l.t64; }
-template <> const Level::Tune& tune_of<float>(const Level& l) { return l.t32; }
-template <typename T> const T* sell_vals(const Level& l);
-template <> const double* sell_vals<double>(const Level& l) { return l.sl_val; }
-template <> const float* sell_vals<float>(const Level& l) { return l.sl_val32; }
-template <typename T> const T* short_vals(const Level& l);
-template <> const double* short_vals<double>(const Level& l) { return l.sh.val; }
-template <> const float* short_vals<float>(const Level& l) { return l.sh.val32; }
-template <typename T> const T* dia_vals(const Level& l);
-template <> const double* dia_vals<double>(const Level& l) { return l.dia.val; }
-template <> const float* dia_vals<float>(const Level& l) { return l.dia.val32; }
-template <typename T> const T* sym_vals(const Level& l);
-template <> const double* sym_vals<double>(const Level& l) { return l.sym.val; }
-template <> const float* sym_vals<float>(const Level& l) { return l.sym.val32; }
-
-// A row operation on A_k with the level's tuned kernel (CSR, sliced ELL in
-// 64-row slices or in the level's shorter slices, or sliced diagonals).
-template <typename T, class Op>
-void launch_level(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
-  const Level::Tune& t = tune_of<T>(lv);
-  if (t.fmt == 4 && lv.ci16)
-    launch_rows16<T>(lv.n, t.lpr, lv.rp, lv.ci16, vals<T>(lv), op, rc, s);
-  else if (t.fmt == 5 && sym_vals<T>(lv))
-    launch_sym_dia<T>(lv.n, lv.sym, sym_vals<T>(lv), op, rc, s, t.pz);
-  else if (t.fmt == 3 && dia_vals<T>(lv))
-    launch_sdia<T>(lv.n, lv.dia.nslices, lv.dia.ptr, lv.dia.off, dia_vals<T>(lv), op, rc, s, t.pz);
-  else if (t.fmt >= 1 && t.sh > 0 && t.sh == lv.sh.h && short_vals<T>(lv))
-    launch_sell<T>(lv.n, lv.sh.nslices, lv.sh.ptr, lv.sh.col, short_vals<T>(lv), op, rc, s,
-                   t.fmt == 2 ? lv.sh.dcol : nullptr, 0, lv.sh.h, lv.sh.perm);
-  else if (t.fmt >= 1 && lv.sl_ptr)
-    launch_sell<T>(lv.n, lv.nslices, lv.sl_ptr, lv.sl_col, sell_vals<T>(lv), op, rc, s,
-                   t.fmt == 2 ? lv.sl_dcol : nullptr, t.pz);
-  else if (t.lpr == 1) launch_stream<T>(lv.n, lv.nnz, lv.rp, lv.ci, vals<T>(lv), op, rc, s);
-  else launch_rows<T>(lv.n, t.lpr, lv.rp, lv.ci, vals<T>(lv), op, rc, s);
-}
-
-// The probed kernel: while the outer iteration is being captured, close the
-// current graph segment and keep the launch for the host to issue between
-// segments; otherwise launch it (between HIP events when a probe is set).
-void probe_point(Hierarchy& h, bool selected, std::function<void(hipStream_t)> fn) {
-  if (selected && h.split_at_probe) {
-    hipGraph_t g = nullptr;
-    hipGraphExec_t e = nullptr;
-    AMG_HIP(hipStreamEndCapture(h.cap_stream, &g));
-    AMG_HIP(hipGraphInstantiate(&e, g, nullptr, nullptr, 0));
-    AMG_HIP(hipGraphDestroy(g));
-    h.g_iter.push_back(e);
-    h.probe_fn = std::move(fn);
-    AMG_HIP(hipStreamBeginCapture(h.cap_stream, hipStreamCaptureModeRelaxed));
-    return;
-  }
-  const bool timed = selected && h.pev[0] && !h.capturing;
-  if (timed) AMG_HIP(hipEventRecord(h.pev[0], h.stream));
-  fn(h.stream);
-  if (timed) AMG_HIP(hipEventRecord(h.pev[1], h.stream));
-}
 
 // ------------------------------------------------------------ V-cycle tail, one launch
 // The V-cycle levels below the K-cycle that hold S and T, with the coarse
@@ -1389,68 +1203,6 @@ void coarse_solve(Hierarchy& h, const T* b, T* x, const int* act) {
   k_gemv<T><<<(n + rpb - 1) / rpb, kBlock, 0, h.stream>>>(n, cinv<T>(h), b, x, Act{act});
 }
 
-// Residual + post-smoothing of level k on the corrected iterate (and z'q at
-// the top of the outer iteration when fuse_q is given).
-// Chebyshev vectors of a level in the cycle precision: r, two d buffers
-template <typename T>
-struct ChebVecs {
-  T* r;
-  T* d0;
-  T* d1;
-};
-template <typename T>
-ChebVecs<T> cheb_vecs(const Level& lv) {
-  return ChebVecs<T>{static_cast<T*>(lv.cr), static_cast<T*>(lv.cd0), static_cast<T*>(lv.cd1)};
-}
-
-// Pre-smoothing by Chebyshev from x = 0 (degree m = cheb_degree), then the
-// residual r_out = b - A x.
-template <typename T>
-void cheb_pre(Hierarchy& h, const Level& lv, int k, Act A, const T* b, T* xt, T* r_out) {
-  const Level* lp = &lv;
-  RedCtx rc = red(h);
-  const T* dv = wdinv<T>(lv);
-  const int m = h.opt.cheb_degree;
-  const bool sel = k == 0 && h.opt.probe == AMG_PROBE_L0_PRESMOOTH;
-  if (m == 1) {
-    const OpChebPre1Resid<T> op{A, b, dv, lv.cheb, xt, r_out};
-    probe_point(h, sel, [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
-    return;
-  }
-  ChebVecs<T> cv = cheb_vecs<T>(lv);
-  {
-    const OpChebPre2<T> op{A, b, dv, lv.cheb, cv.r, cv.d0, xt};
-    probe_point(h, sel, [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
-  }
-  T* din = cv.d0;
-  T* dout = cv.d1;
-  for (int j = 2; j < m; ++j) {
-    launch_level<T>(lv, OpChebStep<T>{A, dv, din, dout, cv.r, xt, lv.cheb, j}, rc, h.stream);
-    std::swap(din, dout);
-  }
-  launch_level<T>(lv, OpResid<T>{A, b, xt, r_out}, rc, h.stream);
-}
-
-// Post-smoothing by Chebyshev on the corrected iterate, into xo.
-template <typename T, class Corr>
-void cheb_post(Hierarchy& h, const Level& lv, int k, Act A, const T* b, const T* xt, T* xo, Corr corr) {
-  const Level* lp = &lv;
-  RedCtx rc = red(h);
-  const T* dv = wdinv<T>(lv);
-  ChebVecs<T> cv = cheb_vecs<T>(lv);
-  {
-    const OpChebPost1<T, Corr> op{A, b, xt, dv, lv.cheb, cv.r, cv.d0, xo, corr};
-    probe_point(h, k == 0 && h.opt.probe == AMG_PROBE_L0_POSTSMOOTH,
-                [=](hipStream_t st) { launch_level<T>(*lp, op, rc, st); });
-  }
-  T* din = cv.d0;
-  T* dout = cv.d1;
-  for (int j = 1; j < h.opt.cheb_degree; ++j) {
-    launch_level<T>(lv, OpChebStep<T>{A, dv, din, dout, cv.r, xo, lv.cheb, j}, rc, h.stream);
-    std::swap(din, dout);
-  }
-}
-
 // One symmetric Gauss-Seidel step on x in place: the colours forward, then
 // backward.
 template <typename T>
@@ -1472,6 +1224,8 @@ void sgs_sweeps(Hierarchy& h, const Level& lv, Act A, const T* b, T* x) {
   }
 }
 
+// Residual + post-smoothing of level k on the corrected iterate (and z'q at
+// the top of the outer iteration when fuse_q is given).
 template <typename T, class Corr>
 void post_smooth(Hierarchy& h, const Level& lv, int k, Act A, const T* b, const T* xt, const T* wd, T* xo, Corr corr,
                  const double* fuse_q, RedCtx rc) {
@@ -1497,23 +1251,24 @@ void post_smooth(Hierarchy& h, const Level& lv, int k, Act A, const T* b, const 
   }
 }
 
-// A row operation on T_k: streamed (tlpr <= 0: -tlpr entries per lane and
-// group), or with a few lanes per row.
+// A row operation on T_k: streamed (tlpr < 0: -tlpr entries per lane and
+// group; a K-cycle's combination has been formed, CoarseV), or with 4 or 8 lanes
+// per row (post_lanes).
 template <typename T, class Op>
 void launch_post(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
-  if (lv.tlpr > 0) {
-    launch_rows<T>(lv.n, lv.tlpr, lv.tp, lv.tc, tvals<T>(lv), op, rc, s);
-    return;
+  if (lv.tlpr == 8) return launch_rows_l<T, 8>(lv.n, lv.tp, lv.tc, tvals<T>(lv), op, rc, s);
+  if (lv.tlpr == 4) return launch_rows_l<T, 4>(lv.n, lv.tp, lv.tc, tvals<T>(lv), op, rc, s);
+  if constexpr (Op::kStreams) {
+    const void* cols = lv.tc16 ? static_cast<const void*>(lv.tc16) : static_cast<const void*>(lv.tc);
+    auto go = [&](auto q) {
+      constexpr int Q = decltype(q)::value;
+      if (lv.tc16) launch_stream_l<T, Op, 64, Q, true>(lv.n, lv.tp, cols, lv.tbase, tvals<T>(lv), op, rc, s);
+      else launch_stream_l<T, Op, 64, Q, false>(lv.n, lv.tp, cols, nullptr, tvals<T>(lv), op, rc, s);
+    };
+    if (lv.tlpr == -4) go(std::integral_constant<int, 4>());
+    else if (lv.tlpr == -5) go(std::integral_constant<int, 5>());
+    else go(std::integral_constant<int, 8>());
   }
-  const void* cols = lv.tc16 ? static_cast<const void*>(lv.tc16) : static_cast<const void*>(lv.tc);
-  auto go = [&](auto q) {
-    constexpr int Q = decltype(q)::value;
-    if (lv.tc16) launch_stream_l<T, Op, 64, Q, true, false>(lv.n, lv.tp, cols, lv.tbase, tvals<T>(lv), op, rc, s);
-    else launch_stream_l<T, Op, 64, Q, false, false>(lv.n, lv.tp, cols, nullptr, tvals<T>(lv), op, rc, s);
-  };
-  if (lv.tlpr == -4) go(std::integral_constant<int, 4>());
-  else if (lv.tlpr == -5) go(std::integral_constant<int, 5>());
-  else go(std::integral_constant<int, 8>());
 }
 
 // Correction and post-smoothing of a level by T: xo = y + T e (and z'q).
@@ -1665,13 +1420,14 @@ void cycle(Hierarchy& h, int k, const T* b, T* xo, const int* act, const double*
   const T* y = xt;                     // then the iterate after both smoothing steps
   if (both) {
   } else if (cheb || sgs) {
+    bool resid = false;
     if (cheb) {
-      cheb_pre<T>(h, lv, k, A, b, xt, r);
-    } else {   // from x = 0, then the residual
+      resid = cheb_pre<T>(h, lv, k, A, b, xt, r);
+    } else {   // from x = 0
       launch_elem(lv.n, OpFillAct<T>{A, xt}, rc, s);
       sgs_sweeps<T>(h, lv, A, b, xt);
-      launch_level<T>(lv, OpResid<T>{A, b, xt, r}, rc, s);
     }
+    if (!resid) launch_level<T>(lv, OpResid<T>{A, b, xt, r}, rc, s);
   } else if (!kcyc && k > 0 && lv.n <= kFuseCorrectionRows) {
     const int lpr = tune_of<T>(lv).lpr;
     const int grid = lv.nc < 1 ? 1 : lv.nc < 65536 ? lv.nc : 65536;
@@ -2834,7 +2590,9 @@ void spmv_f64(int n, int nnz, const int* rp, const int* ci, const double* val, c
     return;
   }
   if (lpr <= 0) lpr = pick_lpr(n, nnz);
-  launch_rows<double>(n, lpr, rp, ci, val, OpSpmv<double>{Act{nullptr}, x, y}, rc, s);
+  const OpSpmv<double> op{Act{nullptr}, x, y};
+  if (lpr == 1) launch_rows_l<double, 1>(n, rp, ci, val, op, rc, s);
+  else launch_rows<double>(n, lpr, rp, ci, val, op, rc, s);
 }
 
 }  // namespace amg

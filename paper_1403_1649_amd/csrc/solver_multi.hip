@@ -283,12 +283,17 @@ inline int grid_m(int n, int W, bool reduce) {
 }
 
 // A row operator of the block kernels: CSR with 32-bit columns, or (gbase
-// non-null) 16-bit offsets from the base of each 64-row group.
+// non-null) 16-bit offsets from the base of each 64-row group: T_k alone, so
+// only its operations (Op::kOffsets) have that kernel.
 struct MCsr {
   const int* rp;
   const void* cols;
   const int* gbase;
 };
+template <class Op, class = void>
+struct OffsetOp : std::false_type {};
+template <class Op>
+struct OffsetOp<Op, std::enable_if_t<Op::kOffsets>> : std::true_type {};
 
 // Lane groups that share a row's entries: on levels too small to fill the
 // chip with one, as many (up to 8, within a wave) as bring it to kSplitThreads
@@ -309,10 +314,12 @@ void rows_m_w(int n, long nnz, const MCtx& m, const MCsr& A, const T* av, const 
   const int split = split_of(n, nnz, WL);
   const int g = grid_m(n, WL * split, Op::NV > 0);
   for (int c0 = 0; c0 < m.R; c0 += WL * V) {
-    if (A.gbase)
-      k_rows_m<T, WL, V, true, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, A.gbase, av, op, m.part);
-    else
-      k_rows_m<T, WL, V, false, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, nullptr, av, op, m.part);
+    if constexpr (OffsetOp<Op>::value)
+      if (A.gbase) {
+        k_rows_m<T, WL, V, true, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, A.gbase, av, op, m.part);
+        continue;
+      }
+    k_rows_m<T, WL, V, false, Op><<<g, kBlock, 0, s>>>(n, m.R, c0, split, A.rp, A.cols, nullptr, av, op, m.part);
   }
   if constexpr (Op::NV > 0) k_finalize_m<Op><<<Op::NV * m.R, kFinMBlock, 0, s>>>(op, m.part, g, m.R, m.tot, m.ticket);
 }
@@ -346,7 +353,8 @@ void rows_m(int n, long nnz, const MCtx& m, int tile, const MCsr& A, const T* av
       case 4: rows_m_w<T, 4, VM>(n, nnz, m, A, av, op, s); break;
       case 8: rows_m_w<T, 8, VM>(n, nnz, m, A, av, op, s); break;
       case 16: rows_m_w<T, 16, VM>(n, nnz, m, A, av, op, s); break;
-      default: rows_m_w<T, 32, VM>(n, nnz, m, A, av, op, s); break;
+      default:
+        if constexpr (VM == 2) rows_m_w<T, 32, VM>(n, nnz, m, A, av, op, s);   // 64 columns in all
     }
     return;
   }
@@ -450,6 +458,7 @@ struct MResidSmooth {
 template <typename T, bool DOT>
 struct MPostT {
   static constexpr int NV = DOT ? 1 : 0;
+  static constexpr bool kOffsets = true;
   ActAny a;
   int R;
   const T* y;
@@ -926,22 +935,6 @@ struct MTrueResid {
   __device__ void finalize(int c, const double* s) const { sc[mTrue * R + c] = s[0]; }
 };
 
-// Y = A X: the kernel the block autotuner times
-template <typename T>
-struct MSpmvT {
-  static constexpr int NV = 0;
-  ActAny a;
-  int R;
-  const T* xin;
-  T* y;
-  M_COMMON
-  template <int V>
-  __device__ Pack<T, V> x(int j, int c) const { return ldp<V>(xin + (size_t)j * R + c); }
-  template <int V>
-  __device__ void row(int i, int c, const Pack<T, V>& ax, double (&)[1][V]) const { stp<V>(y + (size_t)i * R + c, ax); }
-  __device__ void finalize(int, const double*) const {}
-};
-
 // restart the columns whose recurrence converged but whose true residual did
 // not: r = b - A x for them, running again
 struct MRestartMask {
@@ -1183,7 +1176,7 @@ int tune_tile(Hierarchy& h, const Level& lv, const MWork& W, T* x, T* y) {
   hipStream_t s = h.stream;
   AMG_HIP(hipMemsetAsync(x, 0, (size_t)lv.n * R * sizeof(T), s));
   const T* av = vals_t<T>(lv);
-  const MSpmvT<T> op{ActAny{nullptr}, R, x, y};
+  const MRestrict<T> op{ActAny{nullptr}, R, x, y};   // y = A x
   hipEvent_t e0 = h.ev[2], e1 = h.ev[3];
   float best_us = 1e30f;
   int best = wf;
