@@ -2177,7 +2177,9 @@ Level::Tune tune_one(Hierarchy& h, Level& lv, T* x, T* y) {
     if (us < best.us) { best.us = us; best.fmt = 0; best.lpr = lpr; }
   }
   int csr16_lanes = best.lpr;
-  if (stream_rows(lv.n, lv.nnz)) {   // streamed rows (one lane sums a row)
+  // streamed rows (one lane sums a row); not where the level has symmetric
+  // diagonals, of whose time they took 1.5 to 4.6 times (67,077 to 4,096,000 rows)
+  if (stream_rows(lv.n, lv.nnz) && (force || !sym_vals<T>(lv))) {
     const float us = time_it([&] { launch_stream<T>(lv.n, lv.nnz, lv.rp, lv.ci, vals<T>(lv), op, rc, s); });
     if (std::getenv("AMG_DEBUG"))
       std::fprintf(stderr, "amg: level n=%d CSR streamed: %.2f us (best so far %.2f)\n", lv.n, us, best.us);
@@ -2324,7 +2326,11 @@ void autotune_levels(Hierarchy& h) {
       if (lv.asym) needs();
     }
     if (need_sh) build_short_sell(h, lv, force_h ? std::atoi(force_h) : 0);
-    if (need_dia && !lv.dia.ptr) build_sdia(h, lv);
+    // Undecided, the sliced diagonals are not built where the symmetric ones
+    // are: those move four bytes of values to their seven (five-point grids: three
+    // to five) and took 0.60 to 0.78 of their time on every level of 67,077 to
+    // 4,096,000 rows, while building and timing the loser cost 4 ms at 160^3.
+    if (need_dia && !lv.dia.ptr && (pinned || decided || !lv.sym.u)) build_sdia(h, lv);
     if (need_c16 && !lv.ci16) {
       auto mem = std::make_shared<Arena>();
       lv.ci16 = mem->alloc_n<int16_t>((size_t)std::max(lv.nnz, 1));
