@@ -46,6 +46,7 @@ namespace {
 template <typename T>
 struct OpSpmv {
   static constexpr int NV = 0;
+  static constexpr bool kOnce = true;
   Act a;
   const T* xv;
   T* y;
