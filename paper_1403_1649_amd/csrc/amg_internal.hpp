@@ -568,7 +568,8 @@ int solve_batch_impl(Hierarchy& h, const double* b, double rtol, double* x, int*
 void launch_dense_inverse_batched(const Level& lv, int nterm, const TermInfo* d_term, const TermInfo* h_term,
                                   double* work, int* piv, double* inv, float* inv32, int* err, hipStream_t s);
 void launch_dense_inverse_spd(int nterm, const TermInfo* d_term, const TermInfo* h_term, const int* rp, const int* ci,
-                              const double* val, double* inv, float* inv32, Arena& tmp, int* err, hipStream_t s);
+                              const double* val, double* inv, float* inv32, Arena& tmp, int* err, hipStream_t s,
+                              bool checked = false);
 void build_batch_hierarchy(Hierarchy& h, const amg_csr& A, const int* sys_off);
 void spmv_sell_level(Hierarchy& h, const Level& lv, const double* x, double* y, bool offsets16);
 void level_spmv(const Hierarchy& h, int k, const double* x, double* y, hipStream_t s);

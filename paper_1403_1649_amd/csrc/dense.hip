@@ -523,10 +523,16 @@ __device__ __forceinline__ bool load_and_invert(const double* __restrict__ A, in
 // Buffer that holds system t before panel K: the swap ends in `inv`.
 __device__ __forceinline__ bool source_is_inv(int n, int K) { return ((n + kB - 1) / kB - K) % 2 == 0; }
 
+// Whether the operator was found unfit before the elimination (the error word,
+// or null where nothing looked): the launches then end at once.
+__device__ __forceinline__ bool is_refused(const int* err) { return err && (*err & kErrNotSPD); }
+
 // dense copies of the systems' diagonal blocks (32 rows per workgroup)
 __global__ void __launch_bounds__(256) k_gji_init(const TermInfo* __restrict__ ti, const int* __restrict__ rp,
                                                   const int* __restrict__ ci, const double* __restrict__ val,
-                                                  double* __restrict__ inv, double* __restrict__ work) {
+                                                  double* __restrict__ inv, double* __restrict__ work,
+                                                  const int* refused) {
+  if (is_refused(refused)) return;
   const TermInfo t = ti[blockIdx.y];
   const int r0 = blockIdx.x * kB, rows = min(kB, t.n - r0);
   if (rows <= 0) return;
@@ -543,7 +549,8 @@ __global__ void __launch_bounds__(256) k_gji_init(const TermInfo* __restrict__ t
 // tiles that inverting it in each costs more than a launch
 __global__ void __launch_bounds__(kWave) k_gji_pivot(const TermInfo* __restrict__ ti, const double* __restrict__ inv,
                                                      const double* __restrict__ work, double* __restrict__ mbuf,
-                                                     int K, int* err) {
+                                                     int K, int* err, const int* refused) {
+  if (is_refused(refused)) return;
   const TermInfo t = ti[blockIdx.x];
   const int c0 = K * kB;
   if (c0 >= t.n) return;
@@ -558,7 +565,9 @@ __global__ void __launch_bounds__(kWave) k_gji_pivot(const TermInfo* __restrict_
 template <bool PIVOT>   // the workgroup inverts the pivot block itself (else mbuf)
 __global__ void __launch_bounds__(256) k_gji_panel(const TermInfo* __restrict__ ti, double* __restrict__ inv,
                                                    double* __restrict__ work, float* __restrict__ inv32,
-                                                   const double* __restrict__ mbuf, int K, int* err) {
+                                                   const double* __restrict__ mbuf, int K, int* err,
+                                                   const int* refused) {
+  if (is_refused(refused)) return;
   __shared__ double sM[kB][kB + 1], sA[kB][kB + 1], sT[kB][kB + 1];
   const TermInfo t = ti[blockIdx.z];
   const int n = t.n, c0 = K * kB, r0 = blockIdx.y * kB, q0 = blockIdx.x * kB;
@@ -703,12 +712,16 @@ namespace amg {
 // Inverses of diagonal blocks (one per TermInfo) in inv (row-major n x n at
 // each TermInfo's offset), blocked Gauss-Jordan without pivoting; inv32
 // (optional) receives the float copy.  Raises kErrNotSPD on a non-positive
-// pivot; the caller then redoes the inversion with pivoting.  Scratch from tmp.
+// pivot; the caller then redoes the inversion with pivoting.  checked: the
+// operator was looked at, and a raised kErrNotSPD spares the elimination.  Scratch
+// from tmp.
 constexpr int kNoPivotMax = 8192;    // unknowns of a system at most
 constexpr long kPivotTiles = 2048;   // tiles of a launch up to which each inverts the pivot block itself
 void launch_dense_inverse_spd(int nterm, const TermInfo* d_term, const TermInfo* h_term, const int* rp, const int* ci,
-                              const double* val, double* inv, float* inv32, Arena& tmp, int* err, hipStream_t s) {
+                              const double* val, double* inv, float* inv32, Arena& tmp, int* err, hipStream_t s,
+                              bool checked) {
   if (nterm == 0) return;
+  const int* refused = checked ? err : nullptr;
   size_t total = 0;
   int nmax = 0;
   for (int t = 0; t < nterm; ++t) {
@@ -724,14 +737,14 @@ void launch_dense_inverse_spd(int nterm, const TermInfo* d_term, const TermInfo*
   double* mbuf = own ? nullptr : tmp.alloc_n<double>((size_t)nterm * kB * kB);
   for (int t0 = 0; t0 < nterm; t0 += kZ) {
     const int nt = std::min(kZ, nterm - t0);
-    k_gji_init<<<dim3(np, nt), 256, 0, s>>>(d_term + t0, rp, ci, val, inv, work);
+    k_gji_init<<<dim3(np, nt), 256, 0, s>>>(d_term + t0, rp, ci, val, inv, work, refused);
     for (int K = 0; K < np; ++K) {
       const dim3 g(np, np, nt);
       if (own) {
-        k_gji_panel<true><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, nullptr, K, err);
+        k_gji_panel<true><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, nullptr, K, err, refused);
       } else {
-        k_gji_pivot<<<nt, kWave, 0, s>>>(d_term + t0, inv, work, mbuf, K, err);
-        k_gji_panel<false><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, mbuf, K, err);
+        k_gji_pivot<<<nt, kWave, 0, s>>>(d_term + t0, inv, work, mbuf, K, err, refused);
+        k_gji_panel<false><<<g, 256, 0, s>>>(d_term + t0, inv, work, inv32, mbuf, K, err, refused);
       }
     }
   }

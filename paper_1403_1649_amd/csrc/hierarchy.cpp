@@ -798,11 +798,12 @@ static void coarse_inverse(Hierarchy& h, Arena& tmp, Sync& sy) {
   // through one column each).
   bool inverted = false;
   {
-    if (o.krylov != AMG_KRYLOV_FCG) launch_check_dominant(cl.n, cl.rp, cl.ci, cl.val, cl.B, h.d_err, s);
+    const bool checked = o.krylov != AMG_KRYLOV_FCG;
+    if (checked) launch_check_dominant(cl.n, cl.rp, cl.ci, cl.val, cl.B, h.d_err, s);
     const TermInfo t{0, 0, cl.n, 0, 0};
     TermInfo* dt = tmp.alloc_n<TermInfo>(1);
     AMG_HIP(hipMemcpyAsync(dt, &t, sizeof(TermInfo), hipMemcpyHostToDevice, s));
-    launch_dense_inverse_spd(1, dt, &t, cl.rp, cl.ci, cl.val, h.cinv, h.cinv32, tmp, h.d_err, s);
+    launch_dense_inverse_spd(1, dt, &t, cl.rp, cl.ci, cl.val, h.cinv, h.cinv32, tmp, h.d_err, s, checked);
     inverted = !sy.take_not_spd();
   }
   if (!inverted) launch_dense_inverse(cl.n, cl.rp, cl.ci, cl.val, work, h.cinv, h.cinv32, gj_sync, h.d_err, s);
