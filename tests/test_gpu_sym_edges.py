@@ -1,10 +1,12 @@
 """Symmetric diagonals at their edges: operands with infinities, and operators
-whose entries above the diagonal have no mirror image, or a zero one."""
+whose entries above the diagonal have no mirror image, or a zero one, and a
+layout taken away again."""
 import numpy as np
 import pytest
 
 from synthetic import problems as P
 from tests.gpu_helpers import dev_vec, to_dev
+from tests.test_gpu_slices import _entrywise
 from tests.test_gpu_sym_diagonals import CASES
 
 pytestmark = pytest.mark.gpu
@@ -61,3 +63,28 @@ def test_entries_above_without_a_mirror_image(krylov, monkeypatch):
     B.eliminate_zeros()
     with pytest.raises(amg.AmgError, match="not structurally symmetric"):
         amg.setup(*to_dev(P.CSR(B.indptr, B.indices, B.data)), amg.Options(dim=2, krylov=krylov))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_resetup_of_an_early_layout_to_nonsymmetric_values(precision):
+    """The second setup of a shape lays level 0 out before its Arnoldi products
+    and builds no sliced ELL; a re-setup then takes the layout away, and later
+    values that are symmetric again find the sliced diagonals."""
+    A = P.poisson3d(73)
+    b = P.rhs(A, P.exact_solution(A.n, 3))
+    dev = to_dev(A)
+    amg.setup(*dev, amg.Options(dim=3, precision=precision)).close()
+    h = amg.setup(*dev, amg.Options(dim=3, precision=precision))
+    assert h.level_format(0)[0] == 5
+    v = np.array(A.val)
+    k = int(A.row_ptr[A.n // 2])
+    v[k] = np.nextafter(v[k], 0.0)   # one rounding off: still solvable by flexible CG
+    for val in (v, A.val):
+        M = P.CSR(A.row_ptr, A.col, val)
+        h.resetup(dev_vec(val))
+        assert h.level_format(0)[0] == 3
+        _entrywise(h, 0, 101)
+        x, _, rel = amg.solve(h, dev_vec(b), 1e-8)
+        assert rel <= 1e-8
+        assert np.linalg.norm(b - M.to_scipy() @ x.cpu().numpy()) <= 1.01e-8 * np.linalg.norm(b)
+    h.close()
