@@ -77,7 +77,7 @@ def traffic_file(workload: str) -> str:
     return os.path.join(ROOT, "profiles", f"l0_presmooth_{workload.lower()}_traffic.md")
 
 
-KERNEL_SOURCES = ["solver.hip", "kernels_common.hpp", "device_utils.hpp", "amg_internal.hpp"]
+KERNEL_SOURCES = ["solver.hip", "level_ops.hpp", "kernels_common.hpp", "device_utils.hpp", "amg_internal.hpp"]
 
 
 def kernel_sources_sha256() -> str:

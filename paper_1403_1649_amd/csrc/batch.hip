@@ -7,8 +7,8 @@
 // follows the arithmetic of a solve on its own.
 //
 // Reductions are segmented by a block table: each block covers rows of one
-// system only, writes one partial per reduction, and a one-block finalize
-// sums each system's blocks in order (deterministic, no atomics).  The table
+// system only and writes one partial per reduction, and a finalize with a block
+// per system sums them in a fixed order (deterministic).  The table
 // also gives every block its system, so per-system scalars are read once per
 // block and blocks of systems that are masked off (converged, or not taking
 // the second inner K-cycle step) skip their rows.
@@ -177,7 +177,9 @@ void bfinal(const Level& tab, const BCtx& c, const Op& op, hipStream_t s) {
 }
 
 // rows of a CSR matrix (rp, ci, av) whose rows are those of the level `tab`
-// (A_k itself, or R_k = P_k^T over the rows of level k+1)
+// (A_k itself, or R_k = P_k^T over the rows of level k+1).  lpr: about two entries
+// per lane (pick_lpr), though a lane takes its entries one by one here: twice the
+// lanes make 64 2-D systems (5.7 M rows, mixed) slower, 25.3 -> 26.0 ms.
 template <typename T, class Op>
 void brows_on(const Level& tab, int lpr, const int* rp, const int* ci, const T* av, const BCtx& c, const Op& op,
               hipStream_t s) {

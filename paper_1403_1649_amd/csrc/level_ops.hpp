@@ -18,8 +18,9 @@ struct Act {
 // than the work) the coarse-grid correction is applied where the
 // post-smoothing reads the iterate, x_j + P_j (correction of aggregate agg_j),
 // so it needs no pass of its own; larger levels run the prolongation as its
-// own pass, which is cheaper than three extra gathers per nonzero.  V-cycle: the correction is c; K-cycle: coef_c c (+ coef_d d when
-// the second inner step was kept).
+// own pass, which is cheaper than three extra gathers per nonzero.  V-cycle: the
+// correction is c; K-cycle: coef_c c (+ coef_d d when the second inner step was
+// kept).
 constexpr int kFuseCorrectionRows = 65536;
 
 template <typename T>
@@ -86,8 +87,9 @@ struct SmallLevelOp : std::false_type {};
 template <class Op>
 struct SmallLevelOp<Op, std::enable_if_t<Op::kSmall>> : std::true_type {};
 
-// A row operation on A_k with the level's tuned kernel (CSR, sliced ELL in
-// 64-row slices or in the level's shorter slices, or sliced diagonals).
+// A row operation on A_k with the level's tuned kernel: CSR by lanes or streamed
+// (lpr 1), sliced ELL in 64-row slices or in the level's shorter slices, sliced or
+// symmetric diagonals.
 template <typename T, class Op>
 void launch_level(const Level& lv, const Op& op, RedCtx rc, hipStream_t s) {
   const Level::Tune& t = tune_of<T>(lv);
