@@ -30,6 +30,7 @@ constexpr int kGalWaves = 2;     // waves per block of the reduce passes
 constexpr int kSmallC = 8;       // terms per lane of the first reduce pass (16 to 64 lanes a row, by the average)
 constexpr int kWideC = 16;       // terms per lane of the second, a wave per row
 constexpr int kMaxWaveTerms = kWave * kWideC;
+constexpr int kBigBlocks = 1024;  // of the extraction path, rows dealt in turn: four on a CU, whose waits overlap
 
 // Step 1: number of terms of the k-th fine row in segment order (0 beyond the
 // rows that belong to an aggregate).
@@ -295,7 +296,7 @@ void launch_galerkin_stage(const GalerkinScratch& g, int n, int nc, int nnz, con
   else first(std::integral_constant<int, 64>());
   k_gal_rows<kWave, kWideC, true><<<std::min(1024, (nc + kGalWaves - 1) / kGalWaves), kGalWaves * kWave, 0, s>>>(
       nc, agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list1, g.ctl, list2, g.ctl + 1, fine);
-  k_gal_big<false><<<256, kBig, 0, s>>>(agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list2, g.ctl + 1, nullptr,
+  k_gal_big<false><<<std::min(kBigBlocks, nc), kBig, 0, s>>>(agg_ptr, g.toff, g.tkey, g.tval, g.ucount, list2, g.ctl + 1, nullptr,
                                         nullptr, nullptr);
 }
 
@@ -308,7 +309,7 @@ void launch_galerkin_finish(const GalerkinScratch& g, int nc, const int* agg_ptr
     k_gal_compact<decltype(gl)::value><<<group_grid(nc, G), 256, 0, s>>>(nc, agg_ptr, g.toff, g.tkey, g.tval, rp_c,
                                                                          ci_c, val_c);
   });
-  k_gal_big<true><<<256, kBig, 0, s>>>(agg_ptr, g.toff, g.tkey, g.tval, nullptr, g.list + nc, g.ctl + 1, rp_c,
+  k_gal_big<true><<<std::min(kBigBlocks, nc), kBig, 0, s>>>(agg_ptr, g.toff, g.tkey, g.tval, nullptr, g.list + nc, g.ctl + 1, rp_c,
                                        ci_c, val_c);
 }
 
