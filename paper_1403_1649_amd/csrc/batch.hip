@@ -253,8 +253,8 @@ __global__ void __launch_bounds__(kBlock) k_bsell(const int* __restrict__ blk, i
 
 // Products with T_k (short CSR rows), streamed through LDS as k_stream: a wave
 // takes 64 rows of its block's range at a time, its loads run ahead by one
-// group of rows, and a group of more than 64 Q entries is summed row by row by
-// the whole wave.  Bound by bytes (T's entries, y, out, q); 64 2-D systems of
+// group of rows, and a group of more than 64 Q entries is summed by
+// long_group_sum.  Bound by bytes (T's entries, y, out, q); 64 2-D systems of
 // 5.7 M rows in FP32: 54 us with z'q, in place of the second product with A_k
 // (71 us), the prolongation and a pass for z'q.
 template <typename T, int Q, class Op>
@@ -309,13 +309,7 @@ __global__ void __launch_bounds__(kBlock) k_bstream(const int* __restrict__ blk,
         for (int k = w0.beg - base; k < w0.end - base; ++k) sum += prod[k];
         wave_lds_order();
       } else {
-        for (int i = 0; i < kWave; ++i) {
-          const int b = __builtin_amdgcn_readlane(w0.beg, i), e = __builtin_amdgcn_readlane(w0.end, i);
-          T t = T(0);
-          for (int k = b + lane; k < e; k += kWave) t += av[k] * op.x(ci[k]);
-          t = wave_sum(t);
-          if (lane == i) sum = t;
-        }
+        sum = long_group_sum<T, kWave, Q>(w0.beg, w0.end, prod, [&](int k) { return av[k] * op.x(ci[k]); });
       }
       const int row = r + lane;
       if (row < r1) op.row(row, sys, sum, acc);

@@ -229,11 +229,52 @@ struct RowPre<Op, std::void_t<typename Op::Pre>> {
   __device__ static void row(const Op& op, int i, T sum, const type& p, double* acc) { op.row(i, sum, p, acc); }
 };
 
+// The row sums of a streamed group that exceeds the LDS: as many rows at a time
+// as fit it, their products (entry(k)) by coalesced loads; a row of more than
+// kLongRow entries is summed by the whole wave.  The sum of row l % R, whose
+// entries are beg .. end, in lane l.
+constexpr int kLongRow = 64;
+template <typename T, int R, int Q, class Entry>
+__device__ __forceinline__ T long_group_sum(int beg, int end, T* prod, Entry entry) {
+  constexpr int LPR = kWave / R;
+  constexpr uint64_t kRows = R == kWave ? ~0ull : (1ull << R) - 1;
+  const int lane = threadIdx.x & (kWave - 1), rl = lane & (R - 1), part = lane / R;
+  const uint64_t longs = __ballot(end - beg > kLongRow) & kRows;
+  T sum = T(0);
+  for (int i0 = 0; i0 < R;) {
+    const int base = __builtin_amdgcn_readlane(beg, i0);
+    const uint64_t after = longs >> i0;
+    if (after & 1) {
+      const int e = __builtin_amdgcn_readlane(end, i0);
+      T t = T(0);
+      for (int k = base + lane; k < e; k += kWave) t += entry(k);
+      t = wave_sum(t);
+      if (lane == i0) sum = t;
+      ++i0;
+      continue;
+    }
+    const int upto = after ? i0 + __ffsll((unsigned long long)after) - 1 : R;
+    const int take = __popcll(__ballot(rl >= i0 && rl < upto && end - base <= kWave * Q) & kRows);
+    const int total = __builtin_amdgcn_readlane(end, i0 + take - 1) - base;
+    T p[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) p[q] = q * kWave + lane < total ? entry(base + q * kWave + lane) : T(0);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) prod[q * kWave + lane] = p[q];
+    wave_lds_order();
+    if (rl >= i0 && rl < i0 + take)
+      for (int k = beg - base + part; k < end - base; k += LPR) sum += prod[k];
+    wave_lds_order();
+    i0 += take;
+  }
+  if constexpr (LPR == 2) sum += __shfl_xor(sum, 32, kWave);
+  return sum;
+}
+
 // CSR rows streamed through LDS.  A wave takes groups of R consecutive rows of
-// about 64 Q entries together; a larger group takes a slow path, each row
-// summed by the whole wave.  A group's entries
-// are one contiguous run, loaded coalesced, Q per lane; the products go to the
-// wave's LDS, and 64/R lanes sum each row there.  So there is no padding, no
+// about 64 Q entries together; a larger group takes several turns
+// (long_group_sum).  A group's entries are one contiguous run, loaded coalesced,
+// Q per lane; the products go to the wave's LDS, and 64/R lanes sum each row there.  So there is no padding, no
 // idle lane on short rows, and every load instruction covers whole lines.
 // What bounds it otherwise is the chain row pointers -> columns -> gathers ->
 // sum: the loop keeps three groups in flight (the gathers of one, the columns
@@ -311,18 +352,12 @@ __global__ void __launch_bounds__(kBlock) k_stream(int n, const int* __restrict_
       wave_lds_order();
       if constexpr (LPR == 2) sum += __shfl_xor(sum, 32, kWave);
     } else {
-      for (int i = 0; i < R; ++i) {
-        const int b = __builtin_amdgcn_readlane(r0.beg, i), e = __builtin_amdgcn_readlane(r0.end, i);
-        T t = T(0);
-        for (int k = b + lane; k < e; k += kWave) {
-          int c;
-          if constexpr (D16) c = r0.cbase + (int)static_cast<const int16_t*>(cols)[k];
-          else c = static_cast<const int*>(cols)[k];
-          t += av[k] * op.x(c);
-        }
-        t = wave_sum(t);
-        if (rl == i) sum = t;
-      }
+      sum = long_group_sum<T, R, Q>(r0.beg, r0.end, prod, [&](int k) {
+        int c;
+        if constexpr (D16) c = r0.cbase + (int)static_cast<const int16_t*>(cols)[k];
+        else c = static_cast<const int*>(cols)[k];
+        return av[k] * op.x(c);
+      });
     }
     if (row < n && part == 0) RowPre<Op>::row(op, row, sum, pre, acc);
     r0 = r1;

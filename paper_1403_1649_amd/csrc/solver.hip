@@ -2587,16 +2587,42 @@ void level_spmv(const Hierarchy& h, int k, const double* x, double* y, hipStream
   launch_level<double>(h.levels[k], OpSpmv<double>{Act{nullptr}, x, y}, RedCtx{nullptr, nullptr}, s);
 }
 
-// y = A x for a caller's matrix (float64)
+// y = A x for a caller's matrix (float64); lpr <= 0: by the average row a.
+// Up to kFuseCorrectionRows rows the chip is not full and a lane per entry is best
+// (40,000 rows, random columns, us after other writes: a = 14 12.8 with 16 lanes,
+// 13.4 with 8; a power law of a = 16 83 with 32, 150 with 16).  Larger matrices
+// stream their rows, by as many loads per lane as a group's entries need with some
+// to spare, which also bears rows of any length (a row of 100,000 among rows of
+// two: 1.1 ms, 5.7 by lanes; a power law of a = 14 0.32, 0.56):
+//   2^20 rows, band matrices, us after other writes
+//   a             1    2    3    4    5    7    12   15   16   20   27
+//   streamed      16   22   26   32   37   46   71   84   94   115  135
+//   lane an entry 18   21   29   33   45   50   84   95   97   154  158
+// Beyond 30 entries lanes, two entries each (33: 236 us, 277 with one).
 void spmv_f64(int n, int nnz, const int* rp, const int* ci, const double* val, const double* x, double* y,
               int lpr, hipStream_t s) {
-  RedCtx rc{nullptr, nullptr};
-  if (lpr <= 0 && n > kFuseCorrectionRows && stream_rows(n, nnz)) {
-    launch_stream<double>(n, nnz, rp, ci, val, OpSpmv<double>{Act{nullptr}, x, y}, rc, s);
+  const OpSpmv<double> op{Act{nullptr}, x, y};
+  const RedCtx rc{nullptr, nullptr};
+  const double a = (double)nnz / n;
+  if (lpr <= 0 && n > kFuseCorrectionRows && a <= 30.0) {
+    auto stream = [&](auto rows, auto loads) {
+      launch_stream_l<double, OpSpmv<double>, decltype(rows)::value, decltype(loads)::value, false>(
+          n, rp, ci, nullptr, val, op, rc, s);
+    };
+    const std::integral_constant<int, 64> r64;
+    const std::integral_constant<int, 32> r32;
+    if (a <= 2.0) stream(r64, std::integral_constant<int, 2>());
+    else if (a <= 3.75) stream(r64, std::integral_constant<int, 4>());
+    else if (a <= 4.6) stream(r64, std::integral_constant<int, 5>());
+    else if (a <= 7.5) stream(r64, std::integral_constant<int, 8>());
+    else if (a <= 15.0) stream(r32, std::integral_constant<int, 8>());
+    else if (a <= 18.5) stream(r32, std::integral_constant<int, 10>());
+    else stream(r32, std::integral_constant<int, 16>());
     return;
   }
-  if (lpr <= 0) lpr = pick_lpr(n, nnz);
-  const OpSpmv<double> op{Act{nullptr}, x, y};
+  if (lpr <= 0 && n > kFuseCorrectionRows) lpr = pick_lpr(n, nnz);
+  if (lpr <= 0)
+    for (lpr = 2; lpr < a && lpr < 64;) lpr <<= 1;
   if (lpr == 1) launch_rows_l<double, 1>(n, rp, ci, val, op, rc, s);
   else launch_rows<double>(n, lpr, rp, ci, val, op, rc, s);
 }
