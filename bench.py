@@ -693,7 +693,7 @@ def main():
             tuned["format_gb_s"] = round(fb / t_lvl / 1e9, 1)
             tuned["format_frac"] = round(fb / t_lvl / 1e9 / PEAK_HBM_GBS, 4)
         line["spmv"] = tuned
-        line["spmv_csr"] = {"kernel": "k_rows<double,L,OpSpmv<double>> (lanes from the row length)",
+        line["spmv_csr"] = {"kernel": "k_stream<double,OpSpmv<double>,R,Q,false> (CSR streamed through LDS)",
                             "gb_s": round(nbytes / t_csr / 1e9, 1), "us": round(t_csr * 1e6, 2), "bytes": nbytes,
                             "frac": round(nbytes / t_csr / 1e9 / PEAK_HBM_GBS, 4),
                             "cache": "flushed before each launch"}

@@ -383,8 +383,8 @@ int32_t amg_export_level(const amg_hierarchy* h, int32_t k, int32_t* row_ptr, in
 
 /* y = A x (the sparse mat-vec of Section 3, "axpy" there), float64, with the
  * kernel families the solve uses: lanes_per_row in {1,2,4,8,16,32,64} selects
- * the CSR kernel with that many lanes per row, 0 picks the lane count from the
- * average row length, -1 selects the sliced-ELL kernel (the matrix is
+ * the CSR kernel with that many lanes per row, 0 picks by the number of rows
+ * and the average row length (rows streamed through LDS, or a lane count), -1 selects the sliced-ELL kernel (the matrix is
  * converted into a temporary copy first; synchronises s), -2 the sliced-ELL
  * kernel reading 16-bit column offsets col - row (EINVAL when an offset lies
  * outside [-32768, 32767]; synchronises s).  Otherwise enqueue only. */
